@@ -3,11 +3,15 @@
 // matrix, Givens rotations, least-squares right-hand side, counters) on the device.
 //
 // One restart cycle is a fixed sequence of launches over all cases:
-//   cycle init (per case: idle test, g = beta e1, V_0 = r / beta) |
-//   m x [ z = P^-1 V_j ; w = A z ; classical Gram-Schmidt (2 streaming passes over V, or
-//         4 when re-orthogonalised: option "gram_schmidt" = 2) ;
-//         Givens update of column j and of g, convergence test ; V_{j+1} = w / h_{j+1,j} ] |
-//   y = H^-1 g ; x += P^-1 (V y) ; r = b - A x ; beta = |r|
+//   cycle init (per case: idle test, g = beta e1, s_0 = 1 / beta) |
+//   m x [ z = P^-1 v_j ; w = A z ; classical Gram-Schmidt (2 streaming passes over the basis, or
+//         4 when re-orthogonalised: option "gram_schmidt" = 2), its result is v_{j+1} ;
+//         Givens update of column j and of g, convergence test, s_{j+1} = 1 / h_{j+1,j} ] |
+//   y = H^-1 g ; x += P^-1 (V y) ; r = b - A x (into v_0) ; beta = |r|
+// The basis is stored unnormalised, V_i = s_i v_i with the scale s_i in the case's state: the
+// operator is linear, so the scales enter the dot products' and the update's coefficients, and no
+// pass over the vectors normalises one (k_scale_case took 9.7 us of a 0.50 ms iteration at p = 3 on
+// 256 x 256 elements, and one launch of seven at every size).
 // Per-case flags decide which cases a launch touches: a case whose Arnoldi process has
 // stopped (|g_{j+1}| <= tol |b|, breakdown, iteration cap) is skipped by the rest of the
 // cycle's Arnoldi launches; a case that did not start the cycle is skipped by its update
@@ -24,7 +28,7 @@ namespace {
 
 // layout of one case's GMRES state (doubles) for restart length m
 struct GsLayout {
-    int m, H, CS, SN, G, Y, H1, H2, NRM, BN, BETA, INVHN, SCALE0, total;
+    int m, H, CS, SN, G, Y, H1, H2, DT, SC, NRM, BN, BETA, total;   // H: column by column, m + 1 rows each
     __host__ __device__ explicit GsLayout(int m_) : m(m_) {
         H = 0;
         CS = H + (m + 1) * m;
@@ -33,12 +37,12 @@ struct GsLayout {
         Y = G + m + 1;
         H1 = Y + m;
         H2 = H1 + MAXV;
-        NRM = H2 + MAXV;
-        BN = NRM + 8;
+        DT = H2 + MAXV;
+        SC = DT + MAXV;
+        NRM = SC + m + 1;
+        BN = NRM + 1;
         BETA = BN + 1;
-        INVHN = BETA + 1;
-        SCALE0 = INVHN + 1;
-        total = ((SCALE0 + 1 + 7) / 8) * 8;
+        total = ((BETA + 1 + 7) / 8) * 8;
     }
 };
 
@@ -97,113 +101,90 @@ __global__ void k_cycle_init(Ctl k, int m) {
     if (!run) return;
     for (int i = 0; i <= m; ++i) gs[L.G + i] = 0.0;
     gs[L.G] = beta;
-    gs[L.SCALE0] = 1.0 / beta;
+    gs[L.SC] = 1.0 / beta;
 }
 
-// column j of each case's Hessenberg matrix, Givens rotations, convergence flag
-// Column j of H: the Gram-Schmidt coefficients h_0..h_j (one or two passes summed) through the
-// previous rotations.  Rows 0..j-1 are stored; the rotated row-j entry is returned.  The running
-// entry stays in a register and the inputs are read through pointers that alias nothing written,
-// so the loads of later rows need not wait for the stores of earlier ones.
-__device__ __forceinline__ double rotate_column(const double* __restrict__ h1, const double* __restrict__ h2,
-                                                const double* __restrict__ cs, const double* __restrict__ sn,
-                                                double* __restrict__ Hj, int j, int m, bool two) {
-    constexpr int CH = 8;   // rows whose inputs are loaded together
-    double a = two ? h1[0] + h2[0] : h1[0];
-    for (int i0 = 0; i0 < j; i0 += CH) {
-        double hb[CH], c8[CH], s8[CH];
-#pragma unroll
-        for (int t = 0; t < CH; ++t) {
-            const int i = i0 + t < j ? i0 + t : j - 1;   // rows past j - 1 load row j - 1 again, unused
-            const double x1 = h1[i + 1], x2 = h2[i + 1];
-            hb[t] = two ? x1 + x2 : x1;
-            c8[t] = cs[i];
-            s8[t] = sn[i];
-        }
-#pragma unroll
-        for (int t = 0; t < CH; ++t) {
-            if (i0 + t < j) {
-                Hj[(size_t)(i0 + t) * m] = c8[t] * a + s8[t] * hb[t];
-                a = -s8[t] * a + c8[t] * hb[t];
-            }
-        }
-    }
-    return a;
-}
-
-// One workgroup of 256 threads per case: the second stage of |w|^2 (the update pass's chunk
-// partials in slot 0, summed in the order of the solver's other second stages), then the Givens
-// update on thread 0.
-__global__ void __launch_bounds__(256) k_norm_givens(Ctl k, const int* __restrict__ case_chunk,
-                                                     const double* __restrict__ partial, int j, int m, int passes) {
-    __shared__ double red[256];
-    const int c = blockIdx.x;
+// One workgroup of 256 threads per case: the second stage of |v_{j+1}|^2 (the update pass's item
+// partials), then column j of H: the Gram-Schmidt coefficients h_0..h_j (one or two passes summed)
+// through the previous rotations, the new rotation, g and the convergence test.  The rotations are a
+// serial chain on thread 0; its operands are staged in LDS by all threads, so that the chain waits
+// for one round of loads and not for one every eight rows.
+__global__ void __launch_bounds__(256) k_norm_givens(Ctl k, const int* __restrict__ ufirst,
+                                                     const double* __restrict__ npart, int j, int m, int passes) {
+    __shared__ double red[4];
+    __shared__ double h[MAXV + 8], cs[MAXV + 8], sn[MAXV + 8];
+    const int c = blockIdx.x, tid = threadIdx.x;
     int* gi = k.gi + c * GI_STRIDE;
     if (gi[GI_DONE]) return;   // uniform per workgroup
     const GsLayout L(m);
     double* gs = k.gs + (size_t)c * k.gs_stride;
-    {
-        const int c0 = case_chunk[c], c1 = case_chunk[c + 1];
-        double v = 0.0;
-        for (int b = c0 + threadIdx.x; b < c1; b += blockDim.x) v += partial[(size_t)b * MAXV];
-        red[threadIdx.x] = v;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x != 0) return;
-        gs[L.NRM] = red[0];
+    if (tid <= j) {
+        h[tid] = passes == 2 ? gs[L.H1 + tid] + gs[L.H2 + tid] : gs[L.H1 + tid];
+        cs[tid] = gs[L.CS + tid];   // (row j is not used)
+        sn[tid] = gs[L.SN + tid];
     }
-    double* H = gs + L.H;
-    double* cs = gs + L.CS;
-    double* sn = gs + L.SN;
-    double* g = gs + L.G;
-    const double hn = sqrt(gs[L.NRM]);
-    const double a0 = rotate_column(gs + L.H1, gs + L.H2, cs, sn, H + j, j, m, passes == 2), a1 = hn;
-    const double den = sqrt(a0 * a0 + a1 * a1);
-    cs[j] = den == 0.0 ? 1.0 : a0 / den;
-    sn[j] = den == 0.0 ? 0.0 : a1 / den;
-    H[j * m + j] = cs[j] * a0 + sn[j] * a1;
-    H[(j + 1) * m + j] = 0.0;
-    g[j + 1] = -sn[j] * g[j];
-    g[j] = cs[j] * g[j];
-    gi[GI_CYC] = j + 1;
-    gi[GI_TOTAL] += 1;
-    gs[L.INVHN] = hn > 0.0 ? 1.0 / hn : 0.0;
-    const bool conv = fabs(g[j + 1]) <= k.step[c].tol_res * gs[L.BN];
-    if (conv || !(hn > 0.0) || !isfinite(hn) || gi[GI_TOTAL] >= gi[GI_MAXIT] || j == m - 1) gi[GI_DONE] = 1;
+    double v = 0.0;
+    for (int b = ufirst[c] + tid; b < ufirst[c + 1]; b += 256) v += npart[b];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    if (tid % 64 == 0) red[tid / 64] = v;
+    __syncthreads();
+    if (tid == 0) {
+        const double hn = sqrt(red[0] + red[1] + red[2] + red[3]);
+        // rows 0..j-1: the running row-i entry a and the next row's h through rotation i
+        double a = h[0];
+        for (int i0 = 0; i0 < j; i0 += 8) {
+            double h8[8], c8[8], s8[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) { h8[t] = h[i0 + t + 1]; c8[t] = cs[i0 + t]; s8[t] = sn[i0 + t]; }
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                if (i0 + t < j) {
+                    h[i0 + t] = c8[t] * a + s8[t] * h8[t];
+                    a = -s8[t] * a + c8[t] * h8[t];
+                }
+            }
+        }
+        const double den = sqrt(a * a + hn * hn);
+        const double cj = den == 0.0 ? 1.0 : a / den, sj = den == 0.0 ? 0.0 : hn / den;
+        h[j] = cj * a + sj * hn;
+        gs[L.CS + j] = cj;
+        gs[L.SN + j] = sj;
+        const double gj = gs[L.G + j], gn = -sj * gj;
+        gs[L.G + j + 1] = gn;
+        gs[L.G + j] = cj * gj;
+        gi[GI_CYC] = j + 1;
+        const int total = gi[GI_TOTAL] + 1;
+        gi[GI_TOTAL] = total;
+        gs[L.SC + j + 1] = hn > 0.0 ? 1.0 / hn : 0.0;
+        const bool conv = fabs(gn) <= k.step[c].tol_res * gs[L.BN];
+        if (conv || !(hn > 0.0) || !isfinite(hn) || total >= gi[GI_MAXIT] || j == m - 1) gi[GI_DONE] = 1;
+    }
+    __syncthreads();
+    if (tid <= j) gs[L.H + (size_t)j * (m + 1) + tid] = h[tid];
 }
 
-// y = H^-1 g on the iterations of this cycle
-__global__ void k_backsub(Ctl k, int m) {
-    const int c = case_index();
-    if (c >= k.n) return;
+// y = H^-1 g on the iterations of this cycle, times the scales of the basis vectors: one workgroup
+// per case, thread q holding row q.  Column by column from the last, each column's loads issued one
+// step ahead (one thread walking the rows took 205 us at m = 150).
+__global__ void __launch_bounds__(256) k_backsub(Ctl k, int m) {
+    __shared__ double ys[MAXV];
+    const int c = blockIdx.x, q = threadIdx.x;
     const int* gi = k.gi + c * GI_STRIDE;
-    if (gi[GI_IDLE]) return;
+    if (gi[GI_IDLE]) return;   // uniform per workgroup
     const GsLayout L(m);
     double* gs = k.gs + (size_t)c * k.gs_stride;
     const int jd = gi[GI_CYC];
     const double* H = gs + L.H;
-    double* y = gs + L.Y;
+    double g = q < jd ? gs[L.G + q] : 0.0;
+    double hn = q < jd ? H[(size_t)(jd - 1) * (m + 1) + q] : 0.0;
     for (int i = jd - 1; i >= 0; --i) {
-        double s = gs[L.G + i];
-        // eight terms' loads a pass, subtracted in order (past jd - 1: reload jd - 1, unused)
-        for (int q0 = i + 1; q0 < jd; q0 += 8) {
-            double h8[8], y8[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int q = q0 + u < jd ? q0 + u : jd - 1;
-                h8[u] = H[i * m + q];
-                y8[u] = y[q];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (q0 + u < jd) s -= h8[u] * y8[u];
-        }
-        y[i] = s / H[i * m + i];
+        const double hi = hn;
+        if (i > 0 && q < i) hn = H[(size_t)(i - 1) * (m + 1) + q];
+        if (q == i) ys[i] = g / hi;
+        __syncthreads();
+        if (q < i) g -= hi * ys[i];
     }
-    for (int i = jd; i < m; ++i) y[i] = 0.0;
+    if (q < m) gs[L.Y + q] = q < jd ? ys[q] * gs[L.SC + q] : 0.0;
 }
 
 // beta = |r| after the update; a non-finite beta retires the case; summary for the host
@@ -240,62 +221,16 @@ struct Vec {
     int flag;   // skip flag
 };
 
+// 1024 entries to a workgroup pass
+static_assert(CHUNK % 1024 == 0, "a pass of the vector kernels lies in one chunk");
 #define FR_CHUNKS(vc, ...)                                                                                \
-    for (int ch = blockIdx.x; ch < (vc).nchunks; ch += gridDim.x) {                                       \
-        const int c = (vc).chunk_case[ch];                                                                 \
+    for (long long w_ = blockIdx.x; w_ < (long long)(vc).nchunks * (CHUNK / 1024); w_ += gridDim.x) {      \
+        const int c = (vc).chunk_case[w_ / (CHUNK / 1024)];                                                \
         if ((vc).gi[c * GI_STRIDE + (vc).flag]) continue;                                                  \
-        for (size_t t = (size_t)ch * CHUNK + threadIdx.x; t < (size_t)(ch + 1) * CHUNK; t += blockDim.x) { \
+        for (size_t t = (size_t)w_ * 1024 + threadIdx.x; t < (size_t)(w_ + 1) * 1024; t += blockDim.x) {   \
             __VA_ARGS__                                                                                    \
         }                                                                                                  \
     }
-
-// out = s_c * in, s_c = gs[c * stride + field]; launched with 256 threads
-static_assert(CHUNK % (4 * 256) == 0, "k_scale_case covers a chunk in passes of 4 x 256 entries");
-__global__ void k_scale_case(Vec vc, const double* __restrict__ in, double* __restrict__ out, const double* gs,
-                             int stride, int field) {
-    for (int ch = blockIdx.x; ch < vc.nchunks; ch += gridDim.x) {
-        const int c = vc.chunk_case[ch];
-        if (vc.gi[c * GI_STRIDE + vc.flag]) continue;
-        const double a = gs[(size_t)c * stride + field];
-        // four entries a pass, loaded before the first store (CHUNK is a multiple of 4 blockDim)
-        for (size_t t = (size_t)ch * CHUNK + threadIdx.x; t < (size_t)(ch + 1) * CHUNK; t += 4 * blockDim.x) {
-            double x[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) x[k] = in[t + (size_t)k * blockDim.x];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) out[t + (size_t)k * blockDim.x] = a * x[k];
-        }
-    }
-}
-
-// out = sum_{i < cyc_c} y_c[i] V_i (launched with 256 threads: one per coefficient)
-static_assert(MAXV <= 256, "k_combine_case stages one coefficient per thread");
-__global__ void k_combine_case(Vec vc, const double* __restrict__ V, size_t ldv, const double* gs, int stride,
-                               int yfield, double* __restrict__ out) {
-    __shared__ double y[MAXV];
-    for (int ch = blockIdx.x; ch < vc.nchunks; ch += gridDim.x) {
-        const int c = vc.chunk_case[ch];
-        if (vc.gi[c * GI_STRIDE + vc.flag]) continue;
-        const int nv = vc.gi[c * GI_STRIDE + GI_CYC];
-        __syncthreads();
-        if ((int)threadIdx.x < MAXV) y[threadIdx.x] = (int)threadIdx.x < nv ? gs[(size_t)c * stride + yfield + threadIdx.x] : 0.0;
-        __syncthreads();
-        for (size_t t = (size_t)ch * CHUNK + threadIdx.x; t < (size_t)(ch + 1) * CHUNK; t += blockDim.x) {
-            double s = 0.0;
-            int i = 0;
-            // 16 basis entries loaded before any is used, added in order
-            for (; i + 16 <= nv; i += 16) {
-                double x[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) x[u] = V[(size_t)(i + u) * ldv + t];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) s += y[i + u] * x[u];
-            }
-            for (; i < nv; ++i) s += y[i] * V[i * ldv + t];
-            out[t] = s;
-        }
-    }
-}
 
 __global__ void k_add(Vec vc, const double* __restrict__ z, double* __restrict__ x) { FR_CHUNKS(vc, x[t] += z[t];) }
 __global__ void k_sub(Vec vc, const double* __restrict__ b, const double* __restrict__ w, double* __restrict__ r) {
@@ -304,7 +239,10 @@ __global__ void k_sub(Vec vc, const double* __restrict__ b, const double* __rest
 __global__ void k_fill(Vec vc, double v, double* __restrict__ x) { FR_CHUNKS(vc, x[t] = v;) }
 __global__ void k_copy(Vec vc, const double* __restrict__ a, double* __restrict__ b) { FR_CHUNKS(vc, b[t] = a[t];) }
 
-unsigned vgrid(const Solver& sv) { return (unsigned)(sv.nchunks < 8192 ? sv.nchunks : 8192); }
+unsigned vgrid(const Solver& sv) {
+    const long long g = (long long)sv.nchunks * (CHUNK / 1024);
+    return (unsigned)(g < 8192 ? g : 8192);
+}
 unsigned cgrid(const Solver& sv) { return (unsigned)((sv.n + 63) / 64); }
 
 Ctl ctl(const Solver& sv) { return Ctl{sv.d_gs, sv.gs_stride, sv.d_gi, sv.d_step, sv.d_sum, sv.n}; }
@@ -326,64 +264,76 @@ fr_status bdf_op(const Solver& sv, const double* q, const double* v, double* Av,
     return solver_fused(sv, MODE_LIN, a, s);
 }
 
-// the launches of one cycle (enqueued eagerly or under capture)
-fr_status enqueue_cycle(Solver& sv, int m, hipStream_t s) {
+// the launches of one cycle (enqueued eagerly or under capture): the start, the Arnoldi steps, the end
+fr_status enqueue_start(Solver& sv, int m, hipStream_t s) {
+    hipLaunchKernelGGL(k_cycle_init, dim3(cgrid(sv)), dim3(64), 0, s, ctl(sv), m);
+    FR_HIP(hipGetLastError());
+    return FR_OK;
+}
+
+fr_status enqueue_arnoldi(Solver& sv, int m, int j, hipStream_t s) {
+    const size_t N = sv.Ntot;
+    const GsLayout L(m);
+    const double* q = sv.d_q;
+    double* w = wv(sv, WW);
+    double* z = wv(sv, WZ);
+    double* V = sv.d_V;
+    double* vj = V + (size_t)j * N;
+    double* vn = vj + N;
+    FR_TRY(precond_apply(sv, vj, z, bdf_args(sv, q), sv.d_gi, GI_DONE, s));
+    FR_TRY(bdf_op(sv, q, z, w, GI_DONE, s));
+    // classical Gram-Schmidt: h = V^T w, w -= V h (and once more when re-orthogonalising); each pass
+    // over the basis walks its items the other way from the pass before it
+    const GsRef g1{sv.d_gs, sv.gs_stride, L.DT, L.SC, L.H1, j, 1};
+    FR_TRY(la_dots(sv, V, N, j + 1, w, g1, 0, sv.d_gi, GI_DONE, s));
+    if (sv.gs_passes == 2) {
+        const GsRef g2{sv.d_gs, sv.gs_stride, L.DT, L.SC, L.H2, j, 0};
+        if (sv.fuse_gs && j + 1 <= 32) {
+            FR_TRY(la_update_dots(sv, V, N, j + 1, w, vn, g1, 0, sv.d_gi, GI_DONE, s, true));
+        } else {
+            FR_TRY(la_update(sv, V, N, j + 1, w, vn, false, g1, 0, sv.d_gi, GI_DONE, s, true));
+            FR_TRY(la_dots(sv, V, N, j + 1, vn, g2, 1, sv.d_gi, GI_DONE, s));
+        }
+        FR_TRY(la_update(sv, V, N, j + 1, vn, vn, true, g2, 1, sv.d_gi, GI_DONE, s, !sv.fuse_gs));
+    } else {
+        FR_TRY(la_update(sv, V, N, j + 1, w, vn, true, g1, 0, sv.d_gi, GI_DONE, s, true));
+    }
+    // |v_{j+1}|^2's second stage and the Givens update in one launch
+    hipLaunchKernelGGL(k_norm_givens, dim3(sv.n), dim3(256), 0, s, ctl(sv), sv.d_ufirst, part_norm(sv), j, m,
+                       sv.gs_passes);
+    FR_HIP(hipGetLastError());
+    return FR_OK;
+}
+
+fr_status enqueue_end(Solver& sv, int m, hipStream_t s) {
     const size_t N = sv.Ntot;
     const GsLayout L(m);
     const double* q = sv.d_q;
     const double* b = wv(sv, WB);
     double* x = wv(sv, WDQ);
-    double* r = wv(sv, WRES);
     double* w = wv(sv, WW);
     double* z = wv(sv, WZ);
-    double* V = sv.d_V;
-    double* gs = sv.d_gs;
-    const int gst = sv.gs_stride;
+    double* r = sv.d_V;   // the residual is the next cycle's v_0
     const Ctl k = ctl(sv);
-    hipLaunchKernelGGL(k_cycle_init, dim3(cgrid(sv)), dim3(64), 0, s, k, m);
+    hipLaunchKernelGGL(k_backsub, dim3(sv.n), dim3(256), 0, s, k, m);
     FR_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_scale_case, dim3(vgrid(sv)), dim3(256), 0, s, vec(sv, GI_DONE), r, V, gs, gst, L.SCALE0);
-    FR_HIP(hipGetLastError());
-    for (int j = 0; j < m; ++j) {
-        double* vj = V + (size_t)j * N;
-        FR_TRY(precond_apply(sv, vj, z, bdf_args(sv, q), sv.d_gi, GI_DONE, s));
-        FR_TRY(bdf_op(sv, q, z, w, GI_DONE, s));
-        // classical Gram-Schmidt: h = V^T w, w -= V h (and once more when re-orthogonalising)
-        FR_TRY(la_krylov(sv, V, N, 0, nullptr, 0, j + 1, w, nullptr, false, false, gs + L.H1, gst, sv.d_gi, GI_DONE, s));
-        // each pass over the basis walks its chunks the other way from the pass before it
-        if (sv.gs_passes == 2) {
-            FR_TRY(la_krylov(sv, V, N, j + 1, gs + L.H1, gst, j + 1, w, w, false, false, gs + L.H2, gst, sv.d_gi,
-                             GI_DONE, s, sv.fuse_gs));
-            FR_TRY(la_krylov(sv, V, N, j + 1, gs + L.H2, gst, 0, w, w, true, false, nullptr, gst, sv.d_gi,
-                             GI_DONE, s, !sv.fuse_gs));
-        } else {
-            FR_TRY(la_krylov(sv, V, N, j + 1, gs + L.H1, gst, 0, w, w, true, false, nullptr, gst, sv.d_gi,
-                             GI_DONE, s, true));
-        }
-        // |w|^2's second stage and the Givens update in one launch
-        hipLaunchKernelGGL(k_norm_givens, dim3(sv.n), dim3(256), 0, s, k, sv.d_case_chunk, sv.d_part, j, m,
-                           sv.gs_passes);
-        FR_HIP(hipGetLastError());
-        if (j + 1 < m) {
-            hipLaunchKernelGGL(k_scale_case, dim3(vgrid(sv)), dim3(256), 0, s, vec(sv, GI_DONE), w,
-                               V + (size_t)(j + 1) * N, gs, gst, L.INVHN);
-            FR_HIP(hipGetLastError());
-        }
-    }
-    hipLaunchKernelGGL(k_backsub, dim3(cgrid(sv)), dim3(64), 0, s, k, m);
-    FR_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_combine_case, dim3(vgrid(sv)), dim3(256), 0, s, vec(sv, GI_IDLE), V, N, gs, gst, L.Y, w);
-    FR_HIP(hipGetLastError());
+    FR_TRY(la_combine(sv, sv.d_V, N, sv.d_gs, sv.gs_stride, L.Y, w, sv.d_gi, GI_IDLE, s));
     FR_TRY(precond_apply(sv, w, z, bdf_args(sv, q), sv.d_gi, GI_IDLE, s));
     hipLaunchKernelGGL(k_add, dim3(vgrid(sv)), dim3(256), 0, s, vec(sv, GI_IDLE), z, x);
     FR_HIP(hipGetLastError());
     FR_TRY(bdf_op(sv, q, x, w, GI_IDLE, s));
     hipLaunchKernelGGL(k_sub, dim3(vgrid(sv)), dim3(256), 0, s, vec(sv, GI_IDLE), b, w, r);
     FR_HIP(hipGetLastError());
-    FR_TRY(la_krylov(sv, r, N, 0, nullptr, 0, 0, r, nullptr, true, false, gs + L.NRM, gst, sv.d_gi, GI_IDLE, s));
+    FR_TRY(la_norm(sv, r, false, sv.d_gs + L.NRM, sv.gs_stride, sv.d_gi, GI_IDLE, s));
     hipLaunchKernelGGL(k_cycle_end, dim3(cgrid(sv)), dim3(64), 0, s, k, m);
     FR_HIP(hipGetLastError());
     return FR_OK;
+}
+
+fr_status enqueue_cycle(Solver& sv, int m, hipStream_t s) {
+    FR_TRY(enqueue_start(sv, m, s));
+    for (int j = 0; j < m; ++j) FR_TRY(enqueue_arnoldi(sv, m, j, s));
+    return enqueue_end(sv, m, s);
 }
 
 // ---- Newton-level kernels
@@ -441,10 +391,10 @@ __global__ void k_newton_check(Ctl k, int m, int it) {
 
 // q -= dq for the cases whose step k_newton_check undid
 __global__ void k_reject_restore(Vec vc, const double* __restrict__ dq, double* __restrict__ q) {
-    for (int ch = blockIdx.x; ch < vc.nchunks; ch += gridDim.x) {
-        const int c = vc.chunk_case[ch];
+    for (long long w = blockIdx.x; w < (long long)vc.nchunks * (CHUNK / 1024); w += gridDim.x) {
+        const int c = vc.chunk_case[w / (CHUNK / 1024)];
         if (!vc.gi[c * GI_STRIDE + GI_REJECT]) continue;
-        for (size_t t = (size_t)ch * CHUNK + threadIdx.x; t < (size_t)(ch + 1) * CHUNK; t += blockDim.x) q[t] -= dq[t];
+        for (size_t t = (size_t)w * 1024 + threadIdx.x; t < (size_t)(w + 1) * 1024; t += blockDim.x) q[t] -= dq[t];
     }
 }
 
@@ -498,10 +448,9 @@ fr_status gmres_device(Solver& sv, int m, int prec, int max_it, hipStream_t s) {
     FR_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_fill, dim3(vgrid(sv)), dim3(256), 0, s, vec(sv, GI_NDONE), 0.0, wv(sv, WDQ));
     FR_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_copy, dim3(vgrid(sv)), dim3(256), 0, s, vec(sv, GI_NDONE), wv(sv, WB), wv(sv, WRES));
+    hipLaunchKernelGGL(k_copy, dim3(vgrid(sv)), dim3(256), 0, s, vec(sv, GI_NDONE), wv(sv, WB), sv.d_V);
     FR_HIP(hipGetLastError());
-    FR_TRY(la_krylov(sv, wv(sv, WB), sv.Ntot, 0, nullptr, 0, 0, wv(sv, WB), nullptr, true, false, sv.d_gs + L.NRM,
-                     sv.gs_stride, sv.d_gi, GI_NDONE, s));
+    FR_TRY(la_norm(sv, wv(sv, WB), false, sv.d_gs + L.NRM, sv.gs_stride, sv.d_gi, GI_NDONE, s));
     hipLaunchKernelGGL(k_gm_norm0, dim3(cgrid(sv)), dim3(64), 0, s, k, m);
     FR_HIP(hipGetLastError());
 
@@ -582,8 +531,7 @@ fr_status solver_newton(Solver& sv, const fr_step_opts* o, hipStream_t s) {
         a.fpack = sv.d_fpack; a.spack = sv.d_spack;
         FR_TRY(solver_fused(sv, MODE_PREP, a, s));
         FR_TRY(launch_bdf_rhs(sv, sv.d_q, wv(sv, WQN), wv(sv, WQNM1), wv(sv, WR), wv(sv, WB), sv.d_gi, s));
-        FR_TRY(la_krylov(sv, wv(sv, WB), sv.Ntot, 0, nullptr, 0, 0, wv(sv, WB), nullptr, true, true, sv.d_gs + L.NRM,
-                         sv.gs_stride, sv.d_gi, GI_NDONE, s));
+        FR_TRY(la_norm(sv, wv(sv, WB), true, sv.d_gs + L.NRM, sv.gs_stride, sv.d_gi, GI_NDONE, s));
         hipLaunchKernelGGL(k_newton_check, dim3(cgrid(sv)), dim3(64), 0, s, k, o->krylov, it);
         FR_HIP(hipGetLastError());
         if (sv.reject_on) {

@@ -110,7 +110,7 @@ enum { S_BN = 0, S_BETA, S_TOTAL, S_MORE,      // GMRES: |b|, |r|, iterations, w
        SUM_STRIDE = 16 };
 
 // work vectors of a step inside Solver::d_w
-enum { WB = 0, WR, WQN, WQNM1, WRES, WW, WZ, WDQ, NWORK };
+enum { WB = 0, WR, WQN, WQNM1, WW, WZ, WDQ, NWORK };
 
 // per-case integer state of a step: gi[case * GI_STRIDE + field]
 enum { GI_DONE = 0,   // Arnoldi of the current cycle stopped (skip flag of the cycle's kernels)
@@ -194,6 +194,15 @@ struct Group {
     }
 };
 
+// Unit of the segmented reductions: entries [start, start + len) of the concatenated vector,
+// all of one case.  The partition of a case depends on its own size only, so a case reduces to
+// the same bits alone and in a batch.
+struct Item {
+    int c;
+    unsigned len;
+    unsigned long long start;
+};
+
 struct Solver;
 
 struct fr_ctx_s {
@@ -241,7 +250,13 @@ struct Solver {
     int nchunks = 0;
     CaseDev* d_cases = nullptr;
     int* d_chunk_case = nullptr;           // [nchunks]
-    int* d_case_chunk = nullptr;           // [n + 1] first chunk of each case
+    // items of the dot products and of the updates (with the norm), case by case
+    Item* d_ditem = nullptr;
+    Item* d_uitem = nullptr;
+    int nditem = 0, nuitem = 0;
+    int* d_dfirst = nullptr;               // [n + 1] first dot item of each case
+    int* d_ufirst = nullptr;               // [n + 1] first update item of each case
+    bool all_small = false;                // every case is small (is_small)
     std::vector<Group> groups;
     int device = 0;
     // preconditioner
@@ -268,7 +283,7 @@ struct Solver {
     double* d_gs = nullptr;                // per-case GMRES state [n][gs_stride]
     int gs_stride = 0;
     int* d_gi = nullptr;                   // per-case flags [n][GI_STRIDE]
-    double* d_part = nullptr;              // reduction partials [nchunks][MAXV]
+    double* d_part = nullptr;              // reduction partials: part_dots(0), part_dots(1), part_norm()
     CaseStep* d_step = nullptr;            // [n]
     double* d_sum = nullptr;               // per-case summary [n][SUM_STRIDE]
     double* d_fpack = nullptr;             // linearisation packs of the Newton iterate
@@ -295,6 +310,20 @@ struct fr_batch_s {
 
 constexpr int CHUNK = 4096;   // alignment of case vectors; unit of the segmented reductions
 constexpr int MAXV = 160;     // max vectors in one multi-dot: Krylov dimension up to MAXV - 4
+
+// A small case: its few dot items let every workgroup that needs a dot product sum the partials
+// itself, in place of a launch of the second stage between the dots and the update.
+constexpr size_t SMALL_N = 65536;
+constexpr int SMALL_ITEMS = 16;
+inline __host__ __device__ bool is_small(size_t N) { return N <= SMALL_N; }
+
+// two sets of dot partials [MAXV][nditem] (the re-orthogonalising pass reads one while it writes
+// the other), then the norm partials [max(nuitem, nditem)]
+inline double* part_dots(const Solver& sv, int k) { return sv.d_part + (size_t)k * MAXV * sv.nditem; }
+inline double* part_norm(const Solver& sv) { return sv.d_part + (size_t)2 * MAXV * sv.nditem; }
+inline size_t part_doubles(const Solver& sv) {
+    return (size_t)2 * MAXV * sv.nditem + (size_t)(sv.nuitem > sv.nditem ? sv.nuitem : sv.nditem);
+}
 
 // error handling
 void fr_set_error(const std::string& s);
@@ -367,15 +396,36 @@ fr_status launch_block_apply_ex(const Solver& sv, const double* r, const double*
 // operator described by op (its v and out are set here)
 fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op, const int* flags, int flag,
                         hipStream_t s);
-// segmented reductions over the concatenated vectors: for every case c (not skipped),
-//   w_out = w_in - sum_{i<nv_upd} coef_c[i] V_i            (coef_c = coef + c * cstride)
-//   out_c[i] = V_i . w_out (i < nv_dot), out_c[nv_dot] = |w_out|^2 (want_norm)
-// (out_c = out + c * ostride); mass_only restricts the norm to the first E Np entries.
-// rev: the update passes walk the chunks from the last to the first, so that a pass that follows
-// one over the same basis starts on the chunks still in the Infinity Cache (same results)
-fr_status la_krylov(const Solver& sv, const double* V, size_t ldv, int nv_upd, const double* coef, int cstride,
-                    int nv_dot, const double* w_in, double* w_out, bool want_norm, bool mass_only, double* out,
-                    int ostride, const int* flags, int flag, hipStream_t s, bool rev = false);
+// Gram-Schmidt over a basis whose vectors are stored unnormalised, V_i = s_i v_i, with the scales
+// s_i, the raw dot products and the coefficients in each case's GMRES state (doubles, offsets
+// below; state of case c at gs + c * stride).  The vector w = A P^-1 v_j being orthogonalised
+// carries the factor s_j of its V_j in the first pass.
+struct GsRef {
+    double* gs;
+    int stride;
+    int dt, sc, h;       // offsets: raw dots [MAXV], scales, coefficients h_i of this pass
+    int j;               // the Arnoldi step: vectors v_0 .. v_j
+    int first;           // 1: w carries s_j; 0: the re-orthogonalising pass
+};
+// For every case c (not skipped; flags / flag as everywhere):
+// raw dots v_i . w, i < nv, into partial set `set`, and for cases that are not small also into dt
+fr_status la_dots(const Solver& sv, const double* V, size_t ldv, int nv, const double* w, const GsRef& g, int set,
+                  const int* flags, int flag, hipStream_t s);
+// h_i = s_i (s_j) dot_i of partial set `set`; w_out = (s_j) w_in - sum_i h_i s_i v_i; the partials
+// of |w_out|^2 when want_norm.  The items are walked from the last to the first when rev, so that a
+// pass that follows one over the same basis starts on what is still in the Infinity Cache.
+fr_status la_update(const Solver& sv, const double* V, size_t ldv, int nv, const double* w_in, double* w_out,
+                    bool want_norm, const GsRef& g, int set, const int* flags, int flag, hipStream_t s, bool rev);
+// la_update without the norm and la_dots of its result (into set 1 - set) in one read of the basis;
+// nv <= 32; the same bits as the two
+fr_status la_update_dots(const Solver& sv, const double* V, size_t ldv, int nv, const double* w_in, double* w_out,
+                         const GsRef& g, int set, const int* flags, int flag, hipStream_t s, bool rev);
+// out = sum_i y_c[i] v_i over the cyc_c iterations of case c (y at gs + c * stride + yfield)
+fr_status la_combine(const Solver& sv, const double* V, size_t ldv, const double* gs, int stride, int yfield,
+                     double* out, const int* flags, int flag, hipStream_t s);
+// out[c * ostride] = |w|^2 (mass_only: of its first E Np entries)
+fr_status la_norm(const Solver& sv, const double* w, bool mass_only, double* out, int ostride, const int* flags,
+                  int flag, hipStream_t s);
 fr_status launch_bdf_rhs(const Solver& sv, const double* q, const double* Qn, const double* Qnm1, const double* R,
                          double* b, const int* flags, hipStream_t s);
 fr_status launch_cons(const Solver& sv, const double* q, double* Qc, const int* flags, hipStream_t s);

@@ -147,51 +147,78 @@ __global__ void __launch_bounds__(256) k_block_apply(GroupArgs ga, const Tin* __
 }
 
 // ------------------------------------------------------------------ segmented Krylov reductions
-// The solver vectors are concatenations of per-case segments aligned to CHUNK doubles;
-// every chunk belongs to one case.  First stage: one partial sum per chunk and output;
-// second stage: per case, a fixed-order tree over its chunks (deterministic).
-struct ChunkArgs {
+// The solver vectors are concatenations of per-case segments; the reductions run over items, ranges
+// of entries of one case (Item).  First stage: one partial per item and output; second stage: per
+// case, a fixed-order sum over its items (deterministic).  The padding after a case's entries
+// belongs to no item: it is neither read nor written, so a non-finite value there (a scaling by a
+// non-finite coefficient once produced some) cannot reach a dot product of a later solve.
+struct RedArgs {
     const CaseDev* cases;
-    const int* chunk_case;   // [nchunks]
-    const int* case_chunk;   // [ncase + 1]
-    int nchunks;
+    const Item* items;
+    int nitems;
     const int* flags;        // per-case skip flags or NULL
     int flag;
 };
 
-__device__ __forceinline__ bool chunk_skipped(const ChunkArgs& ca, int c) {
-    return ca.flags && ca.flags[c * GI_STRIDE + ca.flag];
+// where a workgroup finds the dot products of the previous launch
+struct DotRef {
+    const double* part;      // [MAXV][nditem]
+    int nditem;
+    const int* first;        // first dot item of each case
+};
+
+__device__ __forceinline__ bool case_skipped(const RedArgs& ra, int c) {
+    return ra.flags && ra.flags[c * GI_STRIDE + ra.flag];
+}
+__device__ __forceinline__ size_t case_size(const RedArgs& ra, int c) {
+    return (size_t)4 * ra.cases[c].E * ra.cases[c].Np;
 }
 
-// End of chunk ch within its case's entries: the padding after a case's 4 E Np entries is
-// neither read nor written by the reductions, so a non-finite value that arithmetic on the
-// padding once produced (a scaling by a non-finite coefficient) cannot reach a dot product
-// or norm of a later iteration, step or solve.
-__device__ __forceinline__ size_t case_end(const CaseDev& cd, int ch) {
-    const size_t e = cd.off + (size_t)4 * cd.E * cd.Np, ce = (size_t)(ch + 1) * CHUNK;
-    return e < ce ? e : ce;
+__device__ __forceinline__ double wave_sum(double v) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    return v;
 }
 
-// Dot products V_i . w for i in [DB*blockIdx.y, DB*blockIdx.y + DB) ∩ [0, nv), plus |w|^2 in
-// slot nv when want_norm (y-block 0 only; mass_only: first E Np entries of the case).
-// DB = 8 vectors per pass (16 measured slower: fewer workgroups, heavier reduction).
+// Sums of eight values over the wave: in three steps each lane hands half of its values to its
+// partner and keeps the other half, in three more the last value is summed over eight lanes: 10
+// exchanges instead of 48.  The sum of value wave_sum8_index(lane) is returned on the lanes with
+// lane % 8 == 0.
+__device__ __forceinline__ int wave_sum8_index(int lane) { return ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1); }
+__device__ __forceinline__ double wave_sum8(const double* a, int lane) {
+    double b[4], c[2];
+    const bool h5 = lane & 32, h4 = lane & 16, h3 = lane & 8;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = (h5 ? a[i + 4] : a[i]) + __shfl_xor(h5 ? a[i] : a[i + 4], 32, 64);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) c[i] = (h4 ? b[i + 2] : b[i]) + __shfl_xor(h4 ? b[i] : b[i + 2], 16, 64);
+    double d = (h3 ? c[1] : c[0]) + __shfl_xor(h3 ? c[0] : c[1], 8, 64);
+    d += __shfl_xor(d, 4, 64);
+    d += __shfl_xor(d, 2, 64);
+    d += __shfl_xor(d, 1, 64);
+    return d;
+}
+
+// Dot products V_i . w for i in [DB*blockIdx.y, DB*blockIdx.y + DB) ∩ [0, nv) into
+// partial[i][item], plus |w|^2 into npart[item] when it is not null (y-block 0 only; mass_only:
+// over the first E Np entries of the case).  DB = 8 vectors per pass (16 measured slower: fewer
+// workgroups, heavier reduction).
 constexpr int DB = 8;
-__global__ void __launch_bounds__(RED_THREADS) k_dots8(ChunkArgs ca, const double* __restrict__ V, size_t ldv, int nv,
-                                                       const double* __restrict__ w, int want_norm, int mass_only,
-                                                       double* __restrict__ partial) {
+__global__ void __launch_bounds__(RED_THREADS) k_dots8(RedArgs ra, const double* __restrict__ V, size_t ldv, int nv,
+                                                       const double* __restrict__ w, int mass_only,
+                                                       double* __restrict__ partial, double* __restrict__ npart) {
     __shared__ double red[RED_THREADS / 64][DB + 1];
     const int i0 = blockIdx.y * DB;
     const int cnt = nv - i0 < DB ? nv - i0 : DB;
-    const bool nrm = want_norm && blockIdx.y == 0;
+    const bool nrm = npart && blockIdx.y == 0;
     const double* Vc = V + (size_t)i0 * ldv;
     const int lane = threadIdx.x % 64, wid = threadIdx.x / 64;
-    for (int ch = blockIdx.x; ch < ca.nchunks; ch += gridDim.x) {
-        const int c = ca.chunk_case[ch];
-        if (chunk_skipped(ca, c)) continue;
-        const CaseDev& cd = ca.cases[c];
-        const size_t end = case_end(cd, ch);
+    for (int it = blockIdx.x; it < ra.nitems; it += gridDim.x) {
+        const Item im = ra.items[it];
+        if (case_skipped(ra, im.c)) continue;
+        const size_t end = im.start + im.len;
         size_t lim = end;
         if (mass_only) {
+            const CaseDev& cd = ra.cases[im.c];
             const size_t m = cd.off + (size_t)cd.E * cd.Np;
             lim = m < lim ? m : lim;
         }
@@ -199,7 +226,7 @@ __global__ void __launch_bounds__(RED_THREADS) k_dots8(ChunkArgs ca, const doubl
 #pragma unroll
         for (int i = 0; i < DB; ++i) acc[i] = 0.0;
         double nacc = 0.0;
-        for (size_t t = (size_t)ch * CHUNK + threadIdx.x; t < end; t += RED_THREADS) {
+        for (size_t t = im.start + threadIdx.x; t < end; t += RED_THREADS) {
             const double wt = w[t];
             if (cnt > 0) {
                 // all rows loaded before any is used (rows past cnt - 1 reload row cnt - 1, unused)
@@ -212,45 +239,121 @@ __global__ void __launch_bounds__(RED_THREADS) k_dots8(ChunkArgs ca, const doubl
             }
             if (nrm && t < lim) nacc += wt * wt;
         }
-        __syncthreads();   // red[] of the previous chunk consumed
-#pragma unroll
-        for (int i = 0; i < DB + 1; ++i) {
-            const bool live = (i < cnt) || (i == DB && nrm);
-            if (!live) continue;
-            double v = (i < DB) ? acc[i] : nacc;
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-            if (lane == 0) red[wid][i] = v;
+        __syncthreads();   // red[] of the previous item consumed
+        if (cnt > 0) {
+            const double v = wave_sum8(acc, lane);
+            if (lane % 8 == 0) red[wid][wave_sum8_index(lane)] = v;
+        }
+        if (nrm) {
+            const double v = wave_sum(nacc);
+            if (lane == 0) red[wid][DB] = v;
         }
         __syncthreads();
         const int k = threadIdx.x;
         if (k < cnt || (k == DB && nrm)) {
             double v = 0.0;
             for (int q = 0; q < RED_THREADS / 64; ++q) v += red[q][k];
-            partial[(size_t)ch * MAXV + (k < DB ? i0 + k : nv)] = v;
+            if (k < DB) partial[(size_t)(i0 + k) * ra.nitems + it] = v;
+            else npart[it] = v;
         }
     }
 }
 
-// w_out = w_in - sum_{i < nv} coef_c[i] V_i (coef_c = coef + c * cstride), and the partial
-// |w_out|^2 in slot 0 when want_norm
-__global__ void __launch_bounds__(RED_THREADS) k_update(ChunkArgs ca, const double* __restrict__ V, size_t ldv, int nv,
-                                                        const double* __restrict__ coef, int cstride,
-                                                        const double* w_in, double* w_out, int want_norm,
-                                                        double* __restrict__ partial, int rev) {
+// Coefficients of the update that follows a dots launch, per workgroup: cf[i] = h_i s_i with
+// h_i = s_i (s_j) (v_i . w); the workgroup of the case's first item stores the h_i.  The dot
+// products of a small case (at most SMALL_ITEMS partials each, one round of loads) are summed
+// here, those of a larger one were by k_final.  Returns the factor of w.
+__device__ __forceinline__ double update_coefs(const RedArgs& ra, const DotRef& dr, const GsRef& g, int c, int nv,
+                                               bool owner, double* cf) {
+    double* gs = g.gs + (size_t)c * g.stride;
+    const double sj = g.first ? gs[g.sc + g.j] : 1.0;
+    const int i = threadIdx.x;
+    if (i < nv) {
+        double d;
+        if (is_small(case_size(ra, c))) {
+            const int i0 = dr.first[c], n = dr.first[c + 1] - i0;
+            const double* p = dr.part + (size_t)i * dr.nditem + i0;
+            double x[SMALL_ITEMS];
+#pragma unroll
+            for (int k = 0; k < SMALL_ITEMS; ++k) x[k] = p[k < n ? k : 0];
+            d = 0.0;
+#pragma unroll
+            for (int k = 0; k < SMALL_ITEMS; ++k)
+                if (k < n) d += x[k];
+        } else {
+            d = gs[g.dt + i];
+        }
+        const double si = gs[g.sc + i], h = d * si * sj;
+        cf[i] = h * si;
+        if (owner) gs[g.h + i] = h;
+    }
+    return sj;
+}
+
+// sum_{i0 <= i < i1} cf[i] V_i(t): 16 basis entries loaded before any is used
+__device__ __forceinline__ double basis_sum(const double* __restrict__ V, size_t ldv, const double* cf, int i0, int i1,
+                                            size_t t) {
+    double s = 0.0;
+    for (int i = i0; i < i1; i += 16) {
+        double x[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = V[(size_t)(i + u < i1 ? i + u : i1 - 1) * ldv + t];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (i + u < i1) s += cf[i + u] * x[u];
+    }
+    return s;
+}
+
+// The entries of a small case's update item (64 at most), one per lane, with the vectors shared
+// out over the workgroup's waves: every wave's part of sum_i cf[i] V_i, added on wave 0 (valid
+// there).  A wave walks a quarter of a serial chain of loads that is the whole cost at these sizes.
+__device__ __forceinline__ double split_sum(const double* __restrict__ V, size_t ldv, const double* cf, int nv,
+                                            size_t t, bool live, double (*sh)[64]) {
+    constexpr int W = RED_THREADS / 64;
+    const int lane = threadIdx.x % 64, wid = threadIdx.x / 64, q = (nv + W - 1) / W;
+    const int i0 = wid * q < nv ? wid * q : nv, i1 = i0 + q < nv ? i0 + q : nv;
+    sh[wid][lane] = live ? basis_sum(V, ldv, cf, i0, i1, t) : 0.0;
+    __syncthreads();
+    double s = 0.0;
+    if (wid == 0)
+        for (int k = 0; k < W; ++k) s += sh[k][lane];
+    return s;
+}
+
+// w_out = (s_j) w_in - sum_{i < nv} h_i s_i V_i, and the partial |w_out|^2 of each item when
+// npart is not null
+__global__ void __launch_bounds__(RED_THREADS) k_update(RedArgs ra, DotRef dr, GsRef g, const double* __restrict__ V,
+                                                        size_t ldv, int nv, const double* w_in, double* w_out,
+                                                        double* __restrict__ npart, int rev) {
     __shared__ double cf[MAXV];
     __shared__ double red[RED_THREADS / 64];
+    __shared__ double sh[RED_THREADS / 64][64];
     const int lane = threadIdx.x % 64, wid = threadIdx.x / 64;
-    for (int ci = blockIdx.x; ci < ca.nchunks; ci += gridDim.x) {
-        const int ch = rev ? ca.nchunks - 1 - ci : ci;   // chunks last to first (partials by chunk)
-        const int c = ca.chunk_case[ch];
-        if (chunk_skipped(ca, c)) continue;
-        const size_t end = case_end(ca.cases[c], ch);
-        __syncthreads();   // cf[] / red[] of the previous chunk consumed
-        if ((int)threadIdx.x < MAXV) cf[threadIdx.x] = ((int)threadIdx.x < nv) ? coef[(size_t)c * cstride + threadIdx.x] : 0.0;
+    for (int ci = blockIdx.x; ci < ra.nitems; ci += gridDim.x) {
+        const int it = rev ? ra.nitems - 1 - ci : ci;   // items last to first (partials by item)
+        const Item im = ra.items[it];
+        if (case_skipped(ra, im.c)) continue;
+        const size_t end = im.start + im.len;
+        __syncthreads();   // cf[] / red[] of the previous item consumed
+        const double sj = update_coefs(ra, dr, g, im.c, nv, im.start == ra.cases[im.c].off, cf);
         __syncthreads();
         double nacc = 0.0;
-        for (size_t t = (size_t)ch * CHUNK + threadIdx.x; t < end; t += RED_THREADS) {
-            double wt = w_in[t];
+        if (npart && is_small(case_size(ra, im.c))) {
+            const size_t t = im.start + lane;
+            const double s = split_sum(V, ldv, cf, nv, t, t < end, sh);
+            if (wid != 0) continue;   // (the next item's first barrier is met by every wave)
+            if (t < end) {
+                const double wt = sj * w_in[t] - s;
+                w_out[t] = wt;
+                nacc = wt * wt;
+            }
+            nacc = wave_sum(nacc);
+            if (lane == 0) npart[it] = nacc;
+            continue;
+        }
+        for (size_t t = im.start + threadIdx.x; t < end; t += RED_THREADS) {
+            double wt = sj * w_in[t];
             int i = 0;
             // 16 basis entries loaded before any is used, summed in the groups of four below
             for (; i + 16 <= nv; i += 16) {
@@ -268,48 +371,49 @@ __global__ void __launch_bounds__(RED_THREADS) k_update(ChunkArgs ca, const doub
             w_out[t] = wt;
             nacc += wt * wt;
         }
-        if (!want_norm) continue;
-        for (int off = 32; off > 0; off >>= 1) nacc += __shfl_down(nacc, off, 64);
+        if (!npart) continue;
+        nacc = wave_sum(nacc);
         if (lane == 0) red[wid] = nacc;
         __syncthreads();
         if (threadIdx.x == 0) {
             double v = 0.0;
             for (int q = 0; q < RED_THREADS / 64; ++q) v += red[q];
-            partial[(size_t)ch * MAXV] = v;
+            npart[it] = v;
         }
     }
 }
 
 // The re-orthogonalising pass of classical Gram-Schmidt applied twice, in one read of the basis:
-// w_out = w_in - sum_{i < nv} coef_c[i] V_i (as k_update) and the partial dots V_k . w_out,
-// k < nv, of each chunk (as k_dots8 on w_out), from the basis entries already loaded for the
-// update.  The update's grouping and the reductions' order are those of the two kernels, so the
-// results are theirs bit for bit.  NV bounds nv.
+// w_out as k_update and the partial dots V_k . w_out, k < nv, of each dot item (as k_dots8 on
+// w_out), from the basis entries already loaded for the update.  The update's grouping and the
+// reductions' order are those of the two kernels, so the results are theirs bit for bit.  NV bounds
+// nv.
 template <int NV>
-__global__ void __launch_bounds__(RED_THREADS) k_update_dots(ChunkArgs ca, const double* __restrict__ V, size_t ldv,
-                                                             int nv, const double* __restrict__ coef, int cstride,
+__global__ void __launch_bounds__(RED_THREADS) k_update_dots(RedArgs ra, DotRef dr, GsRef g,
+                                                             const double* __restrict__ V, size_t ldv, int nv,
                                                              const double* w_in, double* w_out,
                                                              double* __restrict__ partial, int rev) {
     __shared__ double cf[NV];
     __shared__ double red[RED_THREADS / 64][NV];
     const int lane = threadIdx.x % 64, wid = threadIdx.x / 64;
-    for (int ci = blockIdx.x; ci < ca.nchunks; ci += gridDim.x) {
-        const int ch = rev ? ca.nchunks - 1 - ci : ci;   // chunks last to first (partials by chunk)
-        const int c = ca.chunk_case[ch];
-        if (chunk_skipped(ca, c)) continue;
-        const size_t end = case_end(ca.cases[c], ch);
-        __syncthreads();   // cf[] / red[] of the previous chunk consumed
-        if ((int)threadIdx.x < NV) cf[threadIdx.x] = ((int)threadIdx.x < nv) ? coef[(size_t)c * cstride + threadIdx.x] : 0.0;
+    for (int ci = blockIdx.x; ci < ra.nitems; ci += gridDim.x) {
+        const int it = rev ? ra.nitems - 1 - ci : ci;   // items last to first (partials by item)
+        const Item im = ra.items[it];
+        if (case_skipped(ra, im.c)) continue;
+        const size_t end = im.start + im.len;
+        __syncthreads();   // cf[] / red[] of the previous item consumed
+        const double sj = update_coefs(ra, dr, g, im.c, nv, im.start == ra.cases[im.c].off, cf);
+        if ((int)threadIdx.x >= nv && (int)threadIdx.x < NV) cf[threadIdx.x] = 0.0;
         __syncthreads();
         double acc[NV];
 #pragma unroll
         for (int k = 0; k < NV; ++k) acc[k] = 0.0;
-        for (size_t t = (size_t)ch * CHUNK + threadIdx.x; t < end; t += RED_THREADS) {
+        for (size_t t = im.start + threadIdx.x; t < end; t += RED_THREADS) {
             // all rows loaded before any is used (rows past nv - 1 reload row nv - 1, unused)
             double x[NV];
 #pragma unroll
             for (int k = 0; k < NV; ++k) x[k] = V[(size_t)(k < nv ? k : nv - 1) * ldv + t];
-            double wt = w_in[t];
+            double wt = sj * w_in[t];
             const int n4 = nv & ~3;
 #pragma unroll
             for (int k = 0; k < NV; k += 4)
@@ -323,52 +427,93 @@ __global__ void __launch_bounds__(RED_THREADS) k_update_dots(ChunkArgs ca, const
                 if (k < nv) acc[k] += x[k] * wt;
         }
 #pragma unroll
-        for (int k = 0; k < NV; ++k) {
+        for (int k = 0; k < NV; k += 8) {
             if (k >= nv) continue;
-            double v = acc[k];
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-            if (lane == 0) red[wid][k] = v;
+            const double v = wave_sum8(acc + k, lane);
+            if (lane % 8 == 0) red[wid][k + wave_sum8_index(lane)] = v;
         }
         __syncthreads();
         const int k = threadIdx.x;
         if (k < nv) {
             double v = 0.0;
             for (int q = 0; q < RED_THREADS / 64; ++q) v += red[q][k];
-            partial[(size_t)ch * MAXV + k] = v;
+            partial[(size_t)k * ra.nitems + it] = v;
         }
     }
 }
 
-// out_c[i] = sum over the chunks of case c of partial[chunk][i]; grid (ncase, nout)
-__global__ void __launch_bounds__(256) k_final(ChunkArgs ca, const double* __restrict__ partial,
-                                               double* __restrict__ out, int ostride) {
-    __shared__ double red[256];
-    const int c = blockIdx.x, i = blockIdx.y;
-    if (chunk_skipped(ca, c)) return;
-    const int c0 = ca.case_chunk[c], c1 = ca.case_chunk[c + 1];
-    double v = 0.0;
-    for (int b = c0 + threadIdx.x; b < c1; b += blockDim.x) v += partial[(size_t)b * MAXV + i];
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+// out = sum_{i < cyc_c} y_c[i] V_i
+__global__ void __launch_bounds__(RED_THREADS) k_combine(RedArgs ra, const double* __restrict__ V, size_t ldv,
+                                                         const double* gs, int stride, int yfield,
+                                                         double* __restrict__ out) {
+    __shared__ double y[MAXV];
+    __shared__ double sh[RED_THREADS / 64][64];
+    const int lane = threadIdx.x % 64, wid = threadIdx.x / 64;
+    for (int it = blockIdx.x; it < ra.nitems; it += gridDim.x) {
+        const Item im = ra.items[it];
+        if (case_skipped(ra, im.c)) continue;
+        const int nv = ra.flags[im.c * GI_STRIDE + GI_CYC];
+        const size_t end = im.start + im.len;
         __syncthreads();
+        if ((int)threadIdx.x < nv) y[threadIdx.x] = gs[(size_t)im.c * stride + yfield + threadIdx.x];
+        __syncthreads();
+        if (is_small(case_size(ra, im.c))) {
+            const size_t t = im.start + lane;
+            const double s = split_sum(V, ldv, y, nv, t, t < end, sh);
+            if (wid == 0 && t < end) out[t] = s;
+            continue;
+        }
+        for (size_t t = im.start + threadIdx.x; t < end; t += RED_THREADS) out[t] = basis_sum(V, ldv, y, 0, nv, t);
     }
-    if (threadIdx.x == 0) out[(size_t)c * ostride + i] = red[0];
+}
+
+// dt_c[i] = sum over the dot items of case c of part[i][item], for the cases that are not small;
+// grid (ncase, nv)
+__device__ __forceinline__ double items_sum(const double* __restrict__ p, int i0, int i1, double* red) {
+    double v = 0.0;
+    for (int b = i0 + threadIdx.x; b < i1; b += 256) v += p[b];
+    v = wave_sum(v);
+    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = v;
+    __syncthreads();
+    return red[0] + red[1] + red[2] + red[3];
+}
+__global__ void __launch_bounds__(256) k_final(RedArgs ra, DotRef dr, GsRef g) {
+    __shared__ double red[4];
+    const int c = blockIdx.x, i = blockIdx.y;
+    if (case_skipped(ra, c) || is_small(case_size(ra, c))) return;
+    const double v = items_sum(dr.part + (size_t)i * dr.nditem, dr.first[c], dr.first[c + 1], red);
+    if (threadIdx.x == 0) g.gs[(size_t)c * g.stride + g.dt + i] = v;
+}
+// out_c = sum over the items of case c of npart[item]
+__global__ void __launch_bounds__(256) k_final_norm(RedArgs ra, const double* __restrict__ npart,
+                                                    const int* __restrict__ first, double* __restrict__ out,
+                                                    int ostride) {
+    __shared__ double red[4];
+    const int c = blockIdx.x;
+    if (case_skipped(ra, c)) return;
+    const double v = items_sum(npart, first[c], first[c + 1], red);
+    if (threadIdx.x == 0) out[(size_t)c * ostride] = v;
 }
 
 // ------------------------------------------------------------------ pointwise physics per case
-// Walk the chunks that hold solution points of the first variable of each case: point
-// t of case c covers entries v * E Np + t, v = 0..3.
+// The points of every case, 256 to a workgroup: chunk ch, part sub of it.  Point t of case c covers
+// entries v * E Np + t, v = 0..3, so the chunks past the first variable's have none.
+struct ChunkArgs {
+    const CaseDev* cases;
+    const int* chunk_case;   // [nchunks]
+    int nchunks;
+    const int* flags;        // per-case skip flags or NULL
+    int flag;
+};
 #define FR_POINT_LOOP(ca, ...)                                                                  \
-    for (int ch = blockIdx.x; ch < (ca).nchunks; ch += gridDim.x) {                             \
+    for (long long w_ = blockIdx.x; w_ < (long long)(ca).nchunks * (CHUNK / 256); w_ += gridDim.x) { \
+        const int ch = (int)(w_ / (CHUNK / 256)), sub = (int)(w_ % (CHUNK / 256));               \
         const int c = (ca).chunk_case[ch];                                                       \
-        if (chunk_skipped((ca), c)) continue;                                                    \
+        if ((ca).flags && (ca).flags[c * GI_STRIDE + (ca).flag]) continue;                       \
         const CaseDev& cd = (ca).cases[c];                                                       \
         const size_t EN = (size_t)cd.E * cd.Np;                                                  \
-        const size_t r0 = (size_t)ch * CHUNK - cd.off;                                           \
-        if (r0 >= EN) continue;                                                                  \
-        for (size_t t = r0 + threadIdx.x; t < r0 + CHUNK && t < EN; t += blockDim.x) {           \
+        const size_t t = (size_t)ch * CHUNK - cd.off + (size_t)sub * 256 + threadIdx.x;          \
+        if (t < EN) {                                                                            \
             const size_t base = cd.off + t;                                                      \
             __VA_ARGS__                                                                          \
         }                                                                                        \
@@ -414,19 +559,21 @@ __global__ void k_cons_nm1(ChunkArgs ca, const CaseStep* __restrict__ st, double
 }
 
 ChunkArgs chunk_args(const Solver& sv, const int* flags, int flag) {
-    ChunkArgs ca;
-    ca.cases = sv.d_cases;
-    ca.chunk_case = sv.d_chunk_case;
-    ca.case_chunk = sv.d_case_chunk;
-    ca.nchunks = sv.nchunks;
-    ca.flags = flags;
-    ca.flag = flag;
-    return ca;
+    return ChunkArgs{sv.d_cases, sv.d_chunk_case, sv.nchunks, flags, flag};
 }
 
-unsigned chunk_grid(const Solver& sv) {
-    return (unsigned)(sv.nchunks < MAX_GRID ? sv.nchunks : MAX_GRID);
+unsigned point_grid(const Solver& sv) {
+    const long long g = (long long)sv.nchunks * (CHUNK / 256);
+    return (unsigned)(g < MAX_GRID ? g : MAX_GRID);
 }
+
+RedArgs dot_args(const Solver& sv, const int* flags, int flag) {
+    return RedArgs{sv.d_cases, sv.d_ditem, sv.nditem, flags, flag};
+}
+RedArgs upd_args(const Solver& sv, const int* flags, int flag) {
+    return RedArgs{sv.d_cases, sv.d_uitem, sv.nuitem, flags, flag};
+}
+unsigned item_grid(int nitems) { return (unsigned)(nitems < MAX_GRID ? nitems : MAX_GRID); }
 
 // the tiles of a group at a tile width; color >= 0: the tiles over the members' elements of
 // that colour (pfx null when a table is missing)
@@ -598,74 +745,93 @@ fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op,
     return FR_OK;
 }
 
-fr_status la_krylov(const Solver& sv, const double* V, size_t ldv, int nv_upd, const double* coef, int cstride,
-                    int nv_dot, const double* w_in, double* w_out, bool want_norm, bool mass_only, double* out,
-                    int ostride, const int* flags, int flag, hipStream_t s, bool rev) {
-    if (nv_upd > MAXV - 1 || nv_dot > MAXV - 1) { fr_set_error("too many Krylov vectors"); return FR_EINVAL; }
-    if (mass_only && nv_upd > 0) { fr_set_error("mass-row norm only on a plain norm pass"); return FR_EINVAL; }
-    const ChunkArgs ca = chunk_args(sv, flags, flag);
-    double* partial = sv.d_part;
-    const unsigned grid = chunk_grid(sv);
-    const double* w = w_in;
-    if (sv.fuse_gs && nv_upd > 0 && nv_dot == nv_upd && w_out && !want_norm && !mass_only && nv_upd <= 32) {
-        // update and re-orthogonalising dots share one read of the basis
-        if (nv_upd <= 8)
-            hipLaunchKernelGGL(k_update_dots<8>, dim3(grid), dim3(RED_THREADS), 0, s, ca, V, ldv, nv_upd, coef, cstride,
-                               w_in, w_out, partial, rev ? 1 : 0);
-        else if (nv_upd <= 16)
-            hipLaunchKernelGGL(k_update_dots<16>, dim3(grid), dim3(RED_THREADS), 0, s, ca, V, ldv, nv_upd, coef,
-                               cstride, w_in, w_out, partial, rev ? 1 : 0);
-        else
-            hipLaunchKernelGGL(k_update_dots<32>, dim3(grid), dim3(RED_THREADS), 0, s, ca, V, ldv, nv_upd, coef,
-                               cstride, w_in, w_out, partial, rev ? 1 : 0);
-        FR_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_final, dim3(sv.n, nv_dot), dim3(256), 0, s, ca, partial, out, ostride);
-        FR_HIP(hipGetLastError());
-        return FR_OK;
-    }
-    if (nv_upd > 0) {
-        // the norm of the updated vector rides on the update pass when no dots follow
-        const int nrm = (want_norm && nv_dot == 0) ? 1 : 0;
-        hipLaunchKernelGGL(k_update, dim3(grid), dim3(RED_THREADS), 0, s, ca, V, ldv, nv_upd, coef, cstride, w_in,
-                           w_out, nrm, partial, rev ? 1 : 0);
-        FR_HIP(hipGetLastError());
-        w = w_out;
-        if (nv_dot == 0) {
-            if (nrm && out) {   // (no out: the caller reduces the partials in slot 0 itself)
-                hipLaunchKernelGGL(k_final, dim3(sv.n, 1), dim3(256), 0, s, ca, partial, out, ostride);
-                FR_HIP(hipGetLastError());
-            }
-            return FR_OK;
-        }
-    }
-    const int ychunks = nv_dot > 0 ? (nv_dot + DB - 1) / DB : 1;
-    hipLaunchKernelGGL(k_dots8, dim3(grid, ychunks), dim3(RED_THREADS), 0, s, ca, V, ldv, nv_dot, w,
-                       want_norm ? 1 : 0, mass_only ? 1 : 0, partial);
+static fr_status too_many(int nv) {
+    if (nv <= MAXV - 1) return FR_OK;
+    fr_set_error("too many Krylov vectors");
+    return FR_EINVAL;
+}
+
+// second stage of the dots of partial set `set`, where a case needs one
+static fr_status final_dots(const Solver& sv, int nv, const GsRef& g, int set, const int* flags, int flag,
+                            hipStream_t s) {
+    if (sv.all_small) return FR_OK;
+    const DotRef dr{part_dots(sv, set), sv.nditem, sv.d_dfirst};
+    hipLaunchKernelGGL(k_final, dim3(sv.n, nv), dim3(256), 0, s, dot_args(sv, flags, flag), dr, g);
     FR_HIP(hipGetLastError());
-    const int nout = nv_dot + (want_norm ? 1 : 0);
-    if (nout > 0) {
-        hipLaunchKernelGGL(k_final, dim3(sv.n, nout), dim3(256), 0, s, ca, partial, out, ostride);
-        FR_HIP(hipGetLastError());
-    }
+    return FR_OK;
+}
+
+fr_status la_dots(const Solver& sv, const double* V, size_t ldv, int nv, const double* w, const GsRef& g, int set,
+                  const int* flags, int flag, hipStream_t s) {
+    FR_TRY(too_many(nv));
+    hipLaunchKernelGGL(k_dots8, dim3(item_grid(sv.nditem), (nv + DB - 1) / DB), dim3(RED_THREADS), 0, s,
+                       dot_args(sv, flags, flag), V, ldv, nv, w, 0, part_dots(sv, set), (double*)nullptr);
+    FR_HIP(hipGetLastError());
+    return final_dots(sv, nv, g, set, flags, flag, s);
+}
+
+fr_status la_update(const Solver& sv, const double* V, size_t ldv, int nv, const double* w_in, double* w_out,
+                    bool want_norm, const GsRef& g, int set, const int* flags, int flag, hipStream_t s, bool rev) {
+    FR_TRY(too_many(nv));
+    const DotRef dr{part_dots(sv, set), sv.nditem, sv.d_dfirst};
+    hipLaunchKernelGGL(k_update, dim3(item_grid(sv.nuitem)), dim3(RED_THREADS), 0, s, upd_args(sv, flags, flag), dr, g,
+                       V, ldv, nv, w_in, w_out, want_norm ? part_norm(sv) : nullptr, rev ? 1 : 0);
+    FR_HIP(hipGetLastError());
+    return FR_OK;
+}
+
+fr_status la_update_dots(const Solver& sv, const double* V, size_t ldv, int nv, const double* w_in, double* w_out,
+                         const GsRef& g, int set, const int* flags, int flag, hipStream_t s, bool rev) {
+    if (nv > 32) { fr_set_error("update with dots: at most 32 vectors"); return FR_EINVAL; }
+    const DotRef dr{part_dots(sv, set), sv.nditem, sv.d_dfirst};
+    const RedArgs ra = dot_args(sv, flags, flag);
+    const dim3 grid(item_grid(sv.nditem)), block(RED_THREADS);
+    double* out = part_dots(sv, 1 - set);
+    if (nv <= 8)
+        hipLaunchKernelGGL(k_update_dots<8>, grid, block, 0, s, ra, dr, g, V, ldv, nv, w_in, w_out, out, rev ? 1 : 0);
+    else if (nv <= 16)
+        hipLaunchKernelGGL(k_update_dots<16>, grid, block, 0, s, ra, dr, g, V, ldv, nv, w_in, w_out, out, rev ? 1 : 0);
+    else
+        hipLaunchKernelGGL(k_update_dots<32>, grid, block, 0, s, ra, dr, g, V, ldv, nv, w_in, w_out, out, rev ? 1 : 0);
+    FR_HIP(hipGetLastError());
+    return final_dots(sv, nv, g, 1 - set, flags, flag, s);
+}
+
+fr_status la_combine(const Solver& sv, const double* V, size_t ldv, const double* gs, int stride, int yfield,
+                     double* out, const int* flags, int flag, hipStream_t s) {
+    hipLaunchKernelGGL(k_combine, dim3(item_grid(sv.nuitem)), dim3(RED_THREADS), 0, s, upd_args(sv, flags, flag), V,
+                       ldv, gs, stride, yfield, out);
+    FR_HIP(hipGetLastError());
+    return FR_OK;
+}
+
+fr_status la_norm(const Solver& sv, const double* w, bool mass_only, double* out, int ostride, const int* flags,
+                  int flag, hipStream_t s) {
+    const RedArgs ra = dot_args(sv, flags, flag);
+    hipLaunchKernelGGL(k_dots8, dim3(item_grid(sv.nditem)), dim3(RED_THREADS), 0, s, ra, w, (size_t)0, 0, w,
+                       mass_only ? 1 : 0, part_dots(sv, 0), part_norm(sv));
+    FR_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_final_norm, dim3(sv.n), dim3(256), 0, s, ra, part_norm(sv), sv.d_dfirst, out, ostride);
+    FR_HIP(hipGetLastError());
     return FR_OK;
 }
 
 fr_status launch_cons(const Solver& sv, const double* q, double* Qc, const int* flags, hipStream_t s) {
-    hipLaunchKernelGGL(k_cons, dim3(chunk_grid(sv)), dim3(256), 0, s, chunk_args(sv, flags, GI_NDONE), q, Qc);
+    hipLaunchKernelGGL(k_cons, dim3(point_grid(sv)), dim3(256), 0, s, chunk_args(sv, flags, GI_NDONE), q, Qc);
     FR_HIP(hipGetLastError());
     return FR_OK;
 }
 
 fr_status launch_bdf_rhs(const Solver& sv, const double* q, const double* Qn, const double* Qnm1, const double* R,
                          double* b, const int* flags, hipStream_t s) {
-    hipLaunchKernelGGL(k_bdf_rhs, dim3(chunk_grid(sv)), dim3(256), 0, s, chunk_args(sv, flags, GI_NDONE), sv.d_step, q,
+    hipLaunchKernelGGL(k_bdf_rhs, dim3(point_grid(sv)), dim3(256), 0, s, chunk_args(sv, flags, GI_NDONE), sv.d_step, q,
                        Qn, Qnm1, R, b);
     FR_HIP(hipGetLastError());
     return FR_OK;
 }
 
 fr_status launch_cons_nm1(const Solver& sv, double* buf, hipStream_t s) {
-    hipLaunchKernelGGL(k_cons_nm1, dim3(chunk_grid(sv)), dim3(256), 0, s, chunk_args(sv, nullptr, 0), sv.d_step, buf);
+    hipLaunchKernelGGL(k_cons_nm1, dim3(point_grid(sv)), dim3(256), 0, s, chunk_args(sv, nullptr, 0), sv.d_step, buf);
     FR_HIP(hipGetLastError());
     return FR_OK;
 }

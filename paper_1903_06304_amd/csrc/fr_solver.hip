@@ -28,6 +28,45 @@ fr_status upload(T** d, const std::vector<T>& h) {
     return FR_OK;
 }
 
+// Items of the segmented reductions.  A small case (16 items at most in the dots) takes 64 entries
+// per update item, whose four waves share the basis vectors; a larger one about 1024 items of 256 to
+// 4096 entries, which fill the chip at every size (with 4096 entries throughout, 16 x 16 elements at
+// p = 3 ran their updates on 4 workgroups: 18.5 us at 75 vectors on average, 128 x 128 elements on
+// 256: 22 us for the dots).
+fr_status upload_items(Solver& sv) {
+    std::vector<Item> dots, upd;
+    std::vector<int> dfirst, ufirst;
+    auto cut = [](std::vector<Item>& v, int c, size_t off, size_t N, size_t span) {
+        for (size_t t = 0; t < N; t += span)
+            v.push_back(Item{c, (unsigned)std::min(span, N - t), (unsigned long long)(off + t)});
+    };
+    auto up256 = [](size_t x) { return (x + 255) / 256 * 256; };
+    sv.all_small = true;
+    for (int c = 0; c < sv.n; ++c) {
+        const size_t N = sv.N(c);
+        dfirst.push_back((int)dots.size());
+        ufirst.push_back((int)upd.size());
+        if (is_small(N)) {
+            cut(dots, c, sv.off[c], N, std::max<size_t>(256, up256((N + SMALL_ITEMS - 1) / SMALL_ITEMS)));
+            cut(upd, c, sv.off[c], N, 64);
+        } else {
+            const size_t span = std::min<size_t>(CHUNK, std::max<size_t>(256, up256((N + 1023) / 1024)));
+            cut(dots, c, sv.off[c], N, span);
+            cut(upd, c, sv.off[c], N, span);
+            sv.all_small = false;
+        }
+    }
+    dfirst.push_back((int)dots.size());
+    ufirst.push_back((int)upd.size());
+    sv.nditem = (int)dots.size();
+    sv.nuitem = (int)upd.size();
+    FR_TRY(upload(&sv.d_ditem, dots));
+    FR_TRY(upload(&sv.d_uitem, upd));
+    FR_TRY(upload(&sv.d_dfirst, dfirst));
+    FR_TRY(upload(&sv.d_ufirst, ufirst));
+    return FR_OK;
+}
+
 }  // namespace
 
 fr_status solver_init(Solver& sv, const fr_ctx* ctxs, int n) {
@@ -67,15 +106,12 @@ fr_status solver_init(Solver& sv, const fr_ctx* ctxs, int n) {
     sv.spack_len = so;
     sv.nchunks = (int)(o / CHUNK);
     if ((size_t)sv.nchunks * CHUNK != o || o / CHUNK > (size_t)1 << 30) { fr_set_error("solver too large"); return FR_EINVAL; }
-    std::vector<int> chunk_case(sv.nchunks), case_chunk(n + 1);
-    for (int c = 0; c < n; ++c) {
-        case_chunk[c] = (int)(sv.off[c] / CHUNK);
+    std::vector<int> chunk_case(sv.nchunks);
+    for (int c = 0; c < n; ++c)
         for (size_t k = sv.off[c] / CHUNK; k < (sv.off[c] + sv.len[c]) / CHUNK; ++k) chunk_case[k] = c;
-    }
-    case_chunk[n] = sv.nchunks;
     FR_TRY(upload(&sv.d_cases, cd));
     FR_TRY(upload(&sv.d_chunk_case, chunk_case));
-    FR_TRY(upload(&sv.d_case_chunk, case_chunk));
+    FR_TRY(upload_items(sv));
     // launch groups: cases of one order, viscous and moving kind, with or without boundary
     // faces, and (as the geometry stands when the solver is made) affine or not, so that a
     // case runs the same kernel variant alone and in a batch; whether a group is affine is
@@ -141,7 +177,7 @@ fr_status solver_init(Solver& sv, const fr_ctx* ctxs, int n) {
     FR_TRY(dalloc(&sv.d_sum, (size_t)n * SUM_STRIDE));
     FR_HIP(hipMemset(sv.d_sum, 0, (size_t)n * SUM_STRIDE * sizeof(double)));
     FR_TRY(dalloc(&sv.d_step, (size_t)n));
-    FR_TRY(dalloc(&sv.d_part, (size_t)sv.nchunks * MAXV));
+    FR_TRY(dalloc(&sv.d_part, part_doubles(sv)));
     sv.h_pin_doubles = (size_t)n * (SUM_STRIDE + sizeof(CaseStep) / sizeof(double) + 2) + 64;
     if (hipHostMalloc((void**)&sv.h_pin, sv.h_pin_doubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         sv.h_pin = nullptr;
@@ -159,7 +195,8 @@ void solver_free(Solver& sv) {
         for (auto& x : g.ctiles) { dfree(x.d_pfx); dfree(x.d_csel); }
     }
     sv.groups.clear();
-    dfree(sv.d_cases); dfree(sv.d_chunk_case); dfree(sv.d_case_chunk);
+    dfree(sv.d_cases); dfree(sv.d_chunk_case);
+    dfree(sv.d_ditem); dfree(sv.d_uitem); dfree(sv.d_dfirst); dfree(sv.d_ufirst);
     dfree(sv.d_blk); dfree(sv.d_inv); dfree(sv.d_blk_keep);
     dfree(sv.d_q); dfree(sv.d_w); dfree(sv.d_V); dfree(sv.d_gs); dfree(sv.d_gi); dfree(sv.d_part);
     dfree(sv.d_step); dfree(sv.d_sum); dfree(sv.d_fpack); dfree(sv.d_spack); dfree(sv.d_rscratch);
