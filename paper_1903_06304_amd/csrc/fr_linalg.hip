@@ -321,6 +321,13 @@ __device__ __forceinline__ double split_sum(const double* __restrict__ V, size_t
     return s;
 }
 
+// s_j w, rounded: the kernels that must agree bit for bit may not fuse it into the subtraction that
+// follows in one of them and not in the other
+__device__ __forceinline__ double scaled(double sj, double w) {
+#pragma clang fp contract(off)
+    return sj * w;
+}
+
 // w_out = (s_j) w_in - sum_{i < nv} h_i s_i V_i, and the partial |w_out|^2 of each item when
 // npart is not null
 __global__ void __launch_bounds__(RED_THREADS) k_update(RedArgs ra, DotRef dr, GsRef g, const double* __restrict__ V,
@@ -353,7 +360,7 @@ __global__ void __launch_bounds__(RED_THREADS) k_update(RedArgs ra, DotRef dr, G
             continue;
         }
         for (size_t t = im.start + threadIdx.x; t < end; t += RED_THREADS) {
-            double wt = sj * w_in[t];
+            double wt = scaled(sj, w_in[t]);
             int i = 0;
             // 16 basis entries loaded before any is used, summed in the groups of four below
             for (; i + 16 <= nv; i += 16) {
@@ -413,7 +420,7 @@ __global__ void __launch_bounds__(RED_THREADS) k_update_dots(RedArgs ra, DotRef 
             double x[NV];
 #pragma unroll
             for (int k = 0; k < NV; ++k) x[k] = V[(size_t)(k < nv ? k : nv - 1) * ldv + t];
-            double wt = sj * w_in[t];
+            double wt = scaled(sj, w_in[t]);
             const int n4 = nv & ~3;
 #pragma unroll
             for (int k = 0; k < NV; k += 4)
