@@ -15,9 +15,10 @@
 // Per-case flags decide which cases a launch touches: a case whose Arnoldi process has
 // stopped (|g_{j+1}| <= tol |b|, breakdown, iteration cap) is skipped by the rest of the
 // cycle's Arnoldi launches; a case that did not start the cycle is skipped by its update
-// too.  The sequence holds no host decision, so it is captured once into a hipGraph and
-// replayed; the host synchronises once per cycle to read one "needs another cycle" flag
-// per case.  The Newton loop (paper Sec. 3.2) keeps per-case convergence on the device
+// too.  The sequence is captured into hipGraphs once and replayed: the Arnoldi steps in segments,
+// then the cycle's end.  The host keeps one segment queued behind the one that runs and
+// stops launching them when a segment that has ended reports every case stopped; it synchronises
+// once per cycle to read one "needs another cycle" flag per case.  The Newton loop (paper Sec. 3.2) keeps per-case convergence on the device
 // as well and synchronises once per Newton iteration.
 #include <cmath>
 #include <cstring>
@@ -264,13 +265,7 @@ fr_status bdf_op(const Solver& sv, const double* q, const double* v, double* Av,
     return solver_fused(sv, MODE_LIN, a, s);
 }
 
-// the launches of one cycle (enqueued eagerly or under capture): the start, the Arnoldi steps, the end
-fr_status enqueue_start(Solver& sv, int m, hipStream_t s) {
-    hipLaunchKernelGGL(k_cycle_init, dim3(cgrid(sv)), dim3(64), 0, s, ctl(sv), m);
-    FR_HIP(hipGetLastError());
-    return FR_OK;
-}
-
+// the launches of one cycle (enqueued eagerly or under capture): an Arnoldi step
 fr_status enqueue_arnoldi(Solver& sv, int m, int j, hipStream_t s) {
     const size_t N = sv.Ntot;
     const GsLayout L(m);
@@ -305,6 +300,39 @@ fr_status enqueue_arnoldi(Solver& sv, int m, int j, hipStream_t s) {
     return FR_OK;
 }
 
+// Arnoldi steps per segment.  The steps after the last case has stopped skip every case, but their
+// launches cost 2 to 3 us each (with m = 150 on 16 x 16 elements 410 of 750 launched steps did
+// nothing); a graph launch costs about 15 us.  6 measured best of 4, 6 and 10: 16 x 16 steady
+// GMRES(150) 24.1 -> 20.1 ms a pass, 256 x 256 p = 3 46.8 -> 46.3 ms a step, 128 x 128 deforming
+// 25.0 -> 24.5 ms.  Small cases (about 20 us a step) with a short restart have little to skip and
+// keep the whole cycle, with its end, in one graph: 8 x 8 p = 2, m = 20: 1.83 ms a step against 1.91.
+int segment_len(const Solver& sv, int m) { return sv.all_small && m <= 40 ? m : 6; }
+int nsegments(const Solver& sv, int m) { return (m + segment_len(sv, m) - 1) / segment_len(sv, m); }
+
+// whether some case's Arnoldi process goes on after a segment, to pinned host memory
+__global__ void k_segment_end(Ctl k, int* __restrict__ more) {
+    const int lane = threadIdx.x;   // one wave
+    bool any = false;
+    for (int c = lane; c < k.n; c += 64) any = any || !k.gi[c * GI_STRIDE + GI_DONE];
+    const bool r = __any(any);
+    if (lane == 0) *more = r ? 1 : 0;
+}
+
+// segment i of the cycle (with the cycle's start in the first)
+fr_status enqueue_segment(Solver& sv, int m, int i, hipStream_t s) {
+    if (i == 0) {
+        hipLaunchKernelGGL(k_cycle_init, dim3(cgrid(sv)), dim3(64), 0, s, ctl(sv), m);
+        FR_HIP(hipGetLastError());
+    }
+    const int len = segment_len(sv, m), j1 = (i + 1) * len < m ? (i + 1) * len : m;
+    for (int j = i * len; j < j1; ++j) FR_TRY(enqueue_arnoldi(sv, m, j, s));
+    if (j1 < m) {
+        hipLaunchKernelGGL(k_segment_end, dim3(1), dim3(64), 0, s, ctl(sv), sv.h_seg + i);
+        FR_HIP(hipGetLastError());
+    }
+    return FR_OK;
+}
+
 fr_status enqueue_end(Solver& sv, int m, hipStream_t s) {
     const size_t N = sv.Ntot;
     const GsLayout L(m);
@@ -330,10 +358,48 @@ fr_status enqueue_end(Solver& sv, int m, hipStream_t s) {
     return FR_OK;
 }
 
-fr_status enqueue_cycle(Solver& sv, int m, hipStream_t s) {
-    FR_TRY(enqueue_start(sv, m, s));
-    for (int j = 0; j < m; ++j) FR_TRY(enqueue_arnoldi(sv, m, j, s));
-    return enqueue_end(sv, m, s);
+// capture `enqueue` into an executable graph
+template <class F>
+fr_status capture(hipStream_t s, F&& enqueue, void** out) {
+    hipGraph_t gr;
+    FR_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+    const fr_status cst = enqueue();
+    const hipError_t ee = hipStreamEndCapture(s, &gr);
+    if (cst != FR_OK) { if (ee == hipSuccess) (void)hipGraphDestroy(gr); return cst; }
+    FR_HIP(ee);
+    hipGraphExec_t ex;
+    const hipError_t ie = hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(gr);
+    FR_HIP(ie);
+    *out = ex;
+    return FR_OK;
+}
+
+// launches i of a cycle of nseg segments: the segments, then the end (with a single segment, all at once)
+fr_status enqueue_part(Solver& sv, int m, int i, hipStream_t s) {
+    const int nseg = nsegments(sv, m);
+    if (i < nseg) FR_TRY(enqueue_segment(sv, m, i, s));
+    return i >= nseg || nseg == 1 ? enqueue_end(sv, m, s) : FR_OK;
+}
+int nparts(const Solver& sv, int m) { return nsegments(sv, m) == 1 ? 1 : nsegments(sv, m) + 1; }
+
+// One restart cycle.  Running one segment ahead keeps the GPU busy while the host learns how the
+// last one ended.
+fr_status run_cycle(Solver& sv, int m, bool graph, hipStream_t s) {
+    const int last = nparts(sv, m) - 1;
+    auto launch = [&](int i) -> fr_status {
+        if (!graph) return enqueue_part(sv, m, i, s);
+        FR_HIP(hipGraphLaunch((hipGraphExec_t)sv.graph_exec[i], s));
+        return FR_OK;
+    };
+    for (int i = 0; i < last; ++i) {
+        FR_TRY(launch(i));
+        if (i + 1 < last) FR_HIP(hipEventRecord(sv.ev_seg[i & 1], s));
+        if (i == 0) continue;
+        FR_HIP(hipEventSynchronize(sv.ev_seg[(i - 1) & 1]));
+        if (!*(volatile int*)(sv.h_seg + i - 1)) break;
+    }
+    return launch(last);
 }
 
 // ---- Newton-level kernels
@@ -433,10 +499,8 @@ __global__ void k_axpy_case(Vec vc, const double* __restrict__ dq, double* __res
 size_t gmres_state_doubles(int m) { return (size_t)GsLayout(m).total; }
 
 void gmres_release(Solver& sv) {
-    if (sv.graph_exec) {
-        (void)hipGraphExecDestroy((hipGraphExec_t)sv.graph_exec);
-        sv.graph_exec = nullptr;
-    }
+    for (void* g : sv.graph_exec) (void)hipGraphExecDestroy((hipGraphExec_t)g);
+    sv.graph_exec.clear();
 }
 
 // GMRES on every case still in the Newton iteration: A dq = b with b = WB, dq = WDQ
@@ -465,23 +529,18 @@ fr_status gmres_device(Solver& sv, int m, int prec, int max_it, hipStream_t s) {
         for (int id : sv.groups[g].ids) all = all && sv.cs[id]->all_affine;
         aff[g] = all ? 1 : 0;
     }
-    if (graph && (!sv.graph_exec || sv.graph_m != m || sv.graph_prec != prec || sv.graph_passes != sv.gs_passes ||
+    if (graph && (sv.graph_exec.empty() || sv.graph_m != m || sv.graph_prec != prec || sv.graph_passes != sv.gs_passes ||
                   sv.graph_precond != sv.precond || sv.graph_cl != (int)sv.inv_colour || sv.graph_aff != aff)) {
         gmres_release(sv);
         // capture one cycle (all buffers are solver-owned; tolerances, time coefficients and
-        // caps are read on the device, so the graph depends on m, the block precision and
+        // caps are read on the device, so the graphs depend on m, the block precision and
         // layout, the Gram-Schmidt passes and the preconditioner only)
-        hipGraph_t gr;
-        FR_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-        fr_status cst = enqueue_cycle(sv, m, s);
-        hipError_t ee = hipStreamEndCapture(s, &gr);
-        if (cst != FR_OK) { if (ee == hipSuccess) (void)hipGraphDestroy(gr); return cst; }
-        FR_HIP(ee);
-        hipGraphExec_t ex;
-        hipError_t ie = hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(gr);
-        FR_HIP(ie);
-        sv.graph_exec = ex;
+        for (int i = 0; i < nparts(sv, m); ++i) {
+            void* ex = nullptr;
+            const fr_status st = capture(s, [&] { return enqueue_part(sv, m, i, s); }, &ex);
+            if (st != FR_OK) { gmres_release(sv); return st; }
+            sv.graph_exec.push_back(ex);
+        }
         sv.graph_m = m;
         sv.graph_prec = prec;
         sv.graph_passes = sv.gs_passes;
@@ -491,11 +550,7 @@ fr_status gmres_device(Solver& sv, int m, int prec, int max_it, hipStream_t s) {
     }
     double* hs = sv.h_pin;
     for (;;) {
-        if (graph) {
-            FR_HIP(hipGraphLaunch((hipGraphExec_t)sv.graph_exec, s));
-        } else {
-            FR_TRY(enqueue_cycle(sv, m, s));
-        }
+        FR_TRY(run_cycle(sv, m, graph, s));
         FR_HIP(hipMemcpyAsync(hs, sv.d_sum, (size_t)sv.n * SUM_STRIDE * sizeof(double), hipMemcpyDeviceToHost, s));
         FR_HIP(hipStreamSynchronize(s));
         bool more = false;

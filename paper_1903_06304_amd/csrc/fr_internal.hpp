@@ -292,11 +292,13 @@ struct Solver {
     bool op_packs = false;                 // fr_bdf_operator through the packs (two passes)
     double* d_rscratch = nullptr;          // R of that path
     double* h_pin = nullptr;               // pinned host staging
+    int* h_seg = nullptr;                  // pinned: per segment of a cycle, whether a case goes on (device-written)
     size_t h_pin_doubles = 0;
     hipStream_t ws = nullptr;
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
+    hipEvent_t ev_seg[2] = {nullptr, nullptr};   // ends of the last two segments of a GMRES cycle
     bool use_graph = true;
-    void* graph_exec = nullptr;
+    std::vector<void*> graph_exec;         // the cycle's segments, then its end (empty: not captured)
     int graph_m = 0, graph_prec = -1, graph_passes = 0, graph_precond = -1, graph_cl = -1;
     std::vector<char> graph_aff;           // per group: all members affine when the cycle was captured
     int gs_passes = 1;                     // classical Gram-Schmidt passes per Arnoldi step (1 or 2)

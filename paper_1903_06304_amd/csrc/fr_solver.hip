@@ -184,6 +184,11 @@ fr_status solver_init(Solver& sv, const fr_ctx* ctxs, int n) {
         fr_set_error("hipHostMalloc failed");
         return FR_ENOMEM;
     }
+    if (hipHostMalloc((void**)&sv.h_seg, MAXV * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+        sv.h_seg = nullptr;
+        fr_set_error("hipHostMalloc failed");
+        return FR_ENOMEM;
+    }
     return FR_OK;
 }
 
@@ -205,6 +210,9 @@ void solver_free(Solver& sv) {
     if (sv.ws) (void)hipStreamDestroy(sv.ws);
     if (sv.ev_in) (void)hipEventDestroy(sv.ev_in);
     if (sv.ev_out) (void)hipEventDestroy(sv.ev_out);
+    for (hipEvent_t e : sv.ev_seg)
+        if (e) (void)hipEventDestroy(e);
+    if (sv.h_seg) (void)hipHostFree(sv.h_seg);
     sv = Solver();
 }
 
@@ -269,6 +277,7 @@ fr_status solver_ensure_step(Solver& sv, int m, int prec) {
         FR_HIP(hipStreamCreateWithFlags(&sv.ws, hipStreamNonBlocking));
         FR_HIP(hipEventCreateWithFlags(&sv.ev_in, hipEventDisableTiming));
         FR_HIP(hipEventCreateWithFlags(&sv.ev_out, hipEventDisableTiming));
+        for (hipEvent_t& e : sv.ev_seg) FR_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     }
     return FR_OK;
 }
