@@ -229,7 +229,8 @@ extern "C" fr_status fr_create(const fr_params* prm, const int32_t* h_nbr, const
     pc.inv_Rg = 1.0 / pc.Rg;
     pc.mu_re = prm->viscous ? prm->mu / prm->reynolds : 0.0;
     pc.kc_re = prm->viscous ? prm->mu * pc.Cp / prm->prandtl / prm->reynolds : 0.0;
-    pc.eps_min = prm->kappa * prm->mach_inf;
+    pc.eps_min2 = (prm->kappa * prm->mach_inf) * (prm->kappa * prm->mach_inf);
+    pc.inv_gRg = 1.0 / pc.gRg;
     pc.br2 = 0.5 * c->n * c->n;
     build_tables(c);
     if (hipGetDevice(&c->device) != hipSuccess) { delete c; fr_set_error("no HIP device"); return FR_EHIP; }

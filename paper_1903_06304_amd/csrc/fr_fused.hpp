@@ -443,17 +443,17 @@ k_fused(GroupArgs ga, KArgs a, OpTab op) {
                     }
                 }
                 if (BC && bck) fr_bc_grad<T>(bck, gm, nx, ny, gp);
-                if constexpr (MODE == MODE_PREP) {
-                    double* fpk = a.fpack + cd.fpoff + (size_t)e * NF + lt;
-                    const size_t fs = (size_t)E * NF;
-#pragma unroll
-                    for (int c = 0; c < 6; ++c) fpk[(8 + c) * fs] = gm[c] + gp[c];   // the common flux needs the sum only
-                }
                 // q^com velocity = average of the two traces = q^- + dq/2
                 const T qcu = am_avg<T>(&s_q[QI(el, 1, 0)], lam, f, k, dq[1], n);
                 const T qcv = am_avg<T>(&s_q[QI(el, 2, 0)], lam, f, k, dq[2], n);
-                T dqh[3];
-                fr_common_viscous<T>(pc, dq, qcu, qcv, gm, gp, nx, ny, lg.cc, fn, dqh);
+                T dqh[3], tn[2];
+                fr_common_viscous<T>(pc, dq, qcu, qcv, gm, gp, nx, ny, lg.cc, fn, dqh, tn);
+                if constexpr (MODE == MODE_PREP) {
+                    double* fpk = a.fpack + cd.fpoff + (size_t)e * NF + lt;
+                    const size_t fs = (size_t)E * NF;
+                    fpk[8 * fs] = tn[0];
+                    fpk[9 * fs] = tn[1];
+                }
 #pragma unroll
                 for (int c = 0; c < 3; ++c) s_dq[DI(el, c, lt)] = dqh[c];
             }
@@ -490,21 +490,17 @@ k_fused(GroupArgs ga, KArgs a, OpTab op) {
                     gr[c][1] = gr[c][1] + ij * cy;
                 }
             }
+            T fl[4], gl[4], qc[4], tau[3];
+            fr_point_flux<T, VISC>(pc, qs, gu, gv, gT, fl, gl, qc, tau);
             if constexpr (MODE == MODE_PREP) {
                 double* spk = a.spack + cd.spoff + (size_t)e * Np + lt;
 #pragma unroll
                 for (int vv = 0; vv < 4; ++vv) spk[(size_t)vv * EN] = qs[vv];
                 if (VISC) {
 #pragma unroll
-                    for (int d = 0; d < 2; ++d) {
-                        spk[(size_t)(4 + d) * EN] = gu[d];
-                        spk[(size_t)(6 + d) * EN] = gv[d];
-                        spk[(size_t)(8 + d) * EN] = gT[d];
-                    }
+                    for (int d = 0; d < 3; ++d) spk[(size_t)(4 + d) * EN] = tau[d];
                 }
             }
-            T fl[4], gl[4], qc[4];
-            fr_point_flux<T, VISC>(pc, qs, gu, gv, gT, fl, gl, qc);
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv) {
                 if constexpr (TAN) {
@@ -849,16 +845,16 @@ k_fused_aff(GroupArgs ga, KArgs a, OpTab op) {
                     gp[2 * c] = lg.mxix * dxi + lg.metx * deta;
                     gp[2 * c + 1] = lg.mxiy * dxi + lg.mety * deta;
                 }
+                const T qcu = qm[1] + 0.5 * dq[1];
+                const T qcv = qm[2] + 0.5 * dq[2];
+                T dqh[3], tn[2];
+                fr_common_viscous<T>(pc, dq, qcu, qcv, gm, gp, nx, ny, lg.cc, fn, dqh, tn);
                 if constexpr (MODE == MODE_PREP) {
                     double* fpk = a.fpack + cd.fpoff + (size_t)e * NF + lt;
                     const size_t fs = (size_t)E * NF;
-#pragma unroll
-                    for (int c = 0; c < 6; ++c) fpk[(8 + c) * fs] = gm[c] + gp[c];   // the common flux needs the sum only
+                    fpk[8 * fs] = tn[0];
+                    fpk[9 * fs] = tn[1];
                 }
-                const T qcu = qm[1] + 0.5 * dq[1];
-                const T qcv = qm[2] + 0.5 * dq[2];
-                T dqh[3];
-                fr_common_viscous<T>(pc, dq, qcu, qcv, gm, gp, nx, ny, lg.cc, fn, dqh);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) s_dq[DI(el, c, lt)] = dqh[c];
             }
@@ -893,21 +889,17 @@ k_fused_aff(GroupArgs ga, KArgs a, OpTab op) {
                     gr[c][1] = gr[c][1] + (lg.xiy * lx + lg.ety * le);
                 }
             }
+            T fl[4], gl[4], qc[4], tau[3];
+            fr_point_flux<T, VISC>(pc, qs, gu, gv, gT, fl, gl, qc, tau);
             if constexpr (MODE == MODE_PREP) {
                 double* spk = a.spack + cd.spoff + (size_t)e * Np + lt;
 #pragma unroll
                 for (int vv = 0; vv < 4; ++vv) spk[(size_t)vv * EN] = qs[vv];
                 if (VISC) {
 #pragma unroll
-                    for (int d = 0; d < 2; ++d) {
-                        spk[(size_t)(4 + d) * EN] = gu[d];
-                        spk[(size_t)(6 + d) * EN] = gv[d];
-                        spk[(size_t)(8 + d) * EN] = gT[d];
-                    }
+                    for (int d = 0; d < 3; ++d) spk[(size_t)(4 + d) * EN] = tau[d];
                 }
             }
-            T fl[4], gl[4], qc[4];
-            fr_point_flux<T, VISC>(pc, qs, gu, gv, gT, fl, gl, qc);
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv) {
                 if constexpr (TAN) {
@@ -923,7 +915,7 @@ k_fused_aff(GroupArgs ga, KArgs a, OpTab op) {
         // ---- stage 5: F^num - F^loc, F^loc = |J| Pi F~ (xi faces) or |J| Pi G~ (eta faces)
         if (act && lt < NF) {
             const double* lam = s_lam[f & 1];
-            const double jac = 1.0 / lg.ij;
+            const double jac = frcp(lg.ij);
             const int base = f < 2 ? 0 : 4;
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv) {
@@ -1150,15 +1142,16 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
             const unsigned FE = (unsigned)E * NF;
             const unsigned sid = (unsigned)e * NF + lt;
             const double nx = lg.nx, ny = lg.ny, sc = lg.sc, ugf = lg.fug, vgf = lg.fvg;
-            D fn[4], dq[4], qm[4], qp[4];
+            // the viscous part first: it ends in three numbers, so little of it is live in the
+            // inviscid flux, whose dual numbers are the kernel's register peak
+            double ft[4] = {0.0, 0.0, 0.0, 0.0};
+            double qmv[4], qpv[4];
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv) {
-                qm[vv] = mk(ldo(fpk + (size_t)vv * FE, sid), qmt[vv]);
-                qp[vv] = mk(ldo(fpk + (size_t)(4 + vv) * FE, sid), qpt[vv]);
+                qmv[vv] = ldo(fpk + (size_t)vv * FE, sid);
+                qpv[vv] = ldo(fpk + (size_t)(4 + vv) * FE, sid);
             }
-            fr_common_inviscid<D>(pc, qm, qp, nx, ny, ugf, vgf, fn, dq);
             if (VISC) {
-                D gm[6], gp[6];
                 double gmt[6];
 #pragma unroll
                 for (int c = 0; c < 6; ++c) {
@@ -1166,7 +1159,6 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
 #pragma unroll
                     for (int b = 0; b < n; ++b)
                         if (!ZO) am = am + lam[b] * s_g[GI(el, c, line_pt(n, f, k, b))];
-                    gm[c] = mk(ldo(fpk + (size_t)(8 + c) * FE, sid), am);
                     gmt[c] = am;
                 }
                 double gpt[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -1207,18 +1199,24 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
                     }
                 }
                 if (BC && bck) fr_bc_grad<double>(bck, gmt, nx, ny, gpt);
+                double gs[6], dqt[4], dqh[3];
 #pragma unroll
-                for (int c = 0; c < 6; ++c) gp[c] = mk(0.0, gpt[c]);   // the pack holds g^- + g^+ in gm
-                // q^com velocity = q^- + dq/2 (the own trace as formed above)
-                const D qcu = qm[1] + 0.5 * dq[1];
-                const D qcv = qm[2] + 0.5 * dq[2];
-                D dqh[3];
-                fr_common_viscous<D>(pc, dq, qcu, qcv, gm, gp, nx, ny, lg.cc, fn, dqh);
+                for (int c = 0; c < 6; ++c) gs[c] = gmt[c] + gpt[c];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) s_dq[DI(el, c, lt)] = dqh[c].d[0];
+                for (int vv = 0; vv < 4; ++vv) dqt[vv] = qpt[vv] - qmt[vv];
+                // q^com velocity: the average of the traces
+                fr_common_viscous_tan(pc, dqt, 0.5 * (qmv[1] + qpv[1]), 0.5 * (qmv[2] + qpv[2]), 0.5 * (qmt[1] + qpt[1]),
+                                      0.5 * (qmt[2] + qpt[2]), ldo(fpk + (size_t)8 * FE, sid),
+                                      ldo(fpk + (size_t)9 * FE, sid), gs, nx, ny, lg.cc, ft, dqh);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) s_dq[DI(el, c, lt)] = dqh[c];
             }
+            D fn[4], dq[4], qm[4], qp[4];
 #pragma unroll
-            for (int vv = 0; vv < 4; ++vv) fsc[vv] = (sc * fn[vv]).d[0];
+            for (int vv = 0; vv < 4; ++vv) { qm[vv] = mk(qmv[vv], qmt[vv]); qp[vv] = mk(qpv[vv], qpt[vv]); }
+            fr_common_inviscid<D>(pc, qm, qp, nx, ny, ugf, vgf, fn, dq);
+#pragma unroll
+            for (int vv = 0; vv < 4; ++vv) fsc[vv] = sc * (fn[vv].d[0] + ft[vv]);
             s_S[SI(el, 0, lt)] = sc * nx;
             s_S[SI(el, 1, lt)] = sc * ny;
             s_S[SI(el, 2, lt)] = MOV ? sc * (ugf * nx + vgf * ny) : 0.0;
@@ -1230,14 +1228,21 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
         if (act && lt < Np) {
             const unsigned id = (unsigned)e * Np + lt;
             const double ij = lg.ij;
-            D qs[4], gu[2], gv[2], gT[2];
+            D qs[4];
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv) {
                 qv[vv] = ldo(spk + (size_t)vv * EN, id);
                 qs[vv] = mk(qv[vv], ZO ? 0.0 : s_q[QI(el, vv, lt)]);
             }
+            D fl[4], gl[4], qc[4];
+            fr_point_flux<D, false>(pc, qs, nullptr, nullptr, nullptr, fl, gl, qc);
+            double ft[4], gf[4];
+#pragma unroll
+            for (int vv = 0; vv < 4; ++vv) { ft[vv] = fl[vv].d[0]; gf[vv] = gl[vv].d[0]; }
             if (VISC) {
-                double gt[6];
+                double gt[6], tau[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) tau[c] = ldo(spk + (size_t)(4 + c) * EN, id);
 #pragma unroll
                 for (int c = 0; c < 6; ++c) gt[c] = ZO ? 0.0 : s_g[GI(el, c, lt)];
                 const int fp0 = 0 * n + j, fp1 = 1 * n + j, fp2 = 2 * n + i, fp3 = 3 * n + i;
@@ -1251,19 +1256,12 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
                     gt[2 * c] = gt[2 * c] + ij * cx;
                     gt[2 * c + 1] = gt[2 * c + 1] + ij * cy;
                 }
-#pragma unroll
-                for (int d = 0; d < 2; ++d) {
-                    gu[d] = mk(ldo(spk + (size_t)(4 + d) * EN, id), gt[d]);
-                    gv[d] = mk(ldo(spk + (size_t)(6 + d) * EN, id), gt[2 + d]);
-                    gT[d] = mk(ldo(spk + (size_t)(8 + d) * EN, id), gt[4 + d]);
-                }
+                fr_point_viscous_tan(pc, qv[1], qv[2], qs[1].d[0], qs[2].d[0], tau, gt, ft, gf);
             }
-            D fl[4], gl[4], qc[4];
-            fr_point_flux<D, VISC>(pc, qs, gu, gv, gT, fl, gl, qc);
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv) {
-                s_n[WI(vv, lt)] = fl[vv].d[0];
-                s_n[WI(4 + vv, lt)] = gl[vv].d[0];
+                s_n[WI(vv, lt)] = ft[vv];
+                s_n[WI(4 + vv, lt)] = gf[vv];
                 if (MOV) s_n[WI(8 + vv, lt)] = qc[vv].d[0];
             }
         }
@@ -1382,8 +1380,6 @@ k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
     const int f = (lt % NF) / n, k = lt % n;
     int tile, tend, tstride;
     tile_range(ga.ntiles, ga.xcd, tile, tend, tstride);
-    int pkn = 0;   // connectivity of the next tile, requested one tile ahead
-    int pkn_tile = -1;
     for (; tile < tend; tile += tstride) {
         const int lo = find_member(ga, tile);
         const int cid = sld(ga.ids + lo);
@@ -1400,22 +1396,21 @@ k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
         const double* spk = a.spack + cd.spoff;
         __syncthreads();
         LaneGeo lg;
-        const bool pre = pkn_tile == tile;
         // block columns: the connectivity, the metric terms and the packs once per tile, for
         // every column of the launch (a.ncols from seed0)
-        double fpv[14], spv[10];
+        double fpv[10], spv[7];
         if constexpr (BLK) {
             if (act) {
-                lane_geo_load<P, VISC, false>(g, E, e, lt, pre ? pkn : ldo(g.nbr, (unsigned)(e * 4 + f)), lg);
+                lane_geo_load<P, VISC, false>(g, E, e, lt, ldo(g.nbr, (unsigned)(e * 4 + f)), lg);
                 if (lt < NF) {
                     const unsigned FE = (unsigned)E * NF, sid = (unsigned)e * NF + lt;
 #pragma unroll
-                    for (int c = 0; c < (VISC ? 14 : 8); ++c) fpv[c] = ldo(fpk + (size_t)c * FE, sid);
+                    for (int c = 0; c < npf(VISC); ++c) fpv[c] = ldo(fpk + (size_t)c * FE, sid);
                 }
                 if (lt < Np) {
                     const unsigned id = (unsigned)e * Np + lt;
 #pragma unroll
-                    for (int c = 0; c < (VISC ? 10 : 4); ++c) spv[c] = ldo(spk + (size_t)c * EN, id);
+                    for (int c = 0; c < nps(VISC); ++c) spv[c] = ldo(spk + (size_t)c * EN, id);
                 }
             }
         }
@@ -1435,7 +1430,7 @@ k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
 #pragma unroll
                 for (int vv = 0; vv < 4; ++vv)
                     qo[vv] = BLK ? ((vv * Np + ls == col) ? 1.0 : 0.0) : (cs ? 0.0 : ldo(v + vv * EN, id));
-                if constexpr (!BLK) lane_geo_load<P, VISC, false>(g, E, e, lt, pre ? pkn : ldo(g.nbr, (unsigned)(e * 4 + f)), lg);
+                if constexpr (!BLK) lane_geo_load<P, VISC, false>(g, E, e, lt, ldo(g.nbr, (unsigned)(e * 4 + f)), lg);
                 if (lt < NF) {
                     const unsigned nbase = (unsigned)lg.nb * Np;
                     bool take = true;
@@ -1478,16 +1473,6 @@ k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
                         if (!ZO) s_q[QI(el, vv, lt)] = qo[vv];
                 }
             }
-            if (col == c0) {
-                const int tn = tile + tstride;
-                const int pfx_hi = lo + 1 < ga.nmem ? sld(ga.pfx + lo + 1) : ga.ntiles;
-                pkn_tile = (tn < tend && tn < pfx_hi) ? tn : -1;
-                if (pkn_tile >= 0) {
-                    bool actn;
-                    const int en = tile_elem(ga, g, lo, tn, EPB, el, E, actn);
-                    if (actn) pkn = ldo(g.nbr, (unsigned)(en * 4 + f));
-                }
-            }
             __syncthreads();
             // ---- stage 2: uncorrected gradient tangent
             if (VISC && !ZO && act && lt < Np) {
@@ -1511,26 +1496,29 @@ k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
                 const unsigned FE = (unsigned)E * NF;
                 const unsigned sid = (unsigned)e * NF + lt;
                 const double nx = lg.nx, ny = lg.ny, sc = lg.sc;
-                D fn[4], dq[4], qm[4], qp[4];
+                // the viscous part first: it ends in three numbers, so little of it is live in the
+                // inviscid flux, whose dual numbers are the kernel's register peak
+                double ft[4] = {0.0, 0.0, 0.0, 0.0};
+                double qmv[4], qpv[4], qmt[4];
 #pragma unroll
                 for (int vv = 0; vv < 4; ++vv) {
                     double acc = 0.0;
 #pragma unroll
                     for (int b = 0; b < n; ++b)
                         if (!ZO) acc = acc + lam[b] * s_q[QI(el, vv, line_pt(n, f, k, b))];
-                    qm[vv] = mk(BLK ? fpv[vv] : ldo(fpk + (size_t)vv * FE, sid), acc);
-                    qp[vv] = mk(BLK ? fpv[4 + vv] : ldo(fpk + (size_t)(4 + vv) * FE, sid), qpt[vv]);
+                    qmt[vv] = acc;
+                    qmv[vv] = BLK ? fpv[vv] : ldo(fpk + (size_t)vv * FE, sid);
+                    qpv[vv] = BLK ? fpv[4 + vv] : ldo(fpk + (size_t)(4 + vv) * FE, sid);
                 }
-                fr_common_inviscid<D>(pc, qm, qp, nx, ny, 0.0, 0.0, fn, dq);
                 if (VISC) {
-                    D gm[6], gp[6];
+                    double gs[6], dqt[4], dqh[3];   // gs: sum of the two sides' gradient-trace tangents
 #pragma unroll
                     for (int c = 0; c < 6; ++c) {
                         double acc = 0.0;
 #pragma unroll
                         for (int b = 0; b < n; ++b)
                             if (!ZO) acc = acc + lam[b] * s_g[GI(el, c, line_pt(n, f, k, b))];
-                        gm[c] = mk(BLK ? fpv[8 + c] : ldo(fpk + (size_t)(8 + c) * FE, sid), acc);
+                        gs[c] = acc;
                     }
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
@@ -1538,32 +1526,47 @@ k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
 #pragma unroll
                         for (int m = 0; m < n; ++m) dtan = dtan + s_D[lg.k2 * n + m] * s_F[FI(el, c, f * n + m)];
                         const double dxi = lg.nf < 2 ? dnort[c] : dtan, deta = lg.nf < 2 ? dtan : dnort[c];
-                        gp[2 * c] = mk(0.0, lg.mxix * dxi + lg.metx * deta);   // the pack holds g^- + g^+ in gm
-                        gp[2 * c + 1] = mk(0.0, lg.mxiy * dxi + lg.mety * deta);
+                        gs[2 * c] = gs[2 * c] + (lg.mxix * dxi + lg.metx * deta);
+                        gs[2 * c + 1] = gs[2 * c + 1] + (lg.mxiy * dxi + lg.mety * deta);
                     }
-                    const D qcu = qm[1] + 0.5 * dq[1];
-                    const D qcv = qm[2] + 0.5 * dq[2];
-                    D dqh[3];
-                    fr_common_viscous<D>(pc, dq, qcu, qcv, gm, gp, nx, ny, lg.cc, fn, dqh);
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) s_dq[DI(el, c, lt)] = dqh[c].d[0];
+                    for (int vv = 0; vv < 4; ++vv) dqt[vv] = qpt[vv] - qmt[vv];
+                    const double tnx = BLK ? fpv[8] : ldo(fpk + (size_t)8 * FE, sid);
+                    const double tny = BLK ? fpv[9] : ldo(fpk + (size_t)9 * FE, sid);
+                    // q^com velocity: the average of the traces
+                    fr_common_viscous_tan(pc, dqt, 0.5 * (qmv[1] + qpv[1]), 0.5 * (qmv[2] + qpv[2]),
+                                          0.5 * (qmt[1] + qpt[1]), 0.5 * (qmt[2] + qpt[2]), tnx, tny, gs, nx, ny,
+                                          lg.cc, ft, dqh);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) s_dq[DI(el, c, lt)] = dqh[c];
                 }
+                D fn[4], dq[4], qm[4], qp[4];
 #pragma unroll
-                for (int vv = 0; vv < 4; ++vv) fsc[vv] = (sc * fn[vv]).d[0];
+                for (int vv = 0; vv < 4; ++vv) { qm[vv] = mk(qmv[vv], qmt[vv]); qp[vv] = mk(qpv[vv], qpt[vv]); }
+                fr_common_inviscid<D>(pc, qm, qp, nx, ny, 0.0, 0.0, fn, dq);
+#pragma unroll
+                for (int vv = 0; vv < 4; ++vv) fsc[vv] = sc * (fn[vv].d[0] + ft[vv]);
             }
             __syncthreads();
             // ---- stage 4: corrected gradient tangent, point flux on dual numbers, contravariant tangents
             double qv[4];
             if (act && lt < Np) {
                 const unsigned id = (unsigned)e * Np + lt;
-                D qs[4], gu[2], gv[2], gT[2];
+                D qs[4];
 #pragma unroll
                 for (int vv = 0; vv < 4; ++vv) {
                     qv[vv] = BLK ? spv[vv] : ldo(spk + (size_t)vv * EN, id);
                     qs[vv] = mk(qv[vv], ZO ? 0.0 : s_q[QI(el, vv, lt)]);
                 }
+                D fl[4], gl[4], qc[4];
+                fr_point_flux<D, false>(pc, qs, nullptr, nullptr, nullptr, fl, gl, qc);
+                double ft[4], gf[4];
+#pragma unroll
+                for (int vv = 0; vv < 4; ++vv) { ft[vv] = fl[vv].d[0]; gf[vv] = gl[vv].d[0]; }
                 if (VISC) {
-                    double gt[6];
+                    double gt[6], tau[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) tau[c] = BLK ? spv[4 + c] : ldo(spk + (size_t)(4 + c) * EN, id);
 #pragma unroll
                     for (int c = 0; c < 6; ++c) gt[c] = ZO ? 0.0 : s_g[GI(el, c, lt)];
                     const int fp0 = 0 * n + j, fp1 = 1 * n + j, fp2 = 2 * n + i, fp3 = 3 * n + i;
@@ -1575,26 +1578,19 @@ k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
                         gt[2 * c] = gt[2 * c] + (lg.xix * lx + lg.etx * le);
                         gt[2 * c + 1] = gt[2 * c + 1] + (lg.xiy * lx + lg.ety * le);
                     }
-#pragma unroll
-                    for (int d = 0; d < 2; ++d) {
-                        gu[d] = mk(BLK ? spv[4 + d] : ldo(spk + (size_t)(4 + d) * EN, id), gt[d]);
-                        gv[d] = mk(BLK ? spv[6 + d] : ldo(spk + (size_t)(6 + d) * EN, id), gt[2 + d]);
-                        gT[d] = mk(BLK ? spv[8 + d] : ldo(spk + (size_t)(8 + d) * EN, id), gt[4 + d]);
-                    }
+                    fr_point_viscous_tan(pc, qv[1], qv[2], qs[1].d[0], qs[2].d[0], tau, gt, ft, gf);
                 }
-                D fl[4], gl[4], qc[4];
-                fr_point_flux<D, VISC>(pc, qs, gu, gv, gT, fl, gl, qc);
 #pragma unroll
                 for (int vv = 0; vv < 4; ++vv) {
-                    s_w[WI(el, vv, lt)] = lg.xix * fl[vv].d[0] + lg.xiy * gl[vv].d[0];
-                    s_w[WI(el, 4 + vv, lt)] = lg.etx * fl[vv].d[0] + lg.ety * gl[vv].d[0];
+                    s_w[WI(el, vv, lt)] = lg.xix * ft[vv] + lg.xiy * gf[vv];
+                    s_w[WI(el, 4 + vv, lt)] = lg.etx * ft[vv] + lg.ety * gf[vv];
                 }
             }
             __syncthreads();
             // ---- stage 5: F^num' - F^loc'
             if (act && lt < NF) {
                 const double* lam = s_lam[f & 1];
-                const double jac = 1.0 / lg.ij;
+                const double jac = frcp(lg.ij);
                 const int base = f < 2 ? 0 : 4;
 #pragma unroll
                 for (int vv = 0; vv < 4; ++vv) {

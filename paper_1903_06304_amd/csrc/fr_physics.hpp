@@ -8,7 +8,8 @@
 //    compact row form  r0 = a dp + rho_T dT,  r1 = u r0 + rho du,  r2 = v r0 + rho dv,
 //    r3 = h r0 - dp + rho (u du + v dv) + rho Cp dT  with a = rho_p (M) or Theta (Gamma)
 //  - reference velocity U_r = eps c, eps = min(1, max(kappa Ma_inf, Ma)), Ma from
-//    v - v_g, Eqs. (eps_nonmove), (eps_move)
+//    v - v_g, Eqs. (eps_nonmove), (eps_move); only U_r^2 and eps^2 are needed, and both follow
+//    from |v - v_g|^2 and c^2 without a square root (fr_ur2)
 //  - preconditioned Rusanov flux, Eq. (Rosanov), with |lambda|max = |u_n'| + c' of
 //    Eqs. (eigenvalues), (eigenvalues_para) (alpha = (1 - eps^2)/2 because
 //    beta U_r^2 = eps^2 for an ideal gas), moving-face normal flux of Sec. 3.1
@@ -24,7 +25,8 @@
 struct PhysConst {
     double gam, Rg, Cp, inv_gm1, gRg, inv_Cp, inv_Rg;
     double mu_re, kc_re;      // mu/Re, (mu Cp/Pr)/Re
-    double eps_min;           // kappa * Ma_inf
+    double eps_min2;          // (kappa * Ma_inf)^2
+    double inv_gRg;           // 1 / (gamma R)
     double br2;               // (p+1)^2 / 2
 };
 
@@ -39,10 +41,10 @@ FR_DEV void fr_cons(const PhysConst& c, const T* q, T* qc) {
 }
 
 // Total physical flux (f, g) = (f_inv - f_vis, g_inv - g_vis) and q^c at a point.
-// gu, gv, gT: (d/dx, d/dy) of u, v, T.
+// gu, gv, gT: (d/dx, d/dy) of u, v, T.  tau (may be null): the stresses (txx, tyy, txy).
 template <class T, bool VISC>
 FR_DEV void fr_point_flux(const PhysConst& c, const T* q, const T* gu, const T* gv, const T* gT,
-                         T* f, T* g, T* qc) {
+                         T* f, T* g, T* qc, T* tau = nullptr) {
     fr_cons(c, q, qc);
     const T& p = q[0]; const T& u = q[1]; const T& v = q[2];
     T Ep = qc[3] + p;
@@ -66,14 +68,34 @@ FR_DEV void fr_point_flux(const PhysConst& c, const T* q, const T* gu, const T* 
         g[1] = g[1] - txy;
         g[2] = g[2] - tyy;
         g[3] = g[3] - (u * txy + v * tyy + c.kc_re * gT[1]);
+        if (tau) { tau[0] = txx; tau[1] = tyy; tau[2] = txy; }
     }
 }
 
-// eps of the preconditioner from the velocity relative to the grid and the sound speed
+// Tangent of the viscous part of the total flux, subtracted from the tangents f, g: the stresses are
+// linear in the gradient, so of the linearisation point only the velocity (u, v) and the stresses
+// tau = (txx, tyy, txy) enter.  ut, vt: velocity tangent; gt: gradient tangent (ux, uy, vx, vy, Tx, Ty).
+FR_DEV void fr_point_viscous_tan(const PhysConst& c, double u, double v, double ut, double vt, const double* tau,
+                                 const double* gt, double* f, double* g) {
+    const double div = gt[0] + gt[3];
+    const double txx = c.mu_re * (2.0 * gt[0] - (2.0 / 3.0) * div);
+    const double tyy = c.mu_re * (2.0 * gt[3] - (2.0 / 3.0) * div);
+    const double txy = c.mu_re * (gt[1] + gt[2]);
+    f[1] = f[1] - txx;
+    f[2] = f[2] - txy;
+    f[3] = f[3] - (ut * tau[0] + u * txx + vt * tau[2] + v * txy + c.kc_re * gt[4]);
+    g[1] = g[1] - txy;
+    g[2] = g[2] - tyy;
+    g[3] = g[3] - (ut * tau[2] + u * txy + vt * tau[1] + v * tyy + c.kc_re * gt[5]);
+}
+
+// U_r^2 = min(c^2, max(eps_min^2 c^2, |v - v_g|^2)), the square of eps c: the comparisons, ties and
+// branches are those of eps = min(1, max(eps_min, Ma)).  Not a number where c^2 is negative (or not a
+// number), as its square root would be.
 template <class T>
-FR_DEV T fr_eps(const PhysConst& c, const T& urel, const T& vrel, const T& cs) {
-    T Ma = ssqrt(urel * urel + vrel * vrel) * rcp(cs);
-    return smin(cst<T>(1.0), smax(cst<T>(c.eps_min), Ma));
+FR_DEV T fr_ur2(const PhysConst& c, const T& urel, const T& vrel, const T& c2) {
+    const T r = smin(c2, smax(c.eps_min2 * c2, urel * urel + vrel * vrel));
+    return val(c2) >= 0.0 ? r : cst<T>(__builtin_nan(""));
 }
 
 // out = (a-row matrix) * dq with a = rho_p (M) or Theta (Gamma); state q.
@@ -95,10 +117,8 @@ FR_DEV void fr_time_apply(const PhysConst& c, const T* q, double ug, double vg, 
     T rho = q[0] * c.inv_Rg * iT;
     T rhoT = -rho * iT;
     T rhop = c.inv_Rg * iT;
-    T cs = ssqrt(c.gRg * q[3]);
-    T eps = fr_eps(c, q[1] - ug, q[2] - vg, cs);
-    T Ur = eps * cs;
-    T theta = rcp(Ur * Ur) + c.inv_Cp * iT;
+    T Ur2 = fr_ur2<T>(c, q[1] - ug, q[2] - vg, c.gRg * q[3]);
+    T theta = rcp(Ur2) + c.inv_Cp * iT;
     T h = c.Cp * q[3] + 0.5 * (q[1] * q[1] + q[2] * q[2]);
     V a[4], b[4];
     fr_gm_apply(c, theta, rho, rhoT, h, q, x, a);
@@ -137,18 +157,15 @@ FR_DEV void fr_common_inviscid(const PhysConst& c, const T* qm, const T* qp, dou
     }
     T iT = rcp(qb[3]);
     T rho = qb[0] * c.inv_Rg * iT;
-    T cs = ssqrt(c.gRg * qb[3]);
     T ur = qb[1] - ug, vr = qb[2] - vg;
-    T eps = fr_eps(c, ur, vr, cs);
-    T Ur = eps * cs;
-    T Ur2 = Ur * Ur;
+    T Ur2 = fr_ur2<T>(c, ur, vr, c.gRg * qb[3]);
     T theta = rcp(Ur2) + c.inv_Cp * iT;
     T rhoT = -rho * iT;
     T h = c.Cp * qb[3] + 0.5 * (qb[1] * qb[1] + qb[2] * qb[2]);
     T gd[4];
     fr_gm_apply(c, theta, rho, rhoT, h, qb, dq, gd);
     T un = ur * nx + vr * ny;
-    T alpha = 0.5 * (1.0 - eps * eps);
+    T alpha = 0.5 * (1.0 - Ur2 * (c.inv_gRg * iT));   // eps^2 = U_r^2 / c^2
     T unp = un * (1.0 - alpha);
     T cp = ssqrt(alpha * alpha * un * un + Ur2);
     T lam = sabs(unp) + cp;
@@ -160,10 +177,10 @@ FR_DEV void fr_common_inviscid(const PhysConst& c, const T* qm, const T* qp, dou
 // gradient grad q^com = (g^- + g^+)/2 + cc (q^+ - q^-) n  (cc = (p+1)^2/8 |S| (1/|J|^- + 1/|J|^+),
 // the face-local Radau liftings of both sides evaluated at the face);
 // gm, gp: uncorrected gradient traces (ux, uy, vx, vy, Tx, Ty); qcu, qcv: q^com velocity.
-// Returns dqh = q^com - q^- for (u, v, T).
+// Returns dqh = q^com - q^- for (u, v, T), and (tn, may be null) the stress vector tau . n.
 template <class T>
 FR_DEV void fr_common_viscous(const PhysConst& c, const T* dq, const T& qcu, const T& qcv, const T* gm,
-                              const T* gp, double nx, double ny, double cc, T* fn, T* dqh) {
+                              const T* gp, double nx, double ny, double cc, T* fn, T* dqh, T* tn = nullptr) {
     T ux = 0.5 * (gm[0] + gp[0]) + (cc * nx) * dq[1];
     T uy = 0.5 * (gm[1] + gp[1]) + (cc * ny) * dq[1];
     T vx = 0.5 * (gm[2] + gp[2]) + (cc * nx) * dq[2];
@@ -178,6 +195,32 @@ FR_DEV void fr_common_viscous(const PhysConst& c, const T* dq, const T& qcu, con
     fn[1] = fn[1] - tnx;
     fn[2] = fn[2] - tny;
     fn[3] = fn[3] - (qcu * tnx + qcv * tny + c.kc_re * Tn);
+    dqh[0] = 0.5 * dq[1];
+    dqh[1] = 0.5 * dq[2];
+    dqh[2] = 0.5 * dq[3];
+    if (tn) { tn[0] = tnx; tn[1] = tny; }
+}
+
+// Tangent of fr_common_viscous, subtracted from the flux tangent ft: linear in the gradients, so of
+// the linearisation point only the common velocity and the stress vector (tnx, tny) enter.  dq: jump
+// tangents; (qcu, qcv), (qcut, qcvt): common velocity and its tangent; gs: sum of the two sides'
+// gradient-trace tangents.  Returns the tangent of dqh.
+FR_DEV void fr_common_viscous_tan(const PhysConst& c, const double* dq, double qcu, double qcv, double qcut,
+                                  double qcvt, double tnx, double tny, const double* gs, double nx, double ny,
+                                  double cc, double* ft, double* dqh) {
+    const double ux = 0.5 * gs[0] + (cc * nx) * dq[1];
+    const double uy = 0.5 * gs[1] + (cc * ny) * dq[1];
+    const double vx = 0.5 * gs[2] + (cc * nx) * dq[2];
+    const double vy = 0.5 * gs[3] + (cc * ny) * dq[2];
+    const double Tn = 0.5 * (gs[4] * nx + gs[5] * ny) + cc * dq[3];
+    const double div = ux + vy;
+    const double txx = c.mu_re * (2.0 * ux - (2.0 / 3.0) * div);
+    const double tyy = c.mu_re * (2.0 * vy - (2.0 / 3.0) * div);
+    const double txy = c.mu_re * (uy + vx);
+    const double tnxt = txx * nx + txy * ny, tnyt = txy * nx + tyy * ny;
+    ft[1] = ft[1] - tnxt;
+    ft[2] = ft[2] - tnyt;
+    ft[3] = ft[3] - (qcut * tnx + qcu * tnxt + qcvt * tny + qcv * tnyt + c.kc_re * Tn);
     dqh[0] = 0.5 * dq[1];
     dqh[1] = 0.5 * dq[2];
     dqh[2] = 0.5 * dq[3];

@@ -14,7 +14,7 @@
 //      written to a per-side buffer;
 //   3. k_vjp_gather: each element collects, from its neighbours' side buffers, the
 //      adjoint of its own traces and applies the trace / gradient transposes.
-// Non-smooth points follow the forward convention: eps = Ma only when
+// Non-smooth points follow the forward convention: U_r^2 = |v - v_g|^2 only when
 // eps_min < Ma < 1, d|x|/dx = +1 at x = 0.
 #include "fr_internal.hpp"
 
@@ -44,7 +44,7 @@ template <bool VISC>
 __device__ void point_flux_rev(const PhysConst& c, const double* q, const double* G, const double* af,
                                const double* ag, const double* aqc, double* aq, double* aG) {
     const double p = q[0], u = q[1], v = q[2], T = q[3];
-    const double iT = 1.0 / T;   // one division; the quotients below multiply by it
+    const double iT = frcp(T);   // the quotients below multiply by it
     const double rho = p * c.inv_Rg * iT;
     const double ru = rho * u, rv = rho * v, k2 = u * u + v * v;
     const double E = p * c.inv_gm1 + 0.5 * rho * k2;
@@ -96,7 +96,7 @@ __device__ void point_flux_rev(const PhysConst& c, const double* q, const double
 __device__ void normal_flux_rev(const PhysConst& c, const double* q, double nx, double ny, double vgn,
                                 const double* a, double* aq) {
     const double p = q[0], u = q[1], v = q[2], T = q[3];
-    const double iT = 1.0 / T;
+    const double iT = frcp(T);
     const double rho = p * c.inv_Rg * iT;
     const double ru = rho * u, rv = rho * v;
     const double E = p * c.inv_gm1 + 0.5 * rho * (u * u + v * v);
@@ -140,25 +140,16 @@ __device__ void common_flux_rev(const PhysConst& c, const double* qm, const doub
     const double vgn = ug * nx + vg * ny;
     double qb[4], dq[4];
     for (int r = 0; r < 4; ++r) { qb[r] = 0.5 * (qm[r] + qp[r]); dq[r] = qp[r] - qm[r]; }
-    // reciprocals taken once: T, c, U_r^2 (and |v - v_g|, c' below)
-    const double iT = 1.0 / qb[3];
+    const double iT = frcp(qb[3]);
     const double rho = qb[0] * c.inv_Rg * iT;
-    const double cs = sqrt(c.gRg * qb[3]);
-    const double ics = 1.0 / cs;
+    const double c2 = c.gRg * qb[3];
     const double ur = qb[1] - ug, vr = qb[2] - vg;
-    const double mg = sqrt(ur * ur + vr * vr);
-    const double Ma = mg * ics;
-    // eps = min(1, max(eps_min, Ma)) with the forward tie rules
-    double eps;
-    bool ma_branch = false;
-    {
-        const double t = (c.eps_min >= Ma) ? c.eps_min : Ma;
-        const bool took_ma = !(c.eps_min >= Ma);
-        eps = (1.0 <= t) ? 1.0 : t;
-        ma_branch = took_ma && !(1.0 <= t);
-    }
-    const double Ur = eps * cs, Ur2 = Ur * Ur;
-    const double iUr2 = 1.0 / Ur2;
+    // U_r^2 = min(c^2, max(eps_min^2 c^2, |v - v_g|^2)) with the forward tie rules
+    const double v2 = ur * ur + vr * vr, lo = c.eps_min2 * c2;
+    const double t2 = lo >= v2 ? lo : v2;
+    const bool took_c = c2 <= t2, took_v = !(lo >= v2) && !took_c;
+    const double Ur2 = c2 >= 0.0 ? (took_c ? c2 : t2) : __builtin_nan("");
+    const double iUr2 = frcp(Ur2);
     const double theta = iUr2 + c.inv_Cp * iT;
     const double rhoT = -rho * iT;
     const double h = c.Cp * qb[3] + 0.5 * (qb[1] * qb[1] + qb[2] * qb[2]);
@@ -169,9 +160,11 @@ __device__ void common_flux_rev(const PhysConst& c, const double* qm, const doub
     gd[2] = qb[2] * r0 + rho * dq[2];
     gd[3] = h * r0 - dq[0] + rho * (qb[1] * dq[1] + qb[2] * dq[2]) + (rho * c.Cp) * dq[3];
     const double un = ur * nx + vr * ny;
-    const double alpha = 0.5 * (1.0 - eps * eps);
+    const double eps2 = Ur2 * (c.inv_gRg * iT);
+    const double alpha = 0.5 * (1.0 - eps2);
     const double unp = un * (1.0 - alpha);
-    const double cp = sqrt(alpha * alpha * un * un + Ur2);
+    double cp, hicp;   // c' and 1 / (2 c')
+    fsqrt_both(alpha * alpha * un * un + Ur2, cp, hicp);
     const double lam = (unp >= 0.0 ? unp : -unp) + cp;
 
     double a_qb[4] = {0, 0, 0, 0}, a_dq[4] = {0, 0, 0, 0};
@@ -215,13 +208,15 @@ __device__ void common_flux_rev(const PhysConst& c, const double* qm, const doub
     }
     const double a_unp = a_lam * (unp >= 0.0 ? 1.0 : -1.0);
     const double a_cp = a_lam;
-    const double a_X = a_cp * (0.5 / cp);
+    const double a_X = a_cp * hicp;
     double a_alpha = a_X * 2.0 * alpha * un * un;
     double a_un = a_X * 2.0 * alpha * alpha * un;
     double a_Ur2 = a_X;
     a_un += a_unp * (1.0 - alpha);
     a_alpha -= a_unp * un;
-    double a_eps = -a_alpha * eps;
+    const double a_eps2 = -0.5 * a_alpha;
+    a_Ur2 += a_eps2 * (c.inv_gRg * iT);
+    a_qb[3] -= a_eps2 * eps2 * iT;
     double a_ur = a_un * nx, a_vr = a_un * ny;
     // gd = Gamma~(qb) dq
     double a_r0 = a_gd[0];
@@ -242,20 +237,14 @@ __device__ void common_flux_rev(const PhysConst& c, const double* qm, const doub
     a_qb[3] += a_rhoT * rho * iT * iT;   // d(-rho/T)/dT = rho/T^2
     a_Ur2 -= a_theta * iUr2 * iUr2;
     a_qb[3] -= a_theta * c.inv_Cp * iT * iT;
-    const double a_Ur = 2.0 * Ur * a_Ur2;
-    a_eps += a_Ur * cs;
-    double a_cs = a_Ur * eps;
-    if (ma_branch) {
-        const double a_Ma = a_eps;
-        const double a_mg = a_Ma * ics;
-        a_cs -= a_Ma * Ma * ics;
-        const double img = 1.0 / mg;   // Ma > eps_min >= 0 on this branch, so mg > 0
-        a_ur += a_mg * ur * img;
-        a_vr += a_mg * vr * img;
+    if (took_v) {
+        a_ur += 2.0 * a_Ur2 * ur;
+        a_vr += 2.0 * a_Ur2 * vr;
+    } else {
+        a_qb[3] += a_Ur2 * (took_c ? 1.0 : c.eps_min2) * c.gRg;
     }
     a_qb[1] += a_ur;
     a_qb[2] += a_vr;
-    a_qb[3] += a_cs * c.gRg * (0.5 * ics);
     a_qb[0] += a_rho * c.inv_Rg * iT;
     a_qb[3] -= a_rho * rho * iT;
     for (int r = 0; r < 4; ++r) {
