@@ -26,8 +26,9 @@
  *    maximum and an inverse stored at up to a stated precision; after it those calls
  *    allocate no device memory (a step that captures its GMRES cycle still builds the
  *    graph on its first call, in the runtime's own memory).  Without fr_reserve the first
- *    factor allocates the blocks and the inverse at its precision, and the first step with
- *    a larger Krylov dimension its workspace; residual, JVP, VJP and apply never allocate.
+ *    factor allocates the blocks, the packs it assembles them from and the inverse at its
+ *    precision, and the first step with a larger Krylov dimension its workspace; residual,
+ *    JVP, VJP and apply never allocate.
  */
 #ifndef LMFR_H
 #define LMFR_H
@@ -251,8 +252,8 @@ fr_status fr_steady_solve(fr_ctx ctx, double* q, const fr_steady_opts* opts, fr_
  * passes, the first pass's update and the second pass's dot products share one read of
  * the basis, up to 32 basis vectors; same results bit for bit), "operator_packs" (0/1: fr_bdf_operator first
  * stores the values its nonlinear point functions need at q, then applies the operator
- * on tangents only -- the form the BDF2 step uses inside GMRES; fr_block_jacobi_factor
- * assembles its block columns the same way; same results to rounding), "preconditioner"
+ * on tangents only -- the form the BDF2 step uses inside GMRES; same results to rounding;
+ * fr_block_jacobi_factor always forms its blocks from those values), "preconditioner"
  * (0: element-block Jacobi, the default; 1: symmetric block Gauss-Seidel over the
  * elements in colour order, P = (D + L) D^-1 (D + U) with D the element blocks and L / U
  * the couplings of the Newton operator to elements of lower / higher colour -- colours

@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblmfr.so")
 BUILD = os.path.join(ROOT, "_build")
-SOURCES = ["fr_invert.hip", "fr_fused_p3.hip", "fr_fused_p4.hip", "fr_fused_p2.hip", "fr_fused_p1.hip", "fr_api.hip",
+SOURCES = ["fr_invert.hip", "fr_fused_p3.hip", "fr_fused_p4.hip", "fr_fused_p2.hip", "fr_fused_p1.hip", "fr_assembly.hip", "fr_api.hip",
            "fr_kernels.hip", "fr_vjp.hip", "fr_linalg.hip", "fr_gmres.hip", "fr_solver.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

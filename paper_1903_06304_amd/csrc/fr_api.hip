@@ -187,6 +187,9 @@ extern "C" fr_status fr_create(const fr_params* prm, const int32_t* h_nbr, const
             if (nb == e && nf == f) return bad("fr_create: a face cannot neighbour itself");
             packed[(size_t)e * 4 + f] = nb * 8 + nf * 2 + fl;
         }
+    bool self_nb = false;
+    for (int e = 0; e < E; ++e)
+        for (int f = 0; f < 4; ++f) self_nb = self_nb || h_nbr[e * 4 + f] == e;
     // colours of the Gauss-Seidel sweeps: in element order, the smallest colour no face
     // neighbour has yet (a checkerboard on even periodic meshes; at most 5 colours)
     std::vector<int32_t> colour((size_t)E, -1);
@@ -215,6 +218,7 @@ extern "C" fr_status fr_create(const fr_params* prm, const int32_t* h_nbr, const
     fr_ctx c = new fr_ctx_s();
     c->prm = *prm;
     c->ncolors = ncol;
+    c->self_neighbour = self_nb;
     c->cofs = cofs;
     c->p = prm->order; c->n = c->p + 1; c->Np = c->n * c->n;
     c->pg = prm->geom_order; c->m = c->pg + 1; c->E = E;
@@ -286,6 +290,13 @@ static bool is_tile_option(const char* name) {
     return !strcmp(name, "tile_lanes") || !strcmp(name, "tile_grid") || !strcmp(name, "tile_xcd");
 }
 
+// linearisation packs and the R of the pass that writes them
+static fr_status ensure_packs(Solver& sv) {
+    FR_TRY(dalloc(&sv.d_fpack, sv.fpack_len));
+    FR_TRY(dalloc(&sv.d_spack, sv.spack_len));
+    return dalloc(&sv.d_rscratch, sv.Ntot);
+}
+
 // solver options shared by contexts and batches; returns FR_EINVAL with no message for
 // names it does not know
 static fr_status solver_option(Solver& sv, const char* name, int64_t value) {
@@ -300,11 +311,7 @@ static fr_status solver_option(Solver& sv, const char* name, int64_t value) {
     if (!strcmp(name, "preconditioner")) {
         if (value < 0 || value > 2)
             return bad("preconditioner must be 0 (block Jacobi), 1 (symmetric block Gauss-Seidel) or 2 (forward block Gauss-Seidel)");
-        if (value != 0) {   // the sweeps apply the Newton operator through the linearisation packs
-            FR_TRY(dalloc(&sv.d_fpack, sv.fpack_len));
-            FR_TRY(dalloc(&sv.d_spack, sv.spack_len));
-            FR_TRY(dalloc(&sv.d_rscratch, sv.Ntot));
-        }
+        if (value != 0) FR_TRY(ensure_packs(sv));   // the sweeps apply the Newton operator through the packs
         sv.precond = (int)value;
         gmres_release(sv);
         return FR_OK;
@@ -336,11 +343,7 @@ extern "C" fr_status fr_set_option(fr_ctx c, const char* name, int64_t value) {
     Solver& sv = *c->self;
     if (!strcmp(name, "keep_blocks")) { sv.keep_blocks = value != 0; return FR_OK; }
     if (!strcmp(name, "operator_packs")) {
-        if (value) {
-            FR_TRY(dalloc(&sv.d_fpack, sv.fpack_len));
-            FR_TRY(dalloc(&sv.d_spack, sv.spack_len));
-            FR_TRY(dalloc(&sv.d_rscratch, sv.Ntot));
-        }
+        if (value) FR_TRY(ensure_packs(sv));
         sv.op_packs = value != 0;
         return FR_OK;
     }
@@ -429,13 +432,12 @@ extern "C" fr_status fr_block_jacobi_factor(fr_ctx c, const double* q, double c_
     KArgs a{};
     a.c_time = c_time; a.inv_dtau = inv_dtau;
     sv.f_ct = c_time; sv.f_idt = inv_dtau;
-    if (sv.op_packs || sv.precond != 0) {
-        // linearisation packs of q, then tangent-only block columns
-        KArgs p = plain_args(q, nullptr, sv.d_rscratch, nullptr);
-        p.fpack = sv.d_fpack; p.spack = sv.d_spack;
-        FR_TRY(solver_fused(sv, MODE_PREP, p, s));
-        a.fpack = sv.d_fpack; a.spack = sv.d_spack;
-    }
+    // linearisation packs of q, from which the blocks are written down
+    FR_TRY(ensure_packs(sv));
+    KArgs p = plain_args(q, nullptr, sv.d_rscratch, nullptr);
+    p.fpack = sv.d_fpack; p.spack = sv.d_spack;
+    FR_TRY(solver_fused(sv, MODE_PREP, p, s));
+    a.fpack = sv.d_fpack; a.spack = sv.d_spack;
     FR_TRY(launch_block_assembly(sv, q, a, s));
     if (sv.keep_blocks) FR_HIP(hipMemcpyAsync(sv.d_blk_keep, sv.d_blk, sv.Btot * sizeof(double), hipMemcpyDeviceToDevice, s));
     // a zero pivot marks the case status; reading it synchronises once per refresh

@@ -3,7 +3,8 @@
 //   R      the residual (paper Eq. cpr_ns with the moving-mesh terms),
 //   JVP    the exact forward tangent Jv (and optionally R),
 //   AOP    the Newton operator  Av = inv_dtau Gamma v + c_time M v - Jv,
-//   BLK    one seeded column of every element's diagonal block of that operator.
+// and, from the linearisation packs of a state, that operator on tangents alone (k_lin) and one
+// seeded column of every element's diagonal block of it.
 //
 // Work mapping: a workgroup tile holds EPB elements of one case; each element owns
 // NT = max(Np, 4n) lanes, lane `lt` acting as solution point lt (lt < Np) and as flux
@@ -50,42 +51,16 @@ template <int MODE, int K> struct ModeT { using T = Dual<K>; };
 template <int K> struct ModeT<MODE_R, K> { using T = double; };
 template <int K> struct ModeT<MODE_PREP, K> { using T = double; };
 
-// own state with the tangent the mode asks for: JVP/AOP carry v; block mode seeds the
-// unit column seed0 (+k)
+// a state entry, with the tangent of v for the dual-number modes
 template <class T> struct Seed;
 template <> struct Seed<double> {
-    __device__ static double load(const KArgs& a, const double* q, const double*, unsigned gid, int) { return ldo(q, gid); }
+    __device__ static double load(const double* q, const double*, unsigned gid) { return ldo(q, gid); }
 };
 template <int K> struct Seed<Dual<K>> {
-    __device__ static Dual<K> load(const KArgs& a, const double* q, const double* v, unsigned gid, int col) {
+    __device__ static Dual<K> load(const double* q, const double* v, unsigned gid) {
         Dual<K> r; r.v = ldo(q, gid);
-        if (v) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) r.d[k] = ldo(v, gid);
-        } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) r.d[k] = (col == a.seed0 + k) ? 1.0 : 0.0;
-        }
-        return r;
-    }
-};
-
-// neighbour state: block mode seeds only when the neighbour is the element itself
-// (periodic single-element rows)
-template <class T> struct NbLoad;
-template <> struct NbLoad<double> {
-    __device__ static double load(const KArgs&, const double* q, const double*, unsigned gid, int, bool) { return ldo(q, gid); }
-};
-template <int K> struct NbLoad<Dual<K>> {
-    __device__ static Dual<K> load(const KArgs& a, const double* q, const double* v, unsigned gid, int col, bool self) {
-        Dual<K> r; r.v = ldo(q, gid);
-        if (v) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) r.d[k] = ldo(v, gid);
-        } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) r.d[k] = (self && col == a.seed0 + k) ? 1.0 : 0.0;
-        }
+        for (int k = 0; k < K; ++k) r.d[k] = ldo(v, gid);
         return r;
     }
 };
@@ -318,7 +293,7 @@ k_fused(GroupArgs ga, KArgs a, OpTab op) {
             const unsigned id = (unsigned)e * Np + ls;
             T qo[4];
 #pragma unroll
-            for (int vv = 0; vv < 4; ++vv) qo[vv] = Seed<T>::load(a, q + vv * EN, v ? v + vv * EN : nullptr, id, vv * Np + ls);
+            for (int vv = 0; vv < 4; ++vv) qo[vv] = Seed<T>::load(q + vv * EN, v ? v + vv * EN : nullptr, id);
             // the lane's own face entry is loaded on its own: selecting it from pk4 by the lane's
             // face makes the compiler index a stack copy of pk4 (scratch memory)
             lane_geo_load<P, VISC, MOV>(g, E, e, lt, ldo(g.nbr, (unsigned)(e * 4 + (lt % NF) / n)), lg);
@@ -331,7 +306,7 @@ k_fused(GroupArgs ga, KArgs a, OpTab op) {
                     const unsigned nid = (unsigned)nb * Np + lt;
 #pragma unroll
                     for (int vv = 0; vv < 4; ++vv)
-                        s_n[NI(el, ff * 4 + vv, lt)] = NbLoad<T>::load(a, q + vv * EN, v ? v + vv * EN : nullptr, nid, vv * Np + lt, nb == e);
+                        s_n[NI(el, ff * 4 + vv, lt)] = Seed<T>::load(q + vv * EN, v ? v + vv * EN : nullptr, nid);
                 }
             }
         }
@@ -562,7 +537,7 @@ k_fused(GroupArgs ga, KArgs a, OpTab op) {
                 for (int vv = 0; vv < 4; ++vv) { qv[vv] = qs[vv].v; x[vv] = qs[vv].d[0]; }
                 fr_time_apply<double, double>(pc, qv, geo[G_UG], geo[G_VG], idt, ct, x, tt);
             }
-            double* out = a.out + ((MODE == MODE_BLK) ? cd.boff : cd.off);
+            double* out = a.out + cd.off;
 #pragma unroll 1
             for (int vv = 0; vv < 4; ++vv) {
                 if constexpr (TAN) {
@@ -619,34 +594,6 @@ k_fused(GroupArgs ga, KArgs a, OpTab op) {
                 } else if constexpr (MODE == MODE_AOP) {
                     const double ttv = (vv == 0) ? tt[0] : (vv == 1) ? tt[1] : (vv == 2) ? tt[2] : tt[3];
                     out[vv * EN + id] = ttv - R.d[0];
-                } else {
-                    // block columns seed0..seed0+K-1 of element e, column-major [E][nb][nb]
-                    constexpr int nbk = 4 * Np;
-                    double* blk = out + (size_t)e * nbk * nbk;
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        const int col = a.seed0 + k;
-                        if (col < nbk) blk[(size_t)col * nbk + vv * Np + lt] = -R.d[k];
-                    }
-                }
-            }
-            if constexpr (MODE == MODE_BLK) {
-                // time terms on the diagonal point block of the seeded columns
-                constexpr int nbk = 4 * Np;
-                double* blk = out + (size_t)e * nbk * nbk;
-                double qv[4];
-#pragma unroll
-                for (int vv = 0; vv < 4; ++vv) qv[vv] = qs[vv].v;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const int col = a.seed0 + k;
-                    if (col < nbk && col % Np == lt) {
-                        double x[4] = {0.0, 0.0, 0.0, 0.0}, t4[4];
-                        x[col / Np] = 1.0;
-                        fr_time_apply<double, double>(pc, qv, geo[G_UG], geo[G_VG], idt, ct, x, t4);
-#pragma unroll
-                        for (int vv = 0; vv < 4; ++vv) blk[(size_t)col * nbk + vv * Np + lt] += t4[vv];
-                    }
                 }
             }
         }
@@ -744,7 +691,7 @@ k_fused_aff(GroupArgs ga, KArgs a, OpTab op) {
             const unsigned id = (unsigned)e * Np + ls;
             T qo[4];
 #pragma unroll
-            for (int vv = 0; vv < 4; ++vv) qo[vv] = Seed<T>::load(a, q + vv * EN, v ? v + vv * EN : nullptr, id, vv * Np + ls);
+            for (int vv = 0; vv < 4; ++vv) qo[vv] = Seed<T>::load(q + vv * EN, v ? v + vv * EN : nullptr, id);
             lane_geo_load<P, VISC, false>(g, E, e, lt, pk, lg);
             if (lt < NF) {
                 const unsigned nbase = (unsigned)lg.nb * Np;
@@ -754,7 +701,7 @@ k_fused_aff(GroupArgs ga, KArgs a, OpTab op) {
                     const int sp = line_pt(n, lg.nf, lg.k2, b);
 #pragma unroll
                     for (int vv = 0; vv < 4; ++vv)
-                        ln[vv][b] = NbLoad<T>::load(a, q + vv * EN, v ? v + vv * EN : nullptr, nbase + sp, vv * Np + sp, lg.nb == e);
+                        ln[vv][b] = Seed<T>::load(q + vv * EN, v ? v + vv * EN : nullptr, nbase + sp);
                 }
                 const double* lamn = s_lam[lg.nf & 1];
                 const double* dlamn = s_dlam[lg.nf & 1];
@@ -1338,8 +1285,8 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
 // The Newton operator from the linearisation packs (as k_lin) for static groups whose elements
 // are all affine, with the changes of k_fused_aff: neighbour tangent lines read into
 // registers, the neighbour gradient trace from its traces, contravariant flux tangents, face
-// vectors from the constant metrics.  BLK: one seeded block column per launch.
-template <int P, bool VISC, int LANES, bool BLK, bool CS = false>
+// vectors from the constant metrics.
+template <int P, bool VISC, int LANES, bool CS = false>
 __global__ void __launch_bounds__((Shape<P, LANES>::threads))
 k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
     using D = Dual<1>;
@@ -1368,7 +1315,7 @@ k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
 
     // a Gauss-Seidel coupling pass: the element's own tangent is zero, and so are its gradient,
     // its traces and its time terms, which are therefore not formed
-    constexpr bool ZO = CS && !BLK;
+    constexpr bool ZO = CS;
     const int el = threadIdx.x / NT, lt = threadIdx.x % NT;
     for (int t = threadIdx.x; t < n * n; t += blockDim.x) s_D[t] = op.D[t];
     if (threadIdx.x < n) {
@@ -1391,251 +1338,223 @@ k_lin_aff(GroupArgs ga, KArgs a, OpTab op) {
         bool act;
         const int e = tile_elem(ga, g, lo, tile, EPB, el, E, act);
         const unsigned EN = (unsigned)E * Np;
-        const double* v = BLK ? nullptr : a.v + cd.off;
+        const double* v = a.v + cd.off;
         const double* fpk = a.fpack + cd.fpoff;
         const double* spk = a.spack + cd.spoff;
         __syncthreads();
         LaneGeo lg;
-        // block columns: the connectivity, the metric terms and the packs once per tile, for
-        // every column of the launch (a.ncols from seed0)
-        double fpv[10], spv[7];
-        if constexpr (BLK) {
-            if (act) {
-                lane_geo_load<P, VISC, false>(g, E, e, lt, ldo(g.nbr, (unsigned)(e * 4 + f)), lg);
-                if (lt < NF) {
-                    const unsigned FE = (unsigned)E * NF, sid = (unsigned)e * NF + lt;
+        // ---- stage 1: own tangent; the neighbour's tangent line through this face point
+        double qpt[4], dnort[3];
+        if (act) {
+            const int ls = lt % Np;
+            const unsigned id = (unsigned)e * Np + ls;
+            // a Gauss-Seidel coupling pass takes v on elements of lower (higher) colours only, so
+            // never on the element itself
+            constexpr bool cs = CS;
+            double qo[4];
 #pragma unroll
-                    for (int c = 0; c < npf(VISC); ++c) fpv[c] = ldo(fpk + (size_t)c * FE, sid);
+            for (int vv = 0; vv < 4; ++vv)
+                qo[vv] = cs ? 0.0 : ldo(v + vv * EN, id);
+            lane_geo_load<P, VISC, false>(g, E, e, lt, ldo(g.nbr, (unsigned)(e * 4 + f)), lg);
+            if (lt < NF) {
+                const unsigned nbase = (unsigned)lg.nb * Np;
+                bool take = true;
+                if (cs) {
+                    const int cn = ldo(g.color, (unsigned)lg.nb);
+                    take = a.cbelow ? cn < a.csweep - 1 : cn > a.csweep - 1;
                 }
-                if (lt < Np) {
-                    const unsigned id = (unsigned)e * Np + lt;
+                double ln[4][n];
 #pragma unroll
-                    for (int c = 0; c < nps(VISC); ++c) spv[c] = ldo(spk + (size_t)c * EN, id);
-                }
-            }
-        }
-        const int c0 = BLK ? a.seed0 : 0;
-        const int c1 = BLK ? min(a.seed0 + max(a.ncols, 1), 4 * Np) : 1;
-        for (int col = c0; col < c1; ++col) {
-            if (col > c0) __syncthreads();   // the previous column's readers of LDS are done
-            // ---- stage 1: own tangent; the neighbour's tangent line through this face point
-            double qpt[4], dnort[3];
-            if (act) {
-                const int ls = lt % Np;
-                const unsigned id = (unsigned)e * Np + ls;
-                // a Gauss-Seidel coupling pass takes v on elements of lower (higher) colours only, so
-                // never on the element itself
-                constexpr bool cs = CS && !BLK;
-                double qo[4];
-#pragma unroll
-                for (int vv = 0; vv < 4; ++vv)
-                    qo[vv] = BLK ? ((vv * Np + ls == col) ? 1.0 : 0.0) : (cs ? 0.0 : ldo(v + vv * EN, id));
-                if constexpr (!BLK) lane_geo_load<P, VISC, false>(g, E, e, lt, ldo(g.nbr, (unsigned)(e * 4 + f)), lg);
-                if (lt < NF) {
-                    const unsigned nbase = (unsigned)lg.nb * Np;
-                    bool take = true;
-                    if (cs) {
-                        const int cn = ldo(g.color, (unsigned)lg.nb);
-                        take = a.cbelow ? cn < a.csweep - 1 : cn > a.csweep - 1;
-                    }
-                    double ln[4][n];
-#pragma unroll
-                    for (int b = 0; b < n; ++b) {
-                        const int sp = line_pt(n, lg.nf, lg.k2, b);
-#pragma unroll
-                        for (int vv = 0; vv < 4; ++vv)
-                            ln[vv][b] = BLK ? ((lg.nb == e && vv * Np + sp == col) ? 1.0 : 0.0)
-                                            : (take ? ldo(v + vv * EN, nbase + sp) : 0.0);
-                    }
-                    const double* lamn = s_lam[lg.nf & 1];
-                    const double* dlamn = s_dlam[lg.nf & 1];
-#pragma unroll
-                    for (int vv = 0; vv < 4; ++vv) {
-                        double acc = 0.0;
-#pragma unroll
-                        for (int b = 0; b < n; ++b) acc = acc + lamn[b] * ln[vv][b];
-                        qpt[vv] = acc;
-                    }
-                    if (VISC) {
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            double acc = 0.0;
-#pragma unroll
-                            for (int b = 0; b < n; ++b) acc = acc + dlamn[b] * ln[c + 1][b];
-                            dnort[c] = acc;
-                            s_F[FI(el, c, f * n + lg.k2)] = qpt[c + 1];
-                        }
-                    }
-                }
-                if (lt < Np) {
+                for (int b = 0; b < n; ++b) {
+                    const int sp = line_pt(n, lg.nf, lg.k2, b);
 #pragma unroll
                     for (int vv = 0; vv < 4; ++vv)
-                        if (!ZO) s_q[QI(el, vv, lt)] = qo[vv];
+                        ln[vv][b] = take ? ldo(v + vv * EN, nbase + sp) : 0.0;
                 }
-            }
-            __syncthreads();
-            // ---- stage 2: uncorrected gradient tangent
-            if (VISC && !ZO && act && lt < Np) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    double dxi = 0.0, deta = 0.0;
-#pragma unroll
-                    for (int b = 0; b < n; ++b) {
-                        dxi = dxi + s_D[i * n + b] * s_q[QI(el, c + 1, b + n * j)];
-                        deta = deta + s_D[j * n + b] * s_q[QI(el, c + 1, i + n * b)];
-                    }
-                    s_g[GI(el, 2 * c, lt)] = lg.xix * dxi + lg.etx * deta;
-                    s_g[GI(el, 2 * c + 1, lt)] = lg.xiy * dxi + lg.ety * deta;
-                }
-            }
-            __syncthreads();
-            // ---- stage 3: common flux on dual numbers (values from the face pack)
-            double fsc[4];
-            if (act && lt < NF) {
-                const double* lam = s_lam[f & 1];
-                const unsigned FE = (unsigned)E * NF;
-                const unsigned sid = (unsigned)e * NF + lt;
-                const double nx = lg.nx, ny = lg.ny, sc = lg.sc;
-                // the viscous part first: it ends in three numbers, so little of it is live in the
-                // inviscid flux, whose dual numbers are the kernel's register peak
-                double ft[4] = {0.0, 0.0, 0.0, 0.0};
-                double qmv[4], qpv[4], qmt[4];
+                const double* lamn = s_lam[lg.nf & 1];
+                const double* dlamn = s_dlam[lg.nf & 1];
 #pragma unroll
                 for (int vv = 0; vv < 4; ++vv) {
+                    double acc = 0.0;
+#pragma unroll
+                    for (int b = 0; b < n; ++b) acc = acc + lamn[b] * ln[vv][b];
+                    qpt[vv] = acc;
+                }
+                if (VISC) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        double acc = 0.0;
+#pragma unroll
+                        for (int b = 0; b < n; ++b) acc = acc + dlamn[b] * ln[c + 1][b];
+                        dnort[c] = acc;
+                        s_F[FI(el, c, f * n + lg.k2)] = qpt[c + 1];
+                    }
+                }
+            }
+            if (lt < Np) {
+#pragma unroll
+                for (int vv = 0; vv < 4; ++vv)
+                    if (!ZO) s_q[QI(el, vv, lt)] = qo[vv];
+            }
+        }
+        __syncthreads();
+        // ---- stage 2: uncorrected gradient tangent
+        if (VISC && !ZO && act && lt < Np) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                double dxi = 0.0, deta = 0.0;
+#pragma unroll
+                for (int b = 0; b < n; ++b) {
+                    dxi = dxi + s_D[i * n + b] * s_q[QI(el, c + 1, b + n * j)];
+                    deta = deta + s_D[j * n + b] * s_q[QI(el, c + 1, i + n * b)];
+                }
+                s_g[GI(el, 2 * c, lt)] = lg.xix * dxi + lg.etx * deta;
+                s_g[GI(el, 2 * c + 1, lt)] = lg.xiy * dxi + lg.ety * deta;
+            }
+        }
+        __syncthreads();
+        // ---- stage 3: common flux on dual numbers (values from the face pack)
+        double fsc[4];
+        if (act && lt < NF) {
+            const double* lam = s_lam[f & 1];
+            const unsigned FE = (unsigned)E * NF;
+            const unsigned sid = (unsigned)e * NF + lt;
+            const double nx = lg.nx, ny = lg.ny, sc = lg.sc;
+            // the viscous part first: it ends in three numbers, so little of it is live in the
+            // inviscid flux, whose dual numbers are the kernel's register peak
+            double ft[4] = {0.0, 0.0, 0.0, 0.0};
+            double qmv[4], qpv[4], qmt[4];
+#pragma unroll
+            for (int vv = 0; vv < 4; ++vv) {
+                double acc = 0.0;
+#pragma unroll
+                for (int b = 0; b < n; ++b)
+                    if (!ZO) acc = acc + lam[b] * s_q[QI(el, vv, line_pt(n, f, k, b))];
+                qmt[vv] = acc;
+                qmv[vv] = ldo(fpk + (size_t)vv * FE, sid);
+                qpv[vv] = ldo(fpk + (size_t)(4 + vv) * FE, sid);
+            }
+            if (VISC) {
+                double gs[6], dqt[4], dqh[3];   // gs: sum of the two sides' gradient-trace tangents
+#pragma unroll
+                for (int c = 0; c < 6; ++c) {
                     double acc = 0.0;
 #pragma unroll
                     for (int b = 0; b < n; ++b)
-                        if (!ZO) acc = acc + lam[b] * s_q[QI(el, vv, line_pt(n, f, k, b))];
-                    qmt[vv] = acc;
-                    qmv[vv] = BLK ? fpv[vv] : ldo(fpk + (size_t)vv * FE, sid);
-                    qpv[vv] = BLK ? fpv[4 + vv] : ldo(fpk + (size_t)(4 + vv) * FE, sid);
+                        if (!ZO) acc = acc + lam[b] * s_g[GI(el, c, line_pt(n, f, k, b))];
+                    gs[c] = acc;
                 }
-                if (VISC) {
-                    double gs[6], dqt[4], dqh[3];   // gs: sum of the two sides' gradient-trace tangents
 #pragma unroll
-                    for (int c = 0; c < 6; ++c) {
-                        double acc = 0.0;
+                for (int c = 0; c < 3; ++c) {
+                    double dtan = 0.0;
 #pragma unroll
-                        for (int b = 0; b < n; ++b)
-                            if (!ZO) acc = acc + lam[b] * s_g[GI(el, c, line_pt(n, f, k, b))];
-                        gs[c] = acc;
-                    }
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        double dtan = 0.0;
-#pragma unroll
-                        for (int m = 0; m < n; ++m) dtan = dtan + s_D[lg.k2 * n + m] * s_F[FI(el, c, f * n + m)];
-                        const double dxi = lg.nf < 2 ? dnort[c] : dtan, deta = lg.nf < 2 ? dtan : dnort[c];
-                        gs[2 * c] = gs[2 * c] + (lg.mxix * dxi + lg.metx * deta);
-                        gs[2 * c + 1] = gs[2 * c + 1] + (lg.mxiy * dxi + lg.mety * deta);
-                    }
-#pragma unroll
-                    for (int vv = 0; vv < 4; ++vv) dqt[vv] = qpt[vv] - qmt[vv];
-                    const double tnx = BLK ? fpv[8] : ldo(fpk + (size_t)8 * FE, sid);
-                    const double tny = BLK ? fpv[9] : ldo(fpk + (size_t)9 * FE, sid);
-                    // q^com velocity: the average of the traces
-                    fr_common_viscous_tan(pc, dqt, 0.5 * (qmv[1] + qpv[1]), 0.5 * (qmv[2] + qpv[2]),
-                                          0.5 * (qmt[1] + qpt[1]), 0.5 * (qmt[2] + qpt[2]), tnx, tny, gs, nx, ny,
-                                          lg.cc, ft, dqh);
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) s_dq[DI(el, c, lt)] = dqh[c];
+                    for (int m = 0; m < n; ++m) dtan = dtan + s_D[lg.k2 * n + m] * s_F[FI(el, c, f * n + m)];
+                    const double dxi = lg.nf < 2 ? dnort[c] : dtan, deta = lg.nf < 2 ? dtan : dnort[c];
+                    gs[2 * c] = gs[2 * c] + (lg.mxix * dxi + lg.metx * deta);
+                    gs[2 * c + 1] = gs[2 * c + 1] + (lg.mxiy * dxi + lg.mety * deta);
                 }
-                D fn[4], dq[4], qm[4], qp[4];
 #pragma unroll
-                for (int vv = 0; vv < 4; ++vv) { qm[vv] = mk(qmv[vv], qmt[vv]); qp[vv] = mk(qpv[vv], qpt[vv]); }
-                fr_common_inviscid<D>(pc, qm, qp, nx, ny, 0.0, 0.0, fn, dq);
+                for (int vv = 0; vv < 4; ++vv) dqt[vv] = qpt[vv] - qmt[vv];
+                const double tnx = ldo(fpk + (size_t)8 * FE, sid);
+                const double tny = ldo(fpk + (size_t)9 * FE, sid);
+                // q^com velocity: the average of the traces
+                fr_common_viscous_tan(pc, dqt, 0.5 * (qmv[1] + qpv[1]), 0.5 * (qmv[2] + qpv[2]),
+                                      0.5 * (qmt[1] + qpt[1]), 0.5 * (qmt[2] + qpt[2]), tnx, tny, gs, nx, ny,
+                                      lg.cc, ft, dqh);
 #pragma unroll
-                for (int vv = 0; vv < 4; ++vv) fsc[vv] = sc * (fn[vv].d[0] + ft[vv]);
+                for (int c = 0; c < 3; ++c) s_dq[DI(el, c, lt)] = dqh[c];
             }
-            __syncthreads();
-            // ---- stage 4: corrected gradient tangent, point flux on dual numbers, contravariant tangents
-            double qv[4];
-            if (act && lt < Np) {
-                const unsigned id = (unsigned)e * Np + lt;
-                D qs[4];
+            D fn[4], dq[4], qm[4], qp[4];
 #pragma unroll
-                for (int vv = 0; vv < 4; ++vv) {
-                    qv[vv] = BLK ? spv[vv] : ldo(spk + (size_t)vv * EN, id);
-                    qs[vv] = mk(qv[vv], ZO ? 0.0 : s_q[QI(el, vv, lt)]);
-                }
-                D fl[4], gl[4], qc[4];
-                fr_point_flux<D, false>(pc, qs, nullptr, nullptr, nullptr, fl, gl, qc);
-                double ft[4], gf[4];
+            for (int vv = 0; vv < 4; ++vv) { qm[vv] = mk(qmv[vv], qmt[vv]); qp[vv] = mk(qpv[vv], qpt[vv]); }
+            fr_common_inviscid<D>(pc, qm, qp, nx, ny, 0.0, 0.0, fn, dq);
 #pragma unroll
-                for (int vv = 0; vv < 4; ++vv) { ft[vv] = fl[vv].d[0]; gf[vv] = gl[vv].d[0]; }
-                if (VISC) {
-                    double gt[6], tau[3];
+            for (int vv = 0; vv < 4; ++vv) fsc[vv] = sc * (fn[vv].d[0] + ft[vv]);
+        }
+        __syncthreads();
+        // ---- stage 4: corrected gradient tangent, point flux on dual numbers, contravariant tangents
+        double qv[4];
+        if (act && lt < Np) {
+            const unsigned id = (unsigned)e * Np + lt;
+            D qs[4];
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) tau[c] = BLK ? spv[4 + c] : ldo(spk + (size_t)(4 + c) * EN, id);
-#pragma unroll
-                    for (int c = 0; c < 6; ++c) gt[c] = ZO ? 0.0 : s_g[GI(el, c, lt)];
-                    const int fp0 = 0 * n + j, fp1 = 1 * n + j, fp2 = 2 * n + i, fp3 = 3 * n + i;
-                    const double gL_i = s_gam[0][i], gR_i = s_gam[1][i], gL_j = s_gam[0][j], gR_j = s_gam[1][j];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        const double lx = gL_i * s_dq[DI(el, c, fp0)] + gR_i * s_dq[DI(el, c, fp1)];
-                        const double le = gL_j * s_dq[DI(el, c, fp2)] + gR_j * s_dq[DI(el, c, fp3)];
-                        gt[2 * c] = gt[2 * c] + (lg.xix * lx + lg.etx * le);
-                        gt[2 * c + 1] = gt[2 * c + 1] + (lg.xiy * lx + lg.ety * le);
-                    }
-                    fr_point_viscous_tan(pc, qv[1], qv[2], qs[1].d[0], qs[2].d[0], tau, gt, ft, gf);
-                }
-#pragma unroll
-                for (int vv = 0; vv < 4; ++vv) {
-                    s_w[WI(el, vv, lt)] = lg.xix * ft[vv] + lg.xiy * gf[vv];
-                    s_w[WI(el, 4 + vv, lt)] = lg.etx * ft[vv] + lg.ety * gf[vv];
-                }
+            for (int vv = 0; vv < 4; ++vv) {
+                qv[vv] = ldo(spk + (size_t)vv * EN, id);
+                qs[vv] = mk(qv[vv], ZO ? 0.0 : s_q[QI(el, vv, lt)]);
             }
-            __syncthreads();
-            // ---- stage 5: F^num' - F^loc'
-            if (act && lt < NF) {
-                const double* lam = s_lam[f & 1];
-                const double jac = frcp(lg.ij);
-                const int base = f < 2 ? 0 : 4;
+            D fl[4], gl[4], qc[4];
+            fr_point_flux<D, false>(pc, qs, nullptr, nullptr, nullptr, fl, gl, qc);
+            double ft[4], gf[4];
 #pragma unroll
-                for (int vv = 0; vv < 4; ++vv) {
-                    double acc = 0.0;
+            for (int vv = 0; vv < 4; ++vv) { ft[vv] = fl[vv].d[0]; gf[vv] = gl[vv].d[0]; }
+            if (VISC) {
+                double gt[6], tau[3];
 #pragma unroll
-                    for (int b = 0; b < n; ++b) acc = acc + lam[b] * s_w[WI(el, base + vv, line_pt(n, f, k, b))];
-                    s_F[FI(el, vv, lt)] = fsc[vv] - jac * acc;
+                for (int c = 0; c < 3; ++c) tau[c] = ldo(spk + (size_t)(4 + c) * EN, id);
+#pragma unroll
+                for (int c = 0; c < 6; ++c) gt[c] = ZO ? 0.0 : s_g[GI(el, c, lt)];
+                const int fp0 = 0 * n + j, fp1 = 1 * n + j, fp2 = 2 * n + i, fp3 = 3 * n + i;
+                const double gL_i = s_gam[0][i], gR_i = s_gam[1][i], gL_j = s_gam[0][j], gR_j = s_gam[1][j];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const double lx = gL_i * s_dq[DI(el, c, fp0)] + gR_i * s_dq[DI(el, c, fp1)];
+                    const double le = gL_j * s_dq[DI(el, c, fp2)] + gR_j * s_dq[DI(el, c, fp3)];
+                    gt[2 * c] = gt[2 * c] + (lg.xix * lx + lg.etx * le);
+                    gt[2 * c + 1] = gt[2 * c + 1] + (lg.xiy * lx + lg.ety * le);
                 }
+                fr_point_viscous_tan(pc, qv[1], qv[2], qs[1].d[0], qs[2].d[0], tau, gt, ft, gf);
             }
-            __syncthreads();
-            // ---- stage 6: divergence and lift of the tangents; time terms
-            if (act && lt < Np) {
-                const unsigned id = (unsigned)e * Np + lt;
-                double ct = a.c_time, idt = a.inv_dtau;
-                if (a.cstep) { ct = rfl(a.cstep[cid].ct); idt = rfl(a.cstep[cid].idt); }
-                double tt[4], x[4];
 #pragma unroll
-                for (int vv = 0; vv < 4; ++vv) x[vv] = ZO ? 0.0 : s_q[QI(el, vv, lt)];
-                if constexpr (ZO) {
+            for (int vv = 0; vv < 4; ++vv) {
+                s_w[WI(el, vv, lt)] = lg.xix * ft[vv] + lg.xiy * gf[vv];
+                s_w[WI(el, 4 + vv, lt)] = lg.etx * ft[vv] + lg.ety * gf[vv];
+            }
+        }
+        __syncthreads();
+        // ---- stage 5: F^num' - F^loc'
+        if (act && lt < NF) {
+            const double* lam = s_lam[f & 1];
+            const double jac = frcp(lg.ij);
+            const int base = f < 2 ? 0 : 4;
 #pragma unroll
-                    for (int vv = 0; vv < 4; ++vv) tt[vv] = 0.0;
-                } else {
-                    fr_time_apply<double, double>(pc, qv, 0.0, 0.0, idt, ct, x, tt);
-                }
-                double* out = a.out + (BLK ? cd.boff + (size_t)e * (4 * Np) * (4 * Np) : cd.off);
+            for (int vv = 0; vv < 4; ++vv) {
+                double acc = 0.0;
+#pragma unroll
+                for (int b = 0; b < n; ++b) acc = acc + lam[b] * s_w[WI(el, base + vv, line_pt(n, f, k, b))];
+                s_F[FI(el, vv, lt)] = fsc[vv] - jac * acc;
+            }
+        }
+        __syncthreads();
+        // ---- stage 6: divergence and lift of the tangents; time terms
+        if (act && lt < Np) {
+            const unsigned id = (unsigned)e * Np + lt;
+            double ct = a.c_time, idt = a.inv_dtau;
+            if (a.cstep) { ct = rfl(a.cstep[cid].ct); idt = rfl(a.cstep[cid].idt); }
+            double tt[4], x[4];
+#pragma unroll
+            for (int vv = 0; vv < 4; ++vv) x[vv] = ZO ? 0.0 : s_q[QI(el, vv, lt)];
+            if constexpr (ZO) {
+#pragma unroll
+                for (int vv = 0; vv < 4; ++vv) tt[vv] = 0.0;
+            } else {
+                fr_time_apply<double, double>(pc, qv, 0.0, 0.0, idt, ct, x, tt);
+            }
+            double* out = a.out + cd.off;
 #pragma unroll 1
-                for (int vv = 0; vv < 4; ++vv) {
-                    double dF = 0.0, dG = 0.0;
+            for (int vv = 0; vv < 4; ++vv) {
+                double dF = 0.0, dG = 0.0;
 #pragma unroll
-                    for (int b = 0; b < n; ++b) {
-                        dF = dF + s_D[i * n + b] * s_w[WI(el, vv, b + n * j)];
-                        dG = dG + s_D[j * n + b] * s_w[WI(el, 4 + vv, i + n * b)];
-                    }
-                    const double cor = s_gam[0][i] * s_F[FI(el, vv, 0 * n + j)] + s_gam[1][i] * s_F[FI(el, vv, 1 * n + j)]
-                                     + s_gam[0][j] * s_F[FI(el, vv, 2 * n + i)] + s_gam[1][j] * s_F[FI(el, vv, 3 * n + i)];
-                    const double Rd = -(dF + dG + lg.ij * cor);
-                    const double ttv = (vv == 0) ? tt[0] : (vv == 1) ? tt[1] : (vv == 2) ? tt[2] : tt[3];
-                    if (BLK) {
-                        out[(size_t)col * (4 * Np) + vv * Np + lt] = ttv - Rd;
-                    } else {
-                        out[vv * EN + id] = ttv - Rd;
-                    }
+                for (int b = 0; b < n; ++b) {
+                    dF = dF + s_D[i * n + b] * s_w[WI(el, vv, b + n * j)];
+                    dG = dG + s_D[j * n + b] * s_w[WI(el, 4 + vv, i + n * b)];
                 }
+                const double cor = s_gam[0][i] * s_F[FI(el, vv, 0 * n + j)] + s_gam[1][i] * s_F[FI(el, vv, 1 * n + j)]
+                                 + s_gam[0][j] * s_F[FI(el, vv, 2 * n + i)] + s_gam[1][j] * s_F[FI(el, vv, 3 * n + i)];
+                const double Rd = -(dF + dG + lg.ij * cor);
+                const double ttv = (vv == 0) ? tt[0] : (vv == 1) ? tt[1] : (vv == 2) ? tt[2] : tt[3];
+                out[vv * EN + id] = ttv - Rd;
             }
-        }   // columns
+        }
     }
 }
 
@@ -1683,14 +1602,14 @@ fr_status run(const Solver& sv, const Group& gr, const KArgs& a, int grid, int x
         bool aff = false;
         // a Gauss-Seidel coupling pass: the variants that take v on lower or higher colours only
         const bool cs = !B && a.csweep > 0;
-        if constexpr (!MOV) {
+        if constexpr (!MOV && !B) {
             aff = group_affine(sv, gr);
             if (aff) {
                 if (cs)
-                    hipLaunchKernelGGL((k_lin_aff<P, VISC, LANES, B, !B>), dim3(grid_of(ga.ntiles, grid)),
+                    hipLaunchKernelGGL((k_lin_aff<P, VISC, LANES, true>), dim3(grid_of(ga.ntiles, grid)),
                                        dim3(SH::threads), 0, s, ga, a, op);
                 else
-                    hipLaunchKernelGGL((k_lin_aff<P, VISC, LANES, B>), dim3(grid_of(ga.ntiles, grid)),
+                    hipLaunchKernelGGL((k_lin_aff<P, VISC, LANES>), dim3(grid_of(ga.ntiles, grid)),
                                        dim3(SH::threads), 0, s, ga, a, op);
             }
         }
@@ -1768,7 +1687,7 @@ fr_status run(const Solver& sv, const Group& gr, const KArgs& a, int grid, int x
 // workgroup widths built per mode: plain doubles 64/128/256 lanes, dual numbers 64/128
 template <int P, bool VISC, bool MOV, int MODE>
 fr_status run_lanes(const Solver& sv, const Group& gr, const KArgs& a, const Tune& t, hipStream_t s) {
-    constexpr bool dual = MODE == MODE_JVP || MODE == MODE_AOP || MODE == MODE_BLK;
+    constexpr bool dual = MODE == MODE_JVP || MODE == MODE_AOP;
     int lanes = t.lanes > 0 ? t.lanes : (dual ? 64 : 128);
     if (gr.bnd && lanes > 128) lanes = 128;   // the boundary-face variants are built for 64 and 128 lanes
     switch (lanes) {
@@ -1788,7 +1707,6 @@ fr_status run_mode(const Solver& sv, const Group& gr, int mode, const KArgs& a, 
         case MODE_R: return run_lanes<P, VISC, MOV, MODE_R>(sv, gr, a, t, s);
         case MODE_JVP: return run_lanes<P, VISC, MOV, MODE_JVP>(sv, gr, a, t, s);
         case MODE_AOP: return run_lanes<P, VISC, MOV, MODE_AOP>(sv, gr, a, t, s);
-        case MODE_BLK: return run_lanes<P, VISC, MOV, MODE_BLK>(sv, gr, a, t, s);
         case MODE_PREP: return run_lanes<P, VISC, MOV, MODE_PREP>(sv, gr, a, t, s);
         case MODE_LIN: return run_lanes<P, VISC, MOV, MODE_LIN>(sv, gr, a, t, s);
         case MODE_LINBLK: return run_lanes<P, VISC, MOV, MODE_LINBLK>(sv, gr, a, t, s);

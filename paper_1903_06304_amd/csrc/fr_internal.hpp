@@ -63,10 +63,10 @@ struct Geo {
 // boundary kinds of the per-element face codes (the ABI codes are -1, -2, -3)
 enum { BC_NONE = 0, BC_FARFIELD = 1, BC_SLIP = 2, BC_WALL = 3 };
 
-// R; exact JVP; Newton operator; one seeded block column; R plus the linearisation packs;
-// Newton operator from the packs (tangent-only staging)
-enum FrMode { MODE_R = 0, MODE_JVP = 1, MODE_AOP = 2, MODE_BLK = 3, MODE_PREP = 4, MODE_LIN = 5, MODE_LINBLK = 6,
-              NMODES = 7 };   // MODE_LINBLK: block columns from the packs
+// R; exact JVP; Newton operator; R plus the linearisation packs; Newton operator from the packs
+// (tangent-only staging); one seeded block column from the packs.  The values are part of the
+// autotuner's cache keys.
+enum FrMode { MODE_R = 0, MODE_JVP = 1, MODE_AOP = 2, MODE_PREP = 4, MODE_LIN = 5, MODE_LINBLK = 6, NMODES = 7 };
 
 // Linearisation packs of a state (written by MODE_PREP, read by MODE_LIN): the values the
 // Newton operator's nonlinear point functions need, so that its staged data are tangents.
@@ -131,13 +131,11 @@ enum { GI_DONE = 0,   // Arnoldi of the current cycle stopped (skip flag of the 
 struct KArgs {
     const double* q;      // state
     const double* v;      // tangent direction (JVP / AOP)
-    double* out;          // R, Jv, Av, or the block assembly buffer (block mode)
+    double* out;          // R, Jv, Av, or the block assembly buffer
     double* out2;         // R (JVP) or NULL
     double c_time, inv_dtau;   // time-term coefficients when cstep is NULL
     const CaseStep* cstep;     // per-case coefficients (solver steps) or NULL
-    int seed0;            // first seeded column (block mode)
-    int ncols;            // block columns from the packs (MODE_LINBLK) on affine static groups: the
-                          // columns seed0 .. seed0 + ncols - 1 in one launch (0: one column)
+    int seed0;            // seeded column (MODE_LINBLK)
     const int* flags;     // per-case flags (gi layout) or NULL
     int flag;             // which flag skips a case
     double* fpack;        // linearisation packs (MODE_PREP writes, MODE_LIN reads)
@@ -227,6 +225,7 @@ struct fr_ctx_s {
     double* d_qinf = nullptr;       // [4] far-field state
     bool has_farfield = false, farfield_set = false;
     int ncolors = 0;
+    bool self_neighbour = false;    // some element is its own face neighbour (one-element-wide periodic meshes)
     bool all_affine = false;        // every element affine at the current geometry
     double* d_trace = nullptr;      // neighbour traces (adjoint path)
     double* d_vj = nullptr;         // adjoint trace buffer
@@ -387,6 +386,9 @@ size_t prec_bytes(int prec);
 
 // preconditioner (fr_linalg.hip)
 fr_status launch_block_assembly(Solver& sv, const double* q, const KArgs& base, hipStream_t s);
+// the blocks of one group entry by entry from the packs (fr_assembly.hip), and whether it can
+bool direct_assembly(const Solver& sv, const Group& gr);
+fr_status launch_direct_assembly(const Solver& sv, const Group& gr, const KArgs& a, hipStream_t s);
 fr_status launch_block_invert(Solver& sv, int prec, const int* flags, hipStream_t s);
 // explicit inverses of one group's element blocks, Gauss-Jordan on the matrix cores (fr_invert.hip)
 fr_status launch_block_invert_group(Solver& sv, int p, const GroupArgs& ga, int prec, const int* flags,

@@ -1,11 +1,10 @@
 // Element-block-Jacobi preconditioner and Krylov building blocks for gfx950.
 //
-//  - block assembly: seeded forward tangents of the residual kernel (one column per
-//    launch lane) give the true diagonal block dR_e/dq_e; the time terms
-//    inv_dtau Gamma + c_time M are added pointwise (paper Eq. unsteady_pre_discretized_3)
-//  - block inversion: Gauss-Jordan with partial pivoting in FP64, one workgroup per
-//    element, the block resident in LDS; the explicit inverse is stored in FP64, FP32
-//    or BF16 (round to nearest even), column-major so the apply reads it coalesced
+//  - block assembly: the true diagonal block inv_dtau Gamma + c_time M - dR_e/dq_e (paper Eq.
+//    unsteady_pre_discretized_3) from the linearisation packs, entry by entry (fr_assembly.hip), or
+//    column by column with seeded tangents where a seed reaches beyond its element's faces
+//  - block inversion (fr_invert.hip): the explicit inverse is stored in FP64, FP32 or BF16
+//    (round to nearest even), column-major so the apply reads it coalesced
 //  - block apply z_e = P_e^-1 r_e: memory-bound GEMV, FP64 accumulation
 //  - Krylov reductions: two-stage, fixed-order (deterministic) dot products
 #include "fr_internal.hpp"
@@ -606,28 +605,20 @@ GroupArgs group_args(const Solver& sv, const Group& gr, int epb, int color = -1)
 // ----------------------------------------------------------------------------- launchers
 fr_status launch_block_assembly(Solver& sv, const double* q, const KArgs& base, hipStream_t s) {
     PhaseRange range("lmfr: block assembly (enqueue)");
-    // one seeded column of every element's block per launch and group (every column at once
-    // on affine static groups, below); with the linearisation packs of q in base
-    // (fpack/spack), tangents only
+    if (!base.fpack || !base.spack) { fr_set_error("block assembly without packs"); return FR_EINVAL; }
     KArgs a = base;
     a.q = q; a.v = nullptr; a.out = sv.d_blk; a.out2 = nullptr;
-    const int mode = (a.fpack && a.spack) ? MODE_LINBLK : MODE_BLK;
     for (const Group& gr : sv.groups) {
-        const int nb = 4 * (gr.p + 1) * (gr.p + 1);
-        // the affine kernel over the packs (static groups whose elements are all affine)
-        // assembles every column in one launch, reading the packs of an element once
-        bool all_aff = !gr.mov;
-        for (int id : gr.ids) all_aff = all_aff && sv.cs[id]->all_affine;
-        if (mode == MODE_LINBLK && all_aff) {
-            a.seed0 = 0;
-            a.ncols = nb;
-            FR_TRY(launch_fused(sv, gr, mode, a, gr.tune[mode], s));
-            a.ncols = 0;
+        if (direct_assembly(sv, gr)) {
+            FR_TRY(launch_direct_assembly(sv, gr, a, s));
             continue;
         }
+        // meshes with boundary faces or self-neighbours: one seeded column of every element's block
+        // per launch
+        const int nb = 4 * (gr.p + 1) * (gr.p + 1);
         for (int col = 0; col < nb; ++col) {
             a.seed0 = col;
-            FR_TRY(launch_fused(sv, gr, mode, a, gr.tune[mode], s));
+            FR_TRY(launch_fused(sv, gr, MODE_LINBLK, a, gr.tune[MODE_LINBLK], s));
         }
     }
     return FR_OK;
