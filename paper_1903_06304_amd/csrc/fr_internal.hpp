@@ -390,7 +390,7 @@ fr_status launch_block_assembly(Solver& sv, const double* q, const KArgs& base, 
 bool direct_assembly(const Solver& sv, const Group& gr);
 fr_status launch_direct_assembly(const Solver& sv, const Group& gr, const KArgs& a, hipStream_t s);
 fr_status launch_block_invert(Solver& sv, int prec, const int* flags, hipStream_t s);
-// explicit inverses of one group's element blocks, Gauss-Jordan on the matrix cores (fr_invert.hip)
+// explicit inverses of one group's element blocks, Gauss-Jordan in registers (fr_invert.hip)
 fr_status launch_block_invert_group(Solver& sv, int p, const GroupArgs& ga, int prec, const int* flags,
                                     hipStream_t s);
 fr_status launch_block_apply(const Solver& sv, const double* r, double* z, const int* flags, int flag, hipStream_t s);

@@ -1,53 +1,39 @@
 // Explicit inverse of every element block (the element-block-Jacobi preconditioner of the
-// paper's Sec. 4 set-up): Gauss-Jordan elimination with partial pivoting, blocked by
-// panels of 16 columns, with the trailing update of each panel on the matrix cores.
+// paper's Sec. 4 set-up): in-place Gauss-Jordan elimination with partial pivoting, the whole
+// block in registers.
 //
-// One workgroup (4 waves) per element; the block, padded to NBP = 16 ceil(nb / 16) rows
-// and columns with an identity on the padding, sits in LDS column-major.  Per panel of
-// columns kb .. kb + 15:
-//   1. wave 0 runs the 16 Gauss-Jordan steps on the panel columns only, over every row
-//      (lane l holds rows l and l + 64, where they exist, in registers).  Step j takes as pivot the unused
-//      row with the largest |a(r, kb + j)| (lowest row on ties) and applies the in-place
-//      inverse update: rows stay where they are, column kb + j becomes the transformed
-//      unit vector of the pivot row.  The panel then holds W = M [e_p(0) .. e_p(15)], M
-//      the product of the 16 elementary transforms;
-//   2. every other column c becomes M c = W c(pivot rows) + (c with the panel's pivot rows
-//      zeroed): a rank-16 product W (NBP x 16) times the pivot rows (16 x NBP - 16) added
-//      to the rest, formed as 16 x 16 output tiles of v_mfma_*_16x16x4 (4 k-steps each).
-//      Wave w owns the column tiles J = w mod 4 and reads its pivot-row operands into
-//      registers before it writes any tile of its columns, so no copy is needed.
-// After the last panel the block holds the inverse with rows and columns permuted by
-// the pivot order: inverse(pos(r), piv(k)) = a(r, k), pos the step at which row r was
-// the pivot.  Padding columns pick their own padding row with pivot 1 and change nothing.
+// A group of TR x CT threads holds an element, RPT x CPT entries each (Map): one wave up to
+// 64 x 64, four for 100 x 100.  Thread (tr, tc) holds the rows 2 tr + 2 TR i, + 1 (pairs, so that
+// loads and LDS reads are 16 bytes wide and consecutive) and the columns tc + CT b.  Step k, with
+// the column of step k at register column 0:
+//   1. its owners put the column into LDS; every wave reads it, one or two rows a lane, and takes
+//      the unused row with the largest |a(r, k)| as pivot row p: one DPP maximum over integer keys,
+//      the leading bits of |a| above 127 - row (two entries that agree to 2^-13 count as a tie,
+//      which goes to the lower row);
+//   2. the owners of row p put it into LDS, and everyone applies a(r, c) -= a(r, k) / a(p, k) a(p, c).
+// Row p and column k of the in-place inverse come out of the same update: the row is zeroed in
+// its owners and its multiplier is 1 / a(p, k), the column is zeroed and its entry of the row is 1.
+// Register columns move down by one once the CT columns of register 0 have been pivots: the last
+// of these steps writes each result one register lower, so the loop is one small body with
+// constant register numbers.  Rows stay where they are; at the end the block holds the inverse
+// with rows and columns permuted by the pivot order, inverse(pos(r), piv(k)) = a(r, k), pos the
+// step at which row r was the pivot, and goes out through LDS, CT whole columns at a time.
 //
-// Arithmetic type TC: FP64 (MFMA f64 16x16x4) for an FP64 inverse; FP32 (MFMA f32
-// 16x16x4, FP32 accumulation) for an FP32 or BF16 inverse, the FP64 block rounded to
-// FP32 on load and the FP32 result rounded to nearest even for BF16.
+// Arithmetic type TC: FP64 for an FP64 inverse; FP32 for an FP32 or BF16 inverse, the FP64 block
+// rounded to FP32 on load and the FP32 result rounded to nearest even for BF16.
+//
+// What bounds it: instruction issue.  FP64 matrix instructions share the vector pipe and reach
+// 1.27 times its rate, while a panel form needs the block in LDS (80 KB at p = 4: two workgroups a
+// compute unit) and leaves three waves of four idle through its panels.  65,536 blocks, against
+// panels of 16 columns in LDS with the trailing update on the matrix cores, ms:
+//     nb            16           36           64           100
+//     FP64     0.12 (0.45)  0.59 (1.93)  2.28 (3.41)  7.94 (20.1)
+//     FP32     0.09 (0.27)  0.40 (1.12)  1.12 (1.63)  4.73 (8.34)
+// 256 FP64 blocks of 64, one wave a compute unit: 53 us (44), the latency of the 64 steps.
 #include "fr_internal.hpp"
+#include <type_traits>
 
 namespace {
-
-typedef double mf_d4 __attribute__((ext_vector_type(4)));
-typedef float mf_f4 __attribute__((ext_vector_type(4)));
-
-// 16x16x4 products D = A B + C on one wave: lane l supplies A(l % 16, l / 16) and
-// B(l / 16, l % 16); its r-th accumulator element is D(row(l, r), l % 16).  The output row
-// order differs between the FP64 and FP32 instructions (checked on the device).
-template <class TC> struct Mfma;
-template <> struct Mfma<double> {
-    using V = mf_d4;
-    __device__ __forceinline__ static V step(double a, double b, V c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    __device__ __forceinline__ static int row(int lane, int r) { return (lane >> 4) + 4 * r; }
-};
-template <> struct Mfma<float> {
-    using V = mf_f4;
-    __device__ __forceinline__ static V step(float a, float b, V c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    __device__ __forceinline__ static int row(int lane, int r) { return 4 * (lane >> 4) + r; }
-};
 
 template <class TO, class TC> __device__ __forceinline__ TO store_as(TC x);
 template <> __device__ __forceinline__ double store_as<double, double>(double x) { return x; }
@@ -58,17 +44,7 @@ template <> __device__ __forceinline__ uint16_t store_as<uint16_t, float>(float 
     return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);           // round to nearest even
 }
 
-// Cross-lane moves of a double, no LDS: a DPP move within rows of 16 lanes, and a read
-// of one lane into scalar registers.
-template <int CTRL> __device__ __forceinline__ double dpp_mov(double x) {
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-template <int CTRL> __device__ __forceinline__ float dpp_mov(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
-}
+// one lane's value, read into scalar registers
 __device__ __forceinline__ double lane_value(double x, int lane) {
     const long long b = __double_as_longlong(x);
     const int lo = __builtin_amdgcn_readlane((int)b, lane);
@@ -78,14 +54,19 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
 __device__ __forceinline__ float lane_value(float x, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
-// maximum over the wave: DPP within each row of 16 lanes (quad swaps, then rotations by 4
-// and 8), then the four row maxima read into scalar registers
-template <class T> __device__ __forceinline__ T wave_max(T m) {
-    m = fmax(m, dpp_mov<0xB1>(m));    // quad_perm [1, 0, 3, 2]
-    m = fmax(m, dpp_mov<0x4E>(m));    // quad_perm [2, 3, 0, 1]
-    m = fmax(m, dpp_mov<0x124>(m));   // row_ror 4
-    m = fmax(m, dpp_mov<0x128>(m));   // row_ror 8
-    return fmax(fmax(lane_value(m, 0), lane_value(m, 16)), fmax(lane_value(m, 32), lane_value(m, 48)));
+// maximum over the wave by DPP: within rows of 16 lanes, then across the rows; lane 63 holds it
+template <int CTRL> __device__ __forceinline__ unsigned umax_dpp(unsigned x) {
+    const unsigned y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+    return x > y ? x : y;
+}
+__device__ __forceinline__ unsigned wave_umax(unsigned x) {
+    x = umax_dpp<0x111>(x);   // row_shr 1, 2, 4, 8
+    x = umax_dpp<0x112>(x);
+    x = umax_dpp<0x114>(x);
+    x = umax_dpp<0x118>(x);
+    x = umax_dpp<0x142>(x);   // row_bcast 15, 31
+    x = umax_dpp<0x143>(x);
+    return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
 }
 
 __device__ __forceinline__ int case_of_tile(const GroupArgs& ga, int t) {
@@ -97,21 +78,48 @@ __device__ __forceinline__ int case_of_tile(const GroupArgs& ga, int t) {
     return lo;
 }
 
+// threads and entries of one element: TR x CT threads in NW waves, RPT x CPT entries each.  One
+// wave needs no barrier and shares a step's fixed work over most entries; 100 x 100 takes four for
+// its registers (two waves of 4 x 20 entries: 8.3 ms for 7.9 at FP64, 6.2 for 4.7 at FP32).
+template <int NB> struct Map;
+template <> struct Map<16> { static constexpr int TR = 8, CT = 8, NW = 1, OCC = 8; };
+template <> struct Map<36> { static constexpr int TR = 9, CT = 6, NW = 1, OCC = 4; };
+template <> struct Map<64> { static constexpr int TR = 8, CT = 8, NW = 1, OCC = 2; };
+template <> struct Map<100> { static constexpr int TR = 25, CT = 10, NW = 4, OCC = 3; };
+
+// what the LDS traffic of an element needs between its threads: a barrier, or only order within
+// its one wave
+template <int NW> __device__ __forceinline__ void group_sync() {
+    if constexpr (NW > 1) __syncthreads();
+    else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// pivot key of entry x in the given row: 0 for a NaN, else at least 1
+__device__ __forceinline__ unsigned pivot_key(unsigned hi, unsigned inf, int row) {
+    hi &= 0x7fffffffu;
+    return hi > inf ? 0u : (hi & ~127u) | (unsigned)(127 - row);
+}
+__device__ __forceinline__ unsigned pivot_key(double x, int row) {
+    return pivot_key((unsigned)(__double_as_longlong(x) >> 32), 0x7ff00000u, row);
+}
+__device__ __forceinline__ unsigned pivot_key(float x, int row) { return pivot_key(__float_as_uint(x), 0x7f800000u, row); }
+
 template <int NB, class TC, class TO>
-__global__ void __launch_bounds__(256) k_block_invert_mfma(GroupArgs ga, const double* __restrict__ blk,
-                                                           TO* __restrict__ inv, int* __restrict__ gi,
-                                                           const int* __restrict__ flags, int cl) {
-    constexpr int NBP = (NB + 15) / 16 * 16, NT = NBP / 16;
-    // column stride: one element of padding against bank conflicts where LDS allows two
-    // blocks per CU either way (an FP64 100 x 100 block takes LD = NB to fit twice)
-    constexpr int LD = (NB * (NB + 1) * sizeof(TC) <= 80000) ? NB + 1 : NB;
-    static_assert(NB < 255, "pivot bookkeeping in bytes");
-    __shared__ TC A[NB * LD];          // the real block, column c at A + c * LD; the padding is
-                                       // an identity that the elimination never changes
-    __shared__ uint8_t s_piv[NB];      // pivot row of each step
-    __shared__ uint8_t s_pos[NB];      // step at which each row was the pivot, 255 before
-    __shared__ int s_bad;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__global__ void __launch_bounds__(64 * Map<NB>::NW, Map<NB>::OCC)
+k_block_invert(GroupArgs ga, const double* __restrict__ blk, TO* __restrict__ inv, int* __restrict__ gi,
+               const int* __restrict__ flags, int cl) {
+    using M = Map<NB>;
+    constexpr int TR = M::TR, CT = M::CT, NW = M::NW, RPT = NB / TR, CPT = NB / CT, NTH = 64 * NW;
+    static_assert(RPT * TR == NB && CPT * CT == NB && RPT % 2 == 0 && CPT % 2 == 0, "whole pairs");
+    static_assert(NB <= 127 && TR * CT <= NTH, "row numbers in 7 bits");
+    typedef TC V2 __attribute__((ext_vector_type(2)));
+    __shared__ V2 s_col[NB / 2], s_row[NB / 2];
+    __shared__ TC s_out[CT * NB];
+    __shared__ uint8_t s_piv[NB], s_pos[NB];   // pivot row of each step, step of each pivot row
+    const int tid = threadIdx.x, lane = tid & 63;
     const int t = blockIdx.x;
     if (t >= ga.ntiles) return;                                   // uniform per workgroup
     const int lo = case_of_tile(ga, t);
@@ -123,139 +131,136 @@ __global__ void __launch_bounds__(256) k_block_invert_mfma(GroupArgs ga, const d
     const int slot = t - ga.pfx[lo];
     const int e = cl ? cd.g.corder[slot] : slot;
     const double* src = blk + cd.boff + (size_t)e * NB * NB;
-    for (int idx = tid; idx < NB * NB; idx += 256) {
-        const int c = idx / NB, r = idx % NB;
-        A[c * LD + r] = (TC)src[idx];
-    }
-    for (int r = tid; r < NB; r += 256) s_pos[r] = 255;
-    if (tid == 0) s_bad = 0;
-    __syncthreads();
 
-    for (int kb = 0; kb < NB; kb += 16) {
-        const int nk = NB - kb < 16 ? NB - kb : 16;   // real steps of this panel
-        if (wave == 0) {
-            // the panel's Gauss-Jordan steps on one wave: lane l holds rows l and l + 64
-            // (where they exist) of the panel columns in registers; pivot search and pivot
-            // row broadcast through DPP moves and scalar reads, no LDS
-            constexpr bool TWO = NB > 64;
-            const int r0 = lane, r1 = lane + 64;
-            const bool h0 = r0 < NB, h1 = TWO && r1 < NB;
-            TC p0[16], p1[TWO ? 16 : 1];
+    // idle threads (TR CT < NTH) read as thread 0 does and own nothing
+    const bool act = tid < TR * CT;
+    const int tr = act ? tid % TR : 0, tc = act ? tid / TR : 0;
+    const int own_r = act ? tr : -1, own_c = act ? tc : -1;
+    TC A[RPT][CPT];
 #pragma unroll
-            for (int c = 0; c < 16; ++c) p0[c] = (h0 && c < nk) ? A[(kb + c) * LD + r0] : TC(0);
-            if (TWO) {
+    for (int b = 0; b < CPT; ++b)
 #pragma unroll
-                for (int c = 0; c < 16; ++c) p1[TWO ? c : 0] = (h1 && c < nk) ? A[(kb + c) * LD + r1] : TC(0);
-            }
-            bool u0 = h0 ? s_pos[r0] != 255 : true;
-            bool u1 = h1 ? s_pos[r1] != 255 : true;
-            bool bad = false;
+        for (int i = 0; i < RPT / 2; ++i) {
+            const double2 x = *(const double2*)(src + (tc + CT * b) * NB + 2 * tr + 2 * TR * i);
+            A[2 * i][b] = (TC)x.x;
+            A[2 * i + 1][b] = (TC)x.y;
+        }
+    // rows whose entries this lane looks at in a pivot search
+    bool u0 = lane >= NB, u1 = lane + 64 >= NB, bad = false;
+
+    // the owners' register column 0 into LDS, and zero there
+    auto put_column = [&](int jc) {
+        if (own_c == jc) {
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                if (j < nk) {   // uniform
-                    const TC m0 = u0 ? TC(-1) : fabs(p0[j]);
-                    const TC m1 = u1 ? TC(-1) : fabs(p1[TWO ? j : 0]);
-                    const TC m = wave_max(fmax(m0, m1));
-                    const unsigned long long c0 = __ballot(!u0 && m0 == m);
-                    const unsigned long long c1 = __ballot(!u1 && m1 == m);
-                    int prow = __builtin_amdgcn_readfirstlane(
-                        c0 ? (int)__ffsll((long long)c0) - 1 : (c1 ? 64 + (int)__ffsll((long long)c1) - 1 : -1));
-                    // no usable pivot: the block is singular (or not finite); the steps run on
-                    // with row 0 so that the loop stays straight-line code, and the block is
-                    // discarded
-                    const bool ok = prow >= 0 && m > TC(0);
-                    bad = bad || !ok;
-                    prow = ok ? prow : 0;
-                    const bool own0 = h0 && r0 == prow, own1 = h1 && r1 == prow;
-                    TC pr[16];
-                    const int pl = prow & 63;
-                    if (!TWO || prow < 64) {
-#pragma unroll
-                        for (int c = 0; c < 16; ++c) pr[c] = lane_value(p0[c], pl);
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < 16; ++c) pr[c] = lane_value(p1[TWO ? c : 0], pl);
-                    }
-                    const TC ip = TC(1) / pr[j];
-                    const TC f0 = p0[j], f1 = p1[TWO ? j : 0];
-#pragma unroll
-                    for (int c = 0; c < 16; ++c) {
-                        const TC pc = (c == j ? TC(1) : pr[c]) * ip;   // normalised pivot row
-                        p0[c] = own0 ? pc : ((c == j) ? TC(0) : p0[c]) - f0 * pc;
-                        if (TWO) p1[TWO ? c : 0] = own1 ? pc : ((c == j) ? TC(0) : p1[TWO ? c : 0]) - f1 * pc;
-                    }
-                    u0 = u0 || own0;
-                    u1 = u1 || own1;
-                    if (lane == 0) {
-                        s_piv[kb + j] = (uint8_t)prow;
-                        s_pos[prow] = (uint8_t)(kb + j);
-                    }
-                }
-            }
-            if (bad && lane == 0) s_bad = 1;
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                if (c < nk) {
-                    if (h0) A[(kb + c) * LD + r0] = p0[c];
-                    if (h1) A[(kb + c) * LD + r1] = p1[TWO ? c : 0];
-                }
+            for (int i = 0; i < RPT / 2; ++i) {
+                s_col[tr + TR * i] = V2{A[2 * i][0], A[2 * i + 1][0]};
+                A[2 * i][0] = TC(0);
+                A[2 * i + 1][0] = TC(0);
             }
         }
-        __syncthreads();
-        if (s_bad) {
-            if (tid == 0) gi[cid * GI_STRIDE + GI_STATUS] = 3;   // plain vector store
-            return;                                               // uniform per workgroup
+    };
+    // one elimination step, SHIFT: results one register column lower
+    auto step = [&](auto shift, int k, int jc) {
+        constexpr int SH = decltype(shift)::value;
+        put_column(jc);
+        group_sync<NW>();
+        const TC* col = (const TC*)s_col;
+        const TC x0 = col[NB > 64 ? lane : (lane < NB ? lane : 0)];
+        const TC x1 = NB > 64 ? col[lane + 64 < NB ? lane + 64 : 0] : TC(0);
+        V2 f[RPT / 2];
+#pragma unroll
+        for (int i = 0; i < RPT / 2; ++i) f[i] = s_col[tr + TR * i];
+        unsigned key = u0 ? 0u : pivot_key(x0, lane);
+        if (NB > 64) {
+            const unsigned key1 = u1 ? 0u : pivot_key(x1, lane + 64);
+            key = key > key1 ? key : key1;
         }
-        // trailing update: every column tile but the panel's, D = W Y + Z, with the padding
-        // read as zeros (its identity part never meets a real row or column here) and
-        // padding results dropped
-        const int pj = kb / 16;
-        for (int J = wave; J < NT; J += 4) {
-            if (J == pj) continue;
-            const int col = 16 * J + (lane & 15);
-            const bool cin = col < NB;
-            TC b[4];
+        key = wave_umax(key);
+        // no usable pivot: the block is singular (or not finite); the steps run on with row 0 so
+        // that the loop stays straight-line code, and the block is discarded
+        const int p = key ? 127 - (int)(key & 127u) : 0;
+        TC pv = lane_value(x0, p & 63);
+        if (NB > 64) pv = p < 64 ? pv : lane_value(x1, p & 63);
+        bad = bad || !key || !(fabs(pv) > TC(0));
+        u0 = u0 || lane == p;
+        u1 = u1 || lane + 64 == p;
+        const int pq = (p >> 1) % TR, pa = 2 * ((p >> 1) / TR) + (p & 1);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int k = 4 * s + (lane >> 4);
-                b[s] = (cin && k < nk) ? A[col * LD + s_piv[kb + k]] : TC(0);
-            }
-            for (int I = 0; I < NT; ++I) {
-                typename Mfma<TC>::V acc;
+        for (int a = 0; a < RPT; ++a)
+            if (a == pa) {   // uniform
+                if (own_r == pq) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * I + Mfma<TC>::row(lane, r);
-                    const bool in = cin && row < NB;
-                    const int ps = in ? s_pos[row] : 255;
-                    acc[r] = (!in || (ps >= kb && ps < kb + nk)) ? TC(0) : A[col * LD + row];
-                }
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const int k = 4 * s + (lane >> 4), row = 16 * I + (lane & 15);
-                    const TC a = (k < nk && row < NB) ? A[(kb + k) * LD + row] : TC(0);
-                    acc = Mfma<TC>::step(a, b[s], acc);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * I + Mfma<TC>::row(lane, r);
-                    if (cin && row < NB) A[col * LD + row] = acc[r];
+                    for (int i = 0; i < CPT / 2; ++i) {
+                        s_row[tc * (CPT / 2) + i] = V2{i == 0 && tc == jc ? TC(1) : A[a][2 * i], A[a][2 * i + 1]};
+                        A[a][2 * i] = TC(0);
+                        A[a][2 * i + 1] = TC(0);
+                    }
                 }
             }
+        if (tid == 0) {
+            s_piv[k] = (uint8_t)p;
+            s_pos[p] = (uint8_t)k;
         }
-        __syncthreads();
+        const TC ip = TC(1) / pv;
+        TC g[RPT];
+#pragma unroll
+        for (int a = 0; a < RPT; ++a) g[a] = own_r == pq && a == pa ? ip : -f[a / 2][a % 2] * ip;
+        group_sync<NW>();
+        V2 y[CPT / 2];
+#pragma unroll
+        for (int i = 0; i < CPT / 2; ++i) y[i] = s_row[tc * (CPT / 2) + i];
+        TC c0[RPT];
+#pragma unroll
+        for (int b = 0; b < CPT; ++b)
+#pragma unroll
+            for (int a = 0; a < RPT; ++a) {
+                const TC x = fma(g[a], y[b / 2][b % 2], A[a][b]);
+                if (SH == 0) A[a][b] = x;
+                else if (b == 0) c0[a] = x;
+                else A[a][b - 1] = x;
+            }
+        if (SH) {
+#pragma unroll
+            for (int a = 0; a < RPT; ++a) A[a][CPT - 1] = c0[a];
+        }
+    };
+#pragma unroll 1
+    for (int kb = 0; kb < NB; kb += CT) {
+#pragma unroll 1
+        for (int jc = 0; jc < CT - 1; ++jc) step(std::integral_constant<int, 0>{}, kb + jc, jc);
+        step(std::integral_constant<int, 1>{}, kb + CT - 1, CT - 1);
     }
-    // inverse(row R, col C) = a(piv(R), pos(C)); written column-major, consecutive threads
-    // on consecutive rows
+    if (bad) {                                                    // uniform per workgroup
+        if (tid == 0) gi[cid * GI_STRIDE + GI_STATUS] = 3;   // plain vector store
+        return;
+    }
+    group_sync<NW>();
+    int pos[RPT];
+#pragma unroll
+    for (int a = 0; a < RPT; ++a) pos[a] = s_pos[2 * tr + 2 * TR * (a / 2) + a % 2];
+    // inverse(pos(r), piv(k)) = a(r, k), written column-major: the columns tc + CT b of one b at a
+    // time, consecutive threads on consecutive rows
     TO* dst = inv + cd.boff + (size_t)slot * NB * NB;
-    for (int idx = tid; idx < NB * NB; idx += 256) {
-        const int C = idx / NB, R = idx % NB;
-        dst[idx] = store_as<TO, TC>(A[s_pos[C] * LD + s_piv[R]]);
+#pragma unroll
+    for (int b = 0; b < CPT; ++b) {
+        if (act) {
+#pragma unroll
+            for (int a = 0; a < RPT; ++a) s_out[tc * NB + pos[a]] = A[a][b];
+        }
+        group_sync<NW>();
+        for (int idx = tid; idx < CT * NB / 2; idx += NTH) {
+            const int c = idx / (NB / 2), r = 2 * (idx % (NB / 2));
+            TO* w = dst + s_piv[c + CT * b] * NB + r;
+            typedef TO W2 __attribute__((ext_vector_type(2)));
+            *(W2*)w = W2{store_as<TO, TC>(s_out[c * NB + r]), store_as<TO, TC>(s_out[c * NB + r + 1])};
+        }
+        group_sync<NW>();
     }
 }
 
 template <int NB, class TC, class TO>
 fr_status launch_nb(Solver& sv, const GroupArgs& ga, const int* flags, hipStream_t s) {
-    hipLaunchKernelGGL((k_block_invert_mfma<NB, TC, TO>), dim3(ga.ntiles), dim3(256), 0, s, ga, sv.d_blk,
+    hipLaunchKernelGGL((k_block_invert<NB, TC, TO>), dim3(ga.ntiles), dim3(64 * Map<NB>::NW), 0, s, ga, sv.d_blk,
                        (TO*)sv.d_inv, sv.d_gi, flags, sv.inv_colour ? 1 : 0);
     FR_HIP(hipGetLastError());
     return FR_OK;

@@ -624,7 +624,7 @@ fr_status launch_block_assembly(Solver& sv, const double* q, const KArgs& base, 
     return FR_OK;
 }
 
-// explicit inverse of every element block, on the matrix cores (fr_invert.hip)
+// explicit inverse of every element block (fr_invert.hip)
 static fr_status invert_all(Solver& sv, int prec, const int* flags, hipStream_t s) {
     for (const Group& gr : sv.groups) {
         GroupArgs ga = group_args(sv, gr, 1);
