@@ -27,29 +27,34 @@ __device__ __forceinline__ int tile_member(const GroupArgs& ga, int t) {
     return lo;
 }
 
-// z_e = Ainv_e r_e for the elements of one group; state layout [4][E][Np] per case,
-// block row/col index v*Np + s.  Each thread owns RPT consecutive rows and reads them
-// from every column of the column-major inverse with one load (1 double, 4 floats in 16
-// bytes, or 4 bfloat16 in 8 bytes), so every precision streams its blocks with wide loads;
-// FP64 accumulation over the columns in ascending order.
-template <class Tin> struct Pack8;
-template <> struct Pack8<double> {   // 8-byte loads: 1 row per thread
-    static constexpr int R = 1;
-    using Raw = double;
-    __device__ static Raw ld(const double* p) { return *p; }
-    __device__ static void expand(const Raw& v, double* x) { x[0] = v; }
+// z_e = Ainv_e r_e for the elements of one group; state layout [4][E][Np] per case, block row/col
+// index v*Np + s.  Four parts of an element's threads share its columns, part q takes the columns
+// 4 u + q: a load of the element's threads covers four columns, consecutive in memory (a column alone
+// is 72 to 800 bytes, no whole lines), and a thread's chain of loads is a quarter as long, which is
+// the whole time where the elements do not fill the chip.  A thread holds R consecutive rows, one
+// load of 16 bytes (8 in BF16) each column; FP64 accumulation over a part's columns in ascending
+// order, the parts added in order.
+//
+// Bound by the read of the blocks.  STREAM: with loads that leave no line in the last-level cache
+// (stream_blocks).  One application, us, against one part to an element with ordinary loads:
+//     elements         256            2,048          65,536
+//     p = 2 BF16   3.6 (4.7)      4.0 (4.8)       30.7 (33.4)
+//     p = 3 BF16   3.5 (5.3)      4.6 (6.6)        108 (117)
+//     p = 3 FP32   3.4 (5.0)      5.7 (7.4)        195 (220)
+//     p = 3 FP64   3.3 (4.5)     12.7 (12.4)       362 (391)
+//     p = 4 FP64   4.7 (5.6)     26.1 (24.6)       891 (995; 5.9 TB/s of blocks, a plain read 6.1)
+template <class Tin, int R> struct RowPack;
+template <> struct RowPack<double, 2> {
+    typedef double V __attribute__((ext_vector_type(2)));
+    __device__ static void expand(V v, double* x) { x[0] = v.x; x[1] = v.y; }
 };
-template <> struct Pack8<float> {    // 16-byte loads: 4 rows per thread
-    static constexpr int R = 4;
-    using Raw = float4;
-    __device__ static Raw ld(const float* p) { return *reinterpret_cast<const float4*>(p); }
-    __device__ static void expand(const Raw& v, double* x) { x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
+template <> struct RowPack<float, 4> {
+    typedef float V __attribute__((ext_vector_type(4)));
+    __device__ static void expand(V v, double* x) { x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
 };
-template <> struct Pack8<uint16_t> { // 8-byte loads: 4 rows per thread
-    static constexpr int R = 4;
-    using Raw = uint2;
-    __device__ static Raw ld(const uint16_t* p) { return *reinterpret_cast<const uint2*>(p); }
-    __device__ static void expand(const Raw& v, double* x) {
+template <> struct RowPack<uint16_t, 4> {
+    typedef unsigned V __attribute__((ext_vector_type(2)));
+    __device__ static void expand(V v, double* x) {
         x[0] = (double)__uint_as_float(v.x << 16);
         x[1] = (double)__uint_as_float(v.x & 0xffff0000u);
         x[2] = (double)__uint_as_float(v.y << 16);
@@ -57,92 +62,90 @@ template <> struct Pack8<uint16_t> { // 8-byte loads: 4 rows per thread
     }
 };
 
+// a workgroup: one element, or as many as 256 threads hold where an element's are fewer than a wave
+// or fill their last one badly (p <= 2)
 template <class Tin, int NB>
 struct ApplyShape {
-    static constexpr int RPT = Pack8<Tin>::R, TPE = NB / RPT, EPB = 256 / TPE, threads = EPB * TPE;
-    static_assert(NB % RPT == 0, "block size must be a multiple of the rows per thread");
+    static constexpr int R = sizeof(Tin) == 8 ? 2 : 4, PARTS = 4, TPE = NB / R, TPT = TPE * PARTS;
+    static constexpr int EPB = NB <= 36 ? 256 / TPT : 1, threads = EPB * TPT;
+    static_assert(NB % R == 0 && NB % PARTS == 0 && threads <= 256, "whole packs, whole quarters");
 };
 
 // z_e = D_e^-1 r_e for every element, or, for the Gauss-Seidel sweeps, for the elements of
 // one colour only (tiles over that colour, ga.csel): z_e = D_e^-1 (r_e - b_e) (b may be null),
 // or z_e -= D_e^-1 r_e (sub).
-template <class Tin, int NB>
-__global__ void __launch_bounds__(256) k_block_apply(GroupArgs ga, const Tin* __restrict__ inv,
-                                                     const double* __restrict__ r, const double* __restrict__ b,
-                                                     double* __restrict__ z, int sub,
-                                                     const int* __restrict__ flags, int flag, int cl) {
+template <class Tin, int NB, bool STREAM>
+__global__ void __launch_bounds__(256)
+k_block_apply(GroupArgs ga, const Tin* __restrict__ inv, const double* __restrict__ r, const double* __restrict__ b,
+              double* __restrict__ z, int sub, const int* __restrict__ flags, int flag, int cl) {
     using SH = ApplyShape<Tin, NB>;
-    constexpr int Np = NB / 4, RPT = SH::RPT, TPE = SH::TPE, EPB = SH::EPB;
+    constexpr int Np = NB / 4, R = SH::R, TPE = SH::TPE, EPB = SH::EPB, S = SH::PARTS, Q = NB / S;
+    using P = RowPack<Tin, R>;
     __shared__ double rs[EPB][NB + 1];
+    __shared__ double sh[EPB][S][NB];
     const int t = blockIdx.x;
     if (t >= ga.ntiles) return;
     const int lo = tile_member(ga, t);
     const int cid = ga.ids[lo];
     if (flags && flags[cid * GI_STRIDE + flag]) return;
     const CaseDev& cd = ga.cases[cid];
-    const int el = threadIdx.x / TPE, r0 = (threadIdx.x % TPE) * RPT;
+    const int el = threadIdx.x / SH::TPT, part = threadIdx.x / TPE % S, r0 = (threadIdx.x % TPE) * R;
     // one colour of the Gauss-Seidel sweeps (ga.csel set): the tiles run over the member's
     // elements of that colour, taken from its colour-sorted element list.  slot: the
     // element's block in the stored inverse (its position in that list in the colour layout)
     int slot = (t - ga.pfx[lo]) * EPB + el;
-    bool act = (el < EPB) && (slot < cd.E);
+    bool act = slot < cd.E;
     if (ga.csel) {
-        act = (el < EPB) && (slot < ga.csel[2 * lo + 1]);
+        act = slot < ga.csel[2 * lo + 1];
         slot += ga.csel[2 * lo];
     }
     int e = slot;
     if (ga.csel || cl) e = act ? cd.g.corder[slot] : 0;
     if (!cl) slot = e;
     const size_t EN = (size_t)cd.E * Np;
-    size_t gid[RPT];
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-        const int row = r0 + k;
-        gid[k] = cd.off + (row / Np) * EN + (size_t)e * Np + (row % Np);
-        if (act) rs[el][row] = b ? r[gid[k]] - b[gid[k]] : r[gid[k]];
+    auto gid = [&](int row) { return cd.off + (row / Np) * EN + (size_t)e * Np + (row % Np); };
+    if (act && part < R) {
+        const size_t g = gid(r0 + part);
+        rs[el][r0 + part] = b ? r[g] - b[g] : r[g];
     }
     __syncthreads();
-    if (!act) return;
     const Tin* A = inv + cd.boff + (size_t)slot * NB * NB + r0;
-    double acc[RPT];
+    double acc[R];
 #pragma unroll
-    for (int k = 0; k < RPT; ++k) acc[k] = 0.0;
-    // columns in batches of U, every load of a batch issued before any is used (so that
-    // U loads per thread are in flight), summed in ascending column order
-    constexpr int U = 16, NBU = NB - NB % U;
-    for (int c0 = 0; c0 < NBU; c0 += U) {
-        typename Pack8<Tin>::Raw raw[U];
+    for (int k = 0; k < R; ++k) acc[k] = 0.0;
+    // the part's columns in batches whose loads are all issued before any is used
+    constexpr int NBAT = (Q + 15) / 16, U = (Q + NBAT - 1) / NBAT;
+    if (act) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) raw[u] = Pack8<Tin>::ld(A + (size_t)(c0 + u) * NB);
+        for (int u0 = 0; u0 < Q; u0 += U) {
+            typename P::V raw[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            double x[RPT];
-            Pack8<Tin>::expand(raw[u], x);
-            const double rc = rs[el][c0 + u];
+            for (int u = 0; u < U; ++u)
+                if (u0 + u < Q) {
+                    const auto* x = reinterpret_cast<const typename P::V*>(A + (size_t)(S * (u0 + u) + part) * NB);
+                    raw[u] = STREAM ? __builtin_nontemporal_load(x) : *x;
+                }
 #pragma unroll
-            for (int k = 0; k < RPT; ++k) acc[k] += x[k] * rc;
+            for (int u = 0; u < U; ++u)
+                if (u0 + u < Q) {
+                    double x[R];
+                    P::expand(raw[u], x);
+                    const double rc = rs[el][S * (u0 + u) + part];
+#pragma unroll
+                    for (int k = 0; k < R; ++k) acc[k] += x[k] * rc;
+                }
         }
     }
-    if (NBU < NB) {
-        typename Pack8<Tin>::Raw raw[NB % U > 0 ? NB % U : 1];
 #pragma unroll
-        for (int u = 0; u < NB - NBU; ++u) raw[u] = Pack8<Tin>::ld(A + (size_t)(NBU + u) * NB);
-#pragma unroll
-        for (int u = 0; u < NB - NBU; ++u) {
-            double x[RPT];
-            Pack8<Tin>::expand(raw[u], x);
-            const double rc = rs[el][NBU + u];
-#pragma unroll
-            for (int k = 0; k < RPT; ++k) acc[k] += x[k] * rc;
-        }
-    }
-    if (sub) {
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) z[gid[k]] -= acc[k];
-    } else {
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) z[gid[k]] = acc[k];
-    }
+    for (int k = 0; k < R; ++k) sh[el][part][r0 + k] = acc[k];
+    __syncthreads();
+    // R of the parts add and write a row each
+    if (!act || part >= R) return;
+    const int row = r0 + part;
+    const double v = ((sh[el][0][row] + sh[el][1][row]) + sh[el][2][row]) + sh[el][3][row];
+    const size_t g = gid(row);
+    if (sub) z[g] -= v;
+    else z[g] = v;
 }
 
 // ------------------------------------------------------------------ segmented Krylov reductions
@@ -646,11 +649,27 @@ fr_status launch_block_invert(Solver& sv, int prec, const int* flags, hipStream_
     return FR_OK;
 }
 
-// tile widths (elements per workgroup) of the block apply, per stored precision (FP32 and
-// BF16 both take 4 rows per thread)
+// tile widths (elements per workgroup) of the block apply
+template <int NB> static std::vector<int> apply_widths() { return {ApplyShape<double, NB>::EPB, ApplyShape<float, NB>::EPB}; }
 std::vector<int> block_apply_widths(int p) {
-    const int nb = 4 * (p + 1) * (p + 1);
-    return {256 / nb, 1024 / nb};
+    switch (p) {
+        case 1: return apply_widths<16>();
+        case 2: return apply_widths<36>();
+        case 3: return apply_widths<64>();
+    }
+    return apply_widths<100>();
+}
+
+// size of the last-level cache
+constexpr size_t LLC_BYTES = (size_t)256 << 20;
+// Blocks and Krylov basis are each read once or twice an iteration; together beyond the cache they
+// only evict each other and the smaller vectors and packs, so the blocks are then streamed.  Whole
+// BDF2 steps, ms, streamed (plain): p = 3 FP32, blocks and basis 268 + 260 MB 19.2 (20.5); BF16
+// 134 + 260 MB 16.6 (16.9); FP32 151 + 146 MB 13.0 (13.1); p = 4 FP64 328 + 101 MB 18.9 (20.8); and
+// below the line 184 + 57 MB 13.7 (13.1), 134 + 65 MB 9.8 (9.7).
+static bool stream_blocks(const Solver& sv, size_t entry) {
+    const size_t basis = sv.d_V ? (size_t)(sv.kry_m + 1) * sv.Ntot * sizeof(double) : 0;
+    return sv.Btot * entry + basis > LLC_BYTES;
 }
 
 struct ApplyArgs {
@@ -669,8 +688,9 @@ static fr_status apply_as(const Solver& sv, const Group& gr, const ApplyArgs& x,
     GroupArgs ga = group_args(sv, gr, SH::EPB, x.color);
     if (!ga.pfx) { fr_set_error("tile prefix missing"); return FR_EINVAL; }
     if (ga.ntiles == 0) return FR_OK;
-    hipLaunchKernelGGL((k_block_apply<Tin, NB>), dim3(ga.ntiles), dim3(SH::threads), 0, s, ga, (const Tin*)sv.d_inv,
-                       x.r, x.b, x.z, x.sub, x.flags, x.flag, sv.inv_colour ? 1 : 0);
+    auto kernel = stream_blocks(sv, sizeof(Tin)) ? k_block_apply<Tin, NB, true> : k_block_apply<Tin, NB, false>;
+    hipLaunchKernelGGL(kernel, dim3(ga.ntiles), dim3(SH::threads), 0, s, ga, (const Tin*)sv.d_inv, x.r, x.b, x.z, x.sub,
+                       x.flags, x.flag, sv.inv_colour ? 1 : 0);
     FR_HIP(hipGetLastError());
     return FR_OK;
 }
