@@ -200,11 +200,17 @@ __device__ __forceinline__ double wave_sum8(const double* a, int lane) {
     return d;
 }
 
+// An entry of the basis.  STREAM: with a load that leaves no line in the last-level cache (streamed()).
+template <bool STREAM> __device__ __forceinline__ double basis_entry(const double* p) {
+    return STREAM ? __builtin_nontemporal_load(p) : *p;
+}
+
 // Dot products V_i . w for i in [DB*blockIdx.y, DB*blockIdx.y + DB) ∩ [0, nv) into
 // partial[i][item], plus |w|^2 into npart[item] when it is not null (y-block 0 only; mass_only:
 // over the first E Np entries of the case).  DB = 8 vectors per pass (16 measured slower: fewer
 // workgroups, heavier reduction).
 constexpr int DB = 8;
+template <bool STREAM>
 __global__ void __launch_bounds__(RED_THREADS) k_dots8(RedArgs ra, const double* __restrict__ V, size_t ldv, int nv,
                                                        const double* __restrict__ w, int mass_only,
                                                        double* __restrict__ partial, double* __restrict__ npart) {
@@ -234,7 +240,7 @@ __global__ void __launch_bounds__(RED_THREADS) k_dots8(RedArgs ra, const double*
                 // all rows loaded before any is used (rows past cnt - 1 reload row cnt - 1, unused)
                 double x[DB];
 #pragma unroll
-                for (int i = 0; i < DB; ++i) x[i] = Vc[(size_t)(i < cnt ? i : cnt - 1) * ldv + t];
+                for (int i = 0; i < DB; ++i) x[i] = basis_entry<STREAM>(Vc + (size_t)(i < cnt ? i : cnt - 1) * ldv + t);
 #pragma unroll
                 for (int i = 0; i < DB; ++i)
                     if (i < cnt) acc[i] += x[i] * wt;
@@ -332,6 +338,7 @@ __device__ __forceinline__ double scaled(double sj, double w) {
 
 // w_out = (s_j) w_in - sum_{i < nv} h_i s_i V_i, and the partial |w_out|^2 of each item when
 // npart is not null
+template <bool STREAM>
 __global__ void __launch_bounds__(RED_THREADS) k_update(RedArgs ra, DotRef dr, GsRef g, const double* __restrict__ V,
                                                         size_t ldv, int nv, const double* w_in, double* w_out,
                                                         double* __restrict__ npart, int rev) {
@@ -368,15 +375,18 @@ __global__ void __launch_bounds__(RED_THREADS) k_update(RedArgs ra, DotRef dr, G
             for (; i + 16 <= nv; i += 16) {
                 double x[16];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) x[u] = V[(size_t)(i + u) * ldv + t];
+                for (int u = 0; u < 16; ++u) x[u] = basis_entry<STREAM>(V + (size_t)(i + u) * ldv + t);
 #pragma unroll
                 for (int u = 0; u < 16; u += 4)
                     wt -= cf[i + u] * x[u] + cf[i + u + 1] * x[u + 1] + cf[i + u + 2] * x[u + 2] + cf[i + u + 3] * x[u + 3];
             }
-            for (; i + 4 <= nv; i += 4)
-                wt -= cf[i] * V[i * ldv + t] + cf[i + 1] * V[(i + 1) * ldv + t] + cf[i + 2] * V[(i + 2) * ldv + t] +
-                      cf[i + 3] * V[(i + 3) * ldv + t];
-            for (; i < nv; ++i) wt -= cf[i] * V[i * ldv + t];
+            for (; i + 4 <= nv; i += 4) {
+                double x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = basis_entry<STREAM>(V + (size_t)(i + u) * ldv + t);
+                wt -= cf[i] * x[0] + cf[i + 1] * x[1] + cf[i + 2] * x[2] + cf[i + 3] * x[3];
+            }
+            for (; i < nv; ++i) wt -= cf[i] * basis_entry<STREAM>(V + (size_t)i * ldv + t);
             w_out[t] = wt;
             nacc += wt * wt;
         }
@@ -397,7 +407,7 @@ __global__ void __launch_bounds__(RED_THREADS) k_update(RedArgs ra, DotRef dr, G
 // w_out), from the basis entries already loaded for the update.  The update's grouping and the
 // reductions' order are those of the two kernels, so the results are theirs bit for bit.  NV bounds
 // nv.
-template <int NV>
+template <int NV, bool STREAM>
 __global__ void __launch_bounds__(RED_THREADS) k_update_dots(RedArgs ra, DotRef dr, GsRef g,
                                                              const double* __restrict__ V, size_t ldv, int nv,
                                                              const double* w_in, double* w_out,
@@ -421,7 +431,7 @@ __global__ void __launch_bounds__(RED_THREADS) k_update_dots(RedArgs ra, DotRef 
             // all rows loaded before any is used (rows past nv - 1 reload row nv - 1, unused)
             double x[NV];
 #pragma unroll
-            for (int k = 0; k < NV; ++k) x[k] = V[(size_t)(k < nv ? k : nv - 1) * ldv + t];
+            for (int k = 0; k < NV; ++k) x[k] = basis_entry<STREAM>(V + (size_t)(k < nv ? k : nv - 1) * ldv + t);
             double wt = scaled(sj, w_in[t]);
             const int n4 = nv & ~3;
 #pragma unroll
@@ -779,10 +789,16 @@ static fr_status final_dots(const Solver& sv, int nv, const GsRef& g, int set, c
     return FR_OK;
 }
 
+// a launch's basis vectors exceed the cache: nothing of them is left for the next launch, and loads
+// that leave no line spare what the cache holds of the blocks, packs and other vectors.  BDF2 steps of
+// 256 x 256 elements, 30 Krylov vectors: p = 4 FP64 237.0 -> 232.5 ms, p = 3 BF16 39.6 -> 38.5 ms; below
+// the line a batch of 12 cases, 46.0 ms plain, 46.5 streamed.
+static bool streamed(int nv, size_t ldv) { return nv * ldv * sizeof(double) > LLC_BYTES; }
+
 fr_status la_dots(const Solver& sv, const double* V, size_t ldv, int nv, const double* w, const GsRef& g, int set,
                   const int* flags, int flag, hipStream_t s) {
     FR_TRY(too_many(nv));
-    hipLaunchKernelGGL(k_dots8, dim3(item_grid(sv.nditem), (nv + DB - 1) / DB), dim3(RED_THREADS), 0, s,
+    hipLaunchKernelGGL(streamed(nv, ldv) ? k_dots8<true> : k_dots8<false>, dim3(item_grid(sv.nditem), (nv + DB - 1) / DB), dim3(RED_THREADS), 0, s,
                        dot_args(sv, flags, flag), V, ldv, nv, w, 0, part_dots(sv, set), (double*)nullptr);
     FR_HIP(hipGetLastError());
     return final_dots(sv, nv, g, set, flags, flag, s);
@@ -792,7 +808,7 @@ fr_status la_update(const Solver& sv, const double* V, size_t ldv, int nv, const
                     bool want_norm, const GsRef& g, int set, const int* flags, int flag, hipStream_t s, bool rev) {
     FR_TRY(too_many(nv));
     const DotRef dr{part_dots(sv, set), sv.nditem, sv.d_dfirst};
-    hipLaunchKernelGGL(k_update, dim3(item_grid(sv.nuitem)), dim3(RED_THREADS), 0, s, upd_args(sv, flags, flag), dr, g,
+    hipLaunchKernelGGL(streamed(nv, ldv) ? k_update<true> : k_update<false>, dim3(item_grid(sv.nuitem)), dim3(RED_THREADS), 0, s, upd_args(sv, flags, flag), dr, g,
                        V, ldv, nv, w_in, w_out, want_norm ? part_norm(sv) : nullptr, rev ? 1 : 0);
     FR_HIP(hipGetLastError());
     return FR_OK;
@@ -805,12 +821,13 @@ fr_status la_update_dots(const Solver& sv, const double* V, size_t ldv, int nv, 
     const RedArgs ra = dot_args(sv, flags, flag);
     const dim3 grid(item_grid(sv.nditem)), block(RED_THREADS);
     double* out = part_dots(sv, 1 - set);
+    const bool st = streamed(nv, ldv);
     if (nv <= 8)
-        hipLaunchKernelGGL(k_update_dots<8>, grid, block, 0, s, ra, dr, g, V, ldv, nv, w_in, w_out, out, rev ? 1 : 0);
+        hipLaunchKernelGGL((st ? k_update_dots<8, true> : k_update_dots<8, false>), grid, block, 0, s, ra, dr, g, V, ldv, nv, w_in, w_out, out, rev ? 1 : 0);
     else if (nv <= 16)
-        hipLaunchKernelGGL(k_update_dots<16>, grid, block, 0, s, ra, dr, g, V, ldv, nv, w_in, w_out, out, rev ? 1 : 0);
+        hipLaunchKernelGGL((st ? k_update_dots<16, true> : k_update_dots<16, false>), grid, block, 0, s, ra, dr, g, V, ldv, nv, w_in, w_out, out, rev ? 1 : 0);
     else
-        hipLaunchKernelGGL(k_update_dots<32>, grid, block, 0, s, ra, dr, g, V, ldv, nv, w_in, w_out, out, rev ? 1 : 0);
+        hipLaunchKernelGGL((st ? k_update_dots<32, true> : k_update_dots<32, false>), grid, block, 0, s, ra, dr, g, V, ldv, nv, w_in, w_out, out, rev ? 1 : 0);
     FR_HIP(hipGetLastError());
     return final_dots(sv, nv, g, 1 - set, flags, flag, s);
 }
@@ -826,7 +843,7 @@ fr_status la_combine(const Solver& sv, const double* V, size_t ldv, const double
 fr_status la_norm(const Solver& sv, const double* w, bool mass_only, double* out, int ostride, const int* flags,
                   int flag, hipStream_t s) {
     const RedArgs ra = dot_args(sv, flags, flag);
-    hipLaunchKernelGGL(k_dots8, dim3(item_grid(sv.nditem)), dim3(RED_THREADS), 0, s, ra, w, (size_t)0, 0, w,
+    hipLaunchKernelGGL(k_dots8<false>, dim3(item_grid(sv.nditem)), dim3(RED_THREADS), 0, s, ra, w, (size_t)0, 0, w,
                        mass_only ? 1 : 0, part_dots(sv, 0), part_norm(sv));
     FR_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_final_norm, dim3(sv.n), dim3(256), 0, s, ra, part_norm(sv), sv.d_dfirst, out, ostride);

@@ -1,8 +1,11 @@
-"""Reads past the last-level cache: the block apply takes loads that leave no line there once blocks
-and basis exceed it.
+"""Reads past the last-level cache: the block apply and the Gram-Schmidt kernels take loads that leave
+no line there once blocks and basis exceed it.
 
 * The block apply with the blocks alone (within the cache) and after a reserve whose basis takes both
   past it: bit for bit the same, and D z = r to rounding for one of them.
+* A linear solve whose basis passes the cache inside the cycle: it meets its tolerance in the operator
+  (twice, for the rounding of dq = q1 - q and of the two operator forms), and the fused and separate
+  re-orthogonalisations, which share no launch, agree bit for bit.
 """
 import numpy as np
 import pytest
@@ -48,3 +51,24 @@ def test_streamed_blocks_are_bitwise(p, nx, ny, prec, size):
     g.reserve(156, prec)
     g.block_jacobi_factor(q, 20.0, 3.0, prec)
     assert torch.equal(z, g.block_jacobi_apply(r))
+
+
+def test_streamed_basis():
+    out = []
+    for fused in (0, 1):
+        mesh, g, q = _problem(130, 128, 3)
+        g.set_option("gram_schmidt", 2)
+        g.set_option("fused_gram_schmidt", fused)
+        dtau, tol = 0.2, 1e-6
+        q1 = q.clone()
+        st = g.steady_solve(q1, dtau0=dtau, dtau_min=1e-3, tol_pseudo=1e-30, tol_res=tol, krylov=70, max_lin_it=900,
+                            max_steps=1)
+        # 32 vectors and more pass the cache
+        assert 32 * q.numel() * 8 > LLC and 32 < st["gmres_its"] < 900
+        dq = q1 - q
+        R = g.residual(q)
+        rel = float((R - g.bdf_operator(q, dq, 0.0, 1.0 / dtau)).norm() / R.norm())
+        print(f"[streamed] fused={fused}: {st['gmres_its']} its, {rel:.2e}", flush=True)
+        assert rel <= 2 * tol
+        out.append(q1)
+    assert torch.equal(out[0], out[1])
