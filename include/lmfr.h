@@ -264,8 +264,8 @@ fr_status fr_steady_solve(fr_ctx ctx, double* q, const fr_steady_opts* opts, fr_
  * the forward half of that sweep: K - 1 operator passes over one colour each and one
  * block apply; used by fr_block_jacobi_apply and the GMRES of the BDF2 and steady solves),
  * and a manual launch shape of the fused kernels (what fr_autotune chooses): "tile_lanes" (0 =
- * default, 64, 128, 256; dual-number modes cap it at 128), "tile_grid" (0 = one
- * workgroup per tile, else the persistent grid size), "tile_xcd" (1 = each XCD walks a
+ * default, 64, 128, 256; dual-number modes cap it at 128), "tile_grid" (0 =
+ * default, else the persistent grid size, at most one workgroup per tile), "tile_xcd" (1 = each XCD walks a
  * contiguous eighth of the tiles, 0 = round robin). */
 fr_status fr_set_option(fr_ctx ctx, const char* name, int64_t value);
 

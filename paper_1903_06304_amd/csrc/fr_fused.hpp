@@ -1566,13 +1566,47 @@ inline bool group_affine(const Solver& sv, const Group& gr) {
     return true;
 }
 
-// grid of a launch: one workgroup per tile by default, else the tuned persistent size;
-// always a multiple of 8 (the XCD count) so every XCD walks an equal tile range
-inline unsigned grid_of(int ntiles, int grid) {
-    long long g = grid > 0 ? grid : ntiles;
+// workgroups of a kernel that the device holds at a time (0: not known)
+template <auto KERNEL>
+int resident_workgroups(int threads) {
+    static const int r = [&] {
+        int dev = 0, cus = 0, per_cu = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, threads, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return 0;
+        }
+        return cus * per_cu;
+    }();
+    return r;
+}
+
+// Grid of a launch, a multiple of 8 (the XCD count) so that every XCD walks an equal tile range: the
+// tuned size if there is one, else one workgroup per tile.  resident (the workgroups that the device
+// holds at a time, 0: not given): where they get tile counts that differ little (nine tenths of the
+// last round filled), that many workgroups stay and walk the tiles: they load the operators once and
+// ask for the next tile's connectivity a tile ahead.  Given for the general kernels of J v and of the
+// Newton operator, which run one or two waves a SIMD with little to hide a tile's start: J v, 256 x 256
+// curved elements, 126 us at p = 3 (139 with a workgroup per tile), 275 at p = 4 (297).  Not for the
+// others: the affine J v at p = 4 loses (124 for 118), a residual of 255 x 129 curved elements with
+// its 4,112 tiles in five even rounds of 823 takes 48.6 us for 42.2.
+inline unsigned grid_of(int ntiles, int grid, int resident) {
+    long long g = grid > 0 && grid < ntiles ? grid : ntiles;
+    if (grid == 0 && resident > 0 && ntiles > resident) {
+        const long long rounds = (ntiles + resident - 1) / resident;
+        if (10LL * ntiles >= 9 * rounds * resident) g = (ntiles + rounds - 1) / rounds;
+    }
     g = ((g + 7) / 8) * 8;
     if (g < 8) g = 8;
     return (unsigned)g;
+}
+
+template <auto KERNEL, bool STAY = false>
+void start(const GroupArgs& ga, const KArgs& a, const OpTab& op, int grid, int threads, hipStream_t s) {
+    int resident = 0;
+    if constexpr (STAY) resident = resident_workgroups<KERNEL>(threads);
+    hipLaunchKernelGGL(KERNEL, dim3(grid_of(ga.ntiles, grid, resident)), dim3(threads), 0, s, ga, a, op);
 }
 
 template <int P, bool VISC, bool MOV, int MODE, int LANES>
@@ -1606,30 +1640,24 @@ fr_status run(const Solver& sv, const Group& gr, const KArgs& a, int grid, int x
             aff = group_affine(sv, gr);
             if (aff) {
                 if (cs)
-                    hipLaunchKernelGGL((k_lin_aff<P, VISC, LANES, true>), dim3(grid_of(ga.ntiles, grid)),
-                                       dim3(SH::threads), 0, s, ga, a, op);
+                    start<k_lin_aff<P, VISC, LANES, true>>(ga, a, op, grid, SH::threads, s);
                 else
-                    hipLaunchKernelGGL((k_lin_aff<P, VISC, LANES>), dim3(grid_of(ga.ntiles, grid)),
-                                       dim3(SH::threads), 0, s, ga, a, op);
+                    start<k_lin_aff<P, VISC, LANES>>(ga, a, op, grid, SH::threads, s);
             }
         }
         if (!aff) {
             if (gr.bnd) {
                 if constexpr (LANES <= 128) {
                     if (cs)
-                        hipLaunchKernelGGL((k_lin<P, VISC, MOV, LANES, B, true, !B>), dim3(grid_of(ga.ntiles, grid)),
-                                           dim3(SH::threads), 0, s, ga, a, op);
+                        start<k_lin<P, VISC, MOV, LANES, B, true, !B>, true>(ga, a, op, grid, SH::threads, s);
                     else
-                        hipLaunchKernelGGL((k_lin<P, VISC, MOV, LANES, B, true>), dim3(grid_of(ga.ntiles, grid)),
-                                           dim3(SH::threads), 0, s, ga, a, op);
+                        start<k_lin<P, VISC, MOV, LANES, B, true>, true>(ga, a, op, grid, SH::threads, s);
                 }
             } else {
                 if (cs)
-                    hipLaunchKernelGGL((k_lin<P, VISC, MOV, LANES, B, false, !B>), dim3(grid_of(ga.ntiles, grid)),
-                                       dim3(SH::threads), 0, s, ga, a, op);
+                    start<k_lin<P, VISC, MOV, LANES, B, false, !B>, true>(ga, a, op, grid, SH::threads, s);
                 else
-                    hipLaunchKernelGGL((k_lin<P, VISC, MOV, LANES, B, false>), dim3(grid_of(ga.ntiles, grid)),
-                                       dim3(SH::threads), 0, s, ga, a, op);
+                    start<k_lin<P, VISC, MOV, LANES, B, false>, true>(ga, a, op, grid, SH::threads, s);
             }
         }
     } else {
@@ -1642,14 +1670,11 @@ fr_status run(const Solver& sv, const Group& gr, const KArgs& a, int grid, int x
                 // the tangent-only form whenever R is not wanted as well
                 if constexpr (MODE == MODE_JVP || MODE == MODE_AOP) {
                     if (MODE == MODE_AOP || !a.out2)
-                        hipLaunchKernelGGL((k_fused_aff<P, VISC, MODE, LANES, true>), dim3(grid_of(ga.ntiles, grid)),
-                                           dim3(SH::threads), 0, s, ga, a, op);
+                        start<k_fused_aff<P, VISC, MODE, LANES, true>>(ga, a, op, grid, SH::threads, s);
                     else
-                        hipLaunchKernelGGL((k_fused_aff<P, VISC, MODE, LANES>), dim3(grid_of(ga.ntiles, grid)),
-                                           dim3(SH::threads), 0, s, ga, a, op);
+                        start<k_fused_aff<P, VISC, MODE, LANES>>(ga, a, op, grid, SH::threads, s);
                 } else {
-                    hipLaunchKernelGGL((k_fused_aff<P, VISC, MODE, LANES>), dim3(grid_of(ga.ntiles, grid)),
-                                       dim3(SH::threads), 0, s, ga, a, op);
+                    start<k_fused_aff<P, VISC, MODE, LANES>>(ga, a, op, grid, SH::threads, s);
                 }
             }
         }
@@ -1660,22 +1685,18 @@ fr_status run(const Solver& sv, const Group& gr, const KArgs& a, int grid, int x
                 if constexpr (LANES <= 128) {
                     if constexpr (dual1) {
                         if (tan)
-                            hipLaunchKernelGGL((k_fused<P, VISC, MOV, MODE, 1, LANES, true, true>),
-                                               dim3(grid_of(ga.ntiles, grid)), dim3(SH::threads), 0, s, ga, a, op);
+                            start<k_fused<P, VISC, MOV, MODE, 1, LANES, true, true>, true>(ga, a, op, grid, SH::threads, s);
                     }
                     if (!tan)
-                        hipLaunchKernelGGL((k_fused<P, VISC, MOV, MODE, 1, LANES, true>), dim3(grid_of(ga.ntiles, grid)),
-                                           dim3(SH::threads), 0, s, ga, a, op);
+                        start<k_fused<P, VISC, MOV, MODE, 1, LANES, true>>(ga, a, op, grid, SH::threads, s);
                 }
             } else {
                 if constexpr (dual1) {
                     if (tan)
-                        hipLaunchKernelGGL((k_fused<P, VISC, MOV, MODE, 1, LANES, false, true>),
-                                           dim3(grid_of(ga.ntiles, grid)), dim3(SH::threads), 0, s, ga, a, op);
+                        start<k_fused<P, VISC, MOV, MODE, 1, LANES, false, true>, true>(ga, a, op, grid, SH::threads, s);
                 }
                 if (!tan)
-                    hipLaunchKernelGGL((k_fused<P, VISC, MOV, MODE, 1, LANES, false>), dim3(grid_of(ga.ntiles, grid)),
-                                       dim3(SH::threads), 0, s, ga, a, op);
+                    start<k_fused<P, VISC, MOV, MODE, 1, LANES, false>>(ga, a, op, grid, SH::threads, s);
             }
         }
     }
@@ -1687,8 +1708,13 @@ fr_status run(const Solver& sv, const Group& gr, const KArgs& a, int grid, int x
 // workgroup widths built per mode: plain doubles 64/128/256 lanes, dual numbers 64/128
 template <int P, bool VISC, bool MOV, int MODE>
 fr_status run_lanes(const Solver& sv, const Group& gr, const KArgs& a, const Tune& t, hipStream_t s) {
+    // One wave to a workgroup meets no barrier of another: viscous residual at p = 3, 128 x 128 elements,
+    // 14.5 us affine and 23.6 curved (16.2 and 25.8 at 128 lanes), 256 x 256 43.0 and 74.2 (43.7, 76.0);
+    // Euler residuals are the same or lose up to 6%, the packs' kernels within 1% in whole steps, and
+    // keep 128.  At p = 4 two elements of 25 points leave 14 of 64 lanes idle, five leave 3 of 128: J v
+    // of 256 x 256 elements 117.7 us affine, 297 curved (130.6 and 349 at 64 lanes).
     constexpr bool dual = MODE == MODE_JVP || MODE == MODE_AOP;
-    int lanes = t.lanes > 0 ? t.lanes : (dual ? 64 : 128);
+    int lanes = t.lanes > 0 ? t.lanes : (P != 4 && (dual || (MODE == MODE_R && VISC)) ? 64 : 128);
     if (gr.bnd && lanes > 128) lanes = 128;   // the boundary-face variants are built for 64 and 128 lanes
     switch (lanes) {
         case 64: return run<P, VISC, MOV, MODE, 64>(sv, gr, a, t.grid, t.xcd, s);

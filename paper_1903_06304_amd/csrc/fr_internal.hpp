@@ -163,7 +163,7 @@ struct GroupArgs {
 // launch shape of the fused kernel: workgroup width (lanes) and persistent grid size
 struct Tune {
     int lanes = 0;        // 0: default of the variant
-    int grid = 0;         // 0: one workgroup per tile
+    int grid = 0;         // 0: default of the variant; at most one workgroup per tile
     int xcd = 1;          // 1: each XCD walks a contiguous eighth of the tiles; 0: round robin
 };
 

@@ -179,16 +179,13 @@ fr_status solver_init(Solver& sv, const fr_ctx* ctxs, int n) {
     FR_TRY(dalloc(&sv.d_step, (size_t)n));
     FR_TRY(dalloc(&sv.d_part, part_doubles(sv)));
     sv.h_pin_doubles = (size_t)n * (SUM_STRIDE + sizeof(CaseStep) / sizeof(double) + 2) + 64;
-    if (hipHostMalloc((void**)&sv.h_pin, sv.h_pin_doubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    const size_t pinned = sv.h_pin_doubles * sizeof(double);   // then the segment flags
+    if (hipHostMalloc((void**)&sv.h_pin, pinned + MAXV * sizeof(int), hipHostMallocDefault) != hipSuccess) {
         sv.h_pin = nullptr;
         fr_set_error("hipHostMalloc failed");
         return FR_ENOMEM;
     }
-    if (hipHostMalloc((void**)&sv.h_seg, MAXV * sizeof(int), hipHostMallocDefault) != hipSuccess) {
-        sv.h_seg = nullptr;
-        fr_set_error("hipHostMalloc failed");
-        return FR_ENOMEM;
-    }
+    sv.h_seg = reinterpret_cast<int*>(sv.h_pin + sv.h_pin_doubles);
     return FR_OK;
 }
 
@@ -212,7 +209,6 @@ void solver_free(Solver& sv) {
     if (sv.ev_out) (void)hipEventDestroy(sv.ev_out);
     for (hipEvent_t e : sv.ev_seg)
         if (e) (void)hipEventDestroy(e);
-    if (sv.h_seg) (void)hipHostFree(sv.h_seg);
     sv = Solver();
 }
 
@@ -549,8 +545,9 @@ fr_status solver_autotune(Solver& sv, const char* cache_path, hipStream_t s) {
     std::string appended;
     // persistent grids up to 6144 workgroups: the lighter variants run 3 waves per SIMD, and
     // 768 / 1536 / 3072 workgroups of 256 / 128 / 64 lanes are one resident round at that rate
-    const int grids[] = {0, 512, 1024, 1536, 2048, 3072, 4096, 6144};
-    constexpr int NGRID = 8;
+    // (0: the default rule; the last: one workgroup per tile)
+    const int grids[] = {0, 512, 1024, 1536, 2048, 3072, 4096, 6144, 1 << 24};
+    constexpr int NGRID = 9;
     for (Group& g : sv.groups) {
         for (int mode : {MODE_R, MODE_JVP, MODE_AOP, MODE_PREP, MODE_LIN}) {
             const std::string key = tune_key(arch, sv, g, mode);
