@@ -259,10 +259,47 @@ KArgs bdf_args(const Solver& sv, const double* q) {
     return a;
 }
 
-fr_status bdf_op(const Solver& sv, const double* q, const double* v, double* Av, int flag, hipStream_t s) {
+fr_status bdf_op(const Solver& sv, const double* q, const double* v, double* Av, int flag, hipStream_t s, int only = -1) {
     KArgs a = bdf_args(sv, q);
     a.v = v; a.out = Av; a.flag = flag;
-    return solver_fused(sv, MODE_LIN, a, s);
+    return solver_fused(sv, MODE_LIN, a, s, only);
+}
+
+// Whether the groups' launches of an Arnoldi step go to parallel branches of its graph.  A fork and
+// join of the graph costs about 20 us a step; side by side the kernels of ten launches and more, each
+// too small for the chip, save more than that.  BDF2 steps of batches, ms, in branches (one after the
+// other): 5 groups, Jacobi 42.0 (45.2), 6 groups 31.6 (35.7); symmetric Gauss-Seidel, 4 groups 27.5
+// (33.7), 6 groups 49.1 (63.1); not taken: 3 groups, forward sweeps 16.8 (14.8), 4 groups, Jacobi 29.9
+// (28.1), 5 groups of 8 x 8 cases 28.4 (27.4).
+bool in_branches(const Solver& sv) {
+    const int ng = (int)sv.groups.size(), K = sv.ncolors;
+    const int each = sv.precond == 0 ? 2 : sv.precond == 1 ? 4 * K - 2 : 2 * K;
+    return ng >= 4 && ng * each >= 10 && sv.Ntot > ((size_t)1 << 16);
+}
+
+// w = A P^-1 v.  The groups of a batch have no part of z or w in common (nor of the sweeps' scratch).
+fr_status operate(Solver& sv, const double* q, const double* v, double* z, double* w, hipStream_t s) {
+    const int ng = (int)sv.groups.size();
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (in_branches(sv)) FR_HIP(hipStreamIsCapturing(s, &cap));
+    if (cap != hipStreamCaptureStatusActive) {
+        FR_TRY(precond_apply(sv, v, z, bdf_args(sv, q), sv.d_gi, GI_DONE, s));
+        return bdf_op(sv, q, z, w, GI_DONE, s);
+    }
+    const int nside = ng - 1 < SIDE_STREAMS ? ng - 1 : SIDE_STREAMS;
+    FR_HIP(hipEventRecord(sv.ev_fork, s));
+    for (int k = 0; k < nside; ++k) FR_HIP(hipStreamWaitEvent(sv.side[k], sv.ev_fork, 0));
+    for (int i = 0; i < ng; ++i) {
+        const int k = i % (nside + 1);
+        hipStream_t t = k < nside ? sv.side[k] : s;
+        FR_TRY(precond_apply(sv, v, z, bdf_args(sv, q), sv.d_gi, GI_DONE, t, i));
+        FR_TRY(bdf_op(sv, q, z, w, GI_DONE, t, i));
+    }
+    for (int k = 0; k < nside; ++k) {
+        FR_HIP(hipEventRecord(sv.ev_join[k], sv.side[k]));
+        FR_HIP(hipStreamWaitEvent(s, sv.ev_join[k], 0));
+    }
+    return FR_OK;
 }
 
 // the launches of one cycle (enqueued eagerly or under capture): an Arnoldi step
@@ -275,8 +312,7 @@ fr_status enqueue_arnoldi(Solver& sv, int m, int j, hipStream_t s) {
     double* V = sv.d_V;
     double* vj = V + (size_t)j * N;
     double* vn = vj + N;
-    FR_TRY(precond_apply(sv, vj, z, bdf_args(sv, q), sv.d_gi, GI_DONE, s));
-    FR_TRY(bdf_op(sv, q, z, w, GI_DONE, s));
+    FR_TRY(operate(sv, q, vj, z, w, s));
     // classical Gram-Schmidt: h = V^T w, w -= V h (and once more when re-orthogonalising); each pass
     // over the basis walks its items the other way from the pass before it
     const GsRef g1{sv.d_gs, sv.gs_stride, L.DT, L.SC, L.H1, j, 1};

@@ -243,6 +243,7 @@ inline const char* ctx_not_ready(const fr_ctx_s* c) {
 
 // A solver: one or more cases advanced together (fr_batch, or the one-case solver of a
 // context).  Owns the concatenated work vectors, blocks and device GMRES state.
+constexpr int SIDE_STREAMS = 2;
 struct Solver {
     std::vector<fr_ctx> cs;
     int n = 0;
@@ -297,6 +298,8 @@ struct Solver {
     size_t h_pin_doubles = 0;
     hipStream_t ws = nullptr;
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
+    hipStream_t side[SIDE_STREAMS] = {};   // branches of a captured Arnoldi step (several groups)
+    hipEvent_t ev_fork = nullptr, ev_join[SIDE_STREAMS] = {};
     hipEvent_t ev_seg[2] = {nullptr, nullptr};   // ends of the last two segments of a GMRES cycle
     bool use_graph = true;
     std::vector<void*> graph_exec;         // the cycle's segments, then its end (empty: not captured)
@@ -372,7 +375,7 @@ template <> fr_status launch_fused_p<2>(const Solver&, const Group&, int, const 
 template <> fr_status launch_fused_p<3>(const Solver&, const Group&, int, const KArgs&, const Tune&, hipStream_t);
 template <> fr_status launch_fused_p<4>(const Solver&, const Group&, int, const KArgs&, const Tune&, hipStream_t);
 // every group of the solver with its tuned shape
-fr_status solver_fused(const Solver& sv, int mode, const KArgs& a, hipStream_t s);
+fr_status solver_fused(const Solver& sv, int mode, const KArgs& a, hipStream_t s, int only = -1);   // only: that group alone
 // tile widths (elements per workgroup) a group may be launched with
 std::vector<int> fused_tile_widths(int p);
 
@@ -397,11 +400,11 @@ fr_status launch_block_apply(const Solver& sv, const double* r, double* z, const
 // restricted to the elements of one colour (color >= 0; -1: all):
 //   sub = false: z_e = D_e^-1 (r_e - b_e) (b may be null);  sub = true: z_e -= D_e^-1 r_e
 fr_status launch_block_apply_ex(const Solver& sv, const double* r, const double* b, double* z, int color, bool sub,
-                                const int* flags, int flag, hipStream_t s);
+                                const int* flags, int flag, hipStream_t s, int only = -1);
 // z = P^-1 r with the solver's preconditioner; the Gauss-Seidel sweeps apply the Newton
 // operator described by op (its v and out are set here)
 fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op, const int* flags, int flag,
-                        hipStream_t s);
+                        hipStream_t s, int only = -1);
 // Gram-Schmidt over a basis whose vectors are stored unnormalised, V_i = s_i v_i, with the scales
 // s_i, the raw dot products and the coefficients in each case's GMRES state (doubles, offsets
 // below; state of case c at gs + c * stride).  The vector w = A P^-1 v_j being orthogonalised

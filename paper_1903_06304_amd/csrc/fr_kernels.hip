@@ -272,8 +272,9 @@ fr_status launch_fused(const Solver& sv, const Group& gr, int mode, const KArgs&
     return FR_EUNSUPPORTED;
 }
 
-fr_status solver_fused(const Solver& sv, int mode, const KArgs& a, hipStream_t s) {
-    for (const Group& gr : sv.groups) FR_TRY(launch_fused(sv, gr, mode, a, gr.tune[mode], s));
+fr_status solver_fused(const Solver& sv, int mode, const KArgs& a, hipStream_t s, int only) {
+    for (const Group& gr : sv.groups)
+        if (only < 0 || &gr == &sv.groups[only]) FR_TRY(launch_fused(sv, gr, mode, a, gr.tune[mode], s));
     return FR_OK;
 }
 

@@ -718,9 +718,10 @@ static fr_status apply_p(const Solver& sv, const Group& gr, const ApplyArgs& x, 
 }
 
 fr_status launch_block_apply_ex(const Solver& sv, const double* r, const double* b, double* z, int color, bool sub,
-                                const int* flags, int flag, hipStream_t s) {
+                                const int* flags, int flag, hipStream_t s, int only) {
     const ApplyArgs x{r, b, z, color, sub ? 1 : 0, flags, flag};
     for (const Group& gr : sv.groups) {
+        if (only >= 0 && &gr != &sv.groups[only]) continue;
         switch (sv.inv_prec) {
             case FR_FP64: FR_TRY(apply_p<double>(sv, gr, x, s)); break;
             case FR_FP32: FR_TRY(apply_p<float>(sv, gr, x, s)); break;
@@ -745,8 +746,8 @@ fr_status launch_block_apply(const Solver& sv, const double* r, double* z, const
 // Forward block Gauss-Seidel (option value 2), P = D + L, is the forward sweep alone:
 // K - 1 operator applications over one colour each and one block-apply pass.
 fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op, const int* flags, int flag,
-                        hipStream_t s) {
-    if (sv.precond == 0) return launch_block_apply(sv, r, z, flags, flag, s);
+                        hipStream_t s, int only) {
+    if (sv.precond == 0) return launch_block_apply_ex(sv, r, nullptr, z, -1, false, flags, flag, s, only);
     FR_TRY(dalloc(&sv.d_gst, sv.Ntot));
     const int K = sv.ncolors;
     KArgs a = op;
@@ -760,15 +761,15 @@ fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op,
         if (k > 0) {
             a.csweep = 1 + k;
             a.cbelow = 1;
-            FR_TRY(solver_fused(sv, MODE_LIN, a, s));
+            FR_TRY(solver_fused(sv, MODE_LIN, a, s, only));
         }
-        FR_TRY(launch_block_apply_ex(sv, r, k > 0 ? sv.d_gst : nullptr, z, k, false, flags, flag, s));
+        FR_TRY(launch_block_apply_ex(sv, r, k > 0 ? sv.d_gst : nullptr, z, k, false, flags, flag, s, only));
     }
     for (int k = K - 2; k >= 0 && sv.precond == 1; --k) {
         a.csweep = 1 + k;
         a.cbelow = 0;
-        FR_TRY(solver_fused(sv, MODE_LIN, a, s));
-        FR_TRY(launch_block_apply_ex(sv, sv.d_gst, nullptr, z, k, true, flags, flag, s));
+        FR_TRY(solver_fused(sv, MODE_LIN, a, s, only));
+        FR_TRY(launch_block_apply_ex(sv, sv.d_gst, nullptr, z, k, true, flags, flag, s, only));
     }
     return FR_OK;
 }

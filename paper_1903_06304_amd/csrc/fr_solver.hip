@@ -209,6 +209,11 @@ void solver_free(Solver& sv) {
     if (sv.ev_out) (void)hipEventDestroy(sv.ev_out);
     for (hipEvent_t e : sv.ev_seg)
         if (e) (void)hipEventDestroy(e);
+    for (hipStream_t t : sv.side)
+        if (t) (void)hipStreamDestroy(t);
+    if (sv.ev_fork) (void)hipEventDestroy(sv.ev_fork);
+    for (hipEvent_t e : sv.ev_join)
+        if (e) (void)hipEventDestroy(e);
     sv = Solver();
 }
 
@@ -274,6 +279,13 @@ fr_status solver_ensure_step(Solver& sv, int m, int prec) {
         FR_HIP(hipEventCreateWithFlags(&sv.ev_in, hipEventDisableTiming));
         FR_HIP(hipEventCreateWithFlags(&sv.ev_out, hipEventDisableTiming));
         for (hipEvent_t& e : sv.ev_seg) FR_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        if (sv.groups.size() > 1) {
+            FR_HIP(hipEventCreateWithFlags(&sv.ev_fork, hipEventDisableTiming));
+            for (int k = 0; k < SIDE_STREAMS; ++k) {
+                FR_HIP(hipStreamCreateWithFlags(&sv.side[k], hipStreamNonBlocking));
+                FR_HIP(hipEventCreateWithFlags(&sv.ev_join[k], hipEventDisableTiming));
+            }
+        }
     }
     return FR_OK;
 }
