@@ -25,7 +25,10 @@ namespace {
 template <int P>
 struct Sz {
     static constexpr int n = P + 1, Np = n * n, NF = 4 * n, NT = (Np > NF ? Np : NF);
-    static constexpr int EPB = (128 / NT) > 0 ? 128 / NT : 1;
+    // one wave to a workgroup, whose barriers then wait for no other: 256 x 256 viscous elements at p = 3
+    // 99.6 us affine, 149 curved, 161 moving (102.3, 152, 170 at 128 lanes), 64 x 64 12.6 (14.0); at
+    // p = 4 two elements of 25 lanes would leave 14 of 64 idle
+    static constexpr int EPB = (P == 4 ? 128 : 64) / NT;
     static constexpr int threads = EPB * NT;
 };
 
