@@ -362,13 +362,6 @@ fr_status assemble_p(const Solver& sv, const Group& gr, const KArgs& a, hipStrea
 
 }  // namespace
 
-bool direct_assembly(const Solver& sv, const Group& gr) {
-    if (gr.bnd) return false;
-    for (int id : gr.ids)
-        if (sv.cs[id]->self_neighbour) return false;
-    return true;
-}
-
 fr_status launch_direct_assembly(const Solver& sv, const Group& gr, const KArgs& a, hipStream_t s) {
     if (!a.fpack || !a.spack || !a.out) { fr_set_error("block assembly without packs"); return FR_EINVAL; }
     switch (gr.p) {

@@ -171,6 +171,7 @@ struct Group {
     int p, visc, mov;
     bool aff0 = false;                       // all members affine when the solver was made
     bool bnd = false;                        // the members' meshes have boundary faces
+    bool self = false;                       // each member has an element that neighbours itself
     std::vector<int> ids;
     int* d_ids = nullptr;
     std::vector<std::pair<int, int*>> pfx;   // tile width (elements) -> device prefix
@@ -390,7 +391,7 @@ size_t prec_bytes(int prec);
 // preconditioner (fr_linalg.hip)
 fr_status launch_block_assembly(Solver& sv, const double* q, const KArgs& base, hipStream_t s);
 // the blocks of one group entry by entry from the packs (fr_assembly.hip), and whether it can
-bool direct_assembly(const Solver& sv, const Group& gr);
+inline bool direct_assembly(const Group& gr) { return !gr.bnd && !gr.self; }
 fr_status launch_direct_assembly(const Solver& sv, const Group& gr, const KArgs& a, hipStream_t s);
 fr_status launch_block_invert(Solver& sv, int prec, const int* flags, hipStream_t s);
 // explicit inverses of one group's element blocks, Gauss-Jordan in registers (fr_invert.hip)

@@ -622,7 +622,7 @@ fr_status launch_block_assembly(Solver& sv, const double* q, const KArgs& base, 
     KArgs a = base;
     a.q = q; a.v = nullptr; a.out = sv.d_blk; a.out2 = nullptr;
     for (const Group& gr : sv.groups) {
-        if (direct_assembly(sv, gr)) {
+        if (direct_assembly(gr)) {
             FR_TRY(launch_direct_assembly(sv, gr, a, s));
             continue;
         }

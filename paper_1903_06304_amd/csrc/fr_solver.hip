@@ -113,15 +113,16 @@ fr_status solver_init(Solver& sv, const fr_ctx* ctxs, int n) {
     FR_TRY(upload(&sv.d_chunk_case, chunk_case));
     FR_TRY(upload_items(sv));
     // launch groups: cases of one order, viscous and moving kind, with or without boundary
-    // faces, and (as the geometry stands when the solver is made) affine or not, so that a
-    // case runs the same kernel variant alone and in a batch; whether a group is affine is
-    // checked again at every launch
+    // faces and elements that neighbour themselves (whose blocks are assembled another way), and
+    // (as the geometry stands when the solver is made) affine or not, so that a case runs the
+    // same kernel variant alone and in a batch; whether a group is affine is checked again at
+    // every launch
     for (int c = 0; c < n; ++c) {
         const fr_ctx x = ctxs[c];
         Group* g = nullptr;
         for (Group& h : sv.groups)
             if (h.p == x->p && h.visc == (x->prm.viscous != 0) && h.mov == (x->prm.moving != 0) &&
-                h.aff0 == x->all_affine && h.bnd == (x->d_bc != nullptr))
+                h.aff0 == x->all_affine && h.bnd == (x->d_bc != nullptr) && h.self == x->self_neighbour)
                 g = &h;
         if (!g) {
             sv.groups.emplace_back();
@@ -131,6 +132,7 @@ fr_status solver_init(Solver& sv, const fr_ctx* ctxs, int n) {
             g->mov = x->prm.moving != 0;
             g->aff0 = x->all_affine;
             g->bnd = x->d_bc != nullptr;
+            g->self = x->self_neighbour;
         }
         g->ids.push_back(c);
         g->elems.push_back(x->E);

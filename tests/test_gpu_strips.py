@@ -1,0 +1,48 @@
+"""One-element-wide periodic strips: an element there neighbours itself, so its block holds
+derivatives through its own faces' far sides and is assembled column by column.
+
+* A batch of strips and ordinary cases of the same order and kind: every case's BDF step is bit for
+  bit the step it takes alone.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1903_06304_amd import inputs as I  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(p, nx, ny, curved, viscous, seed):
+    mesh = I.Mesh(nx, ny, p, (0.0, 2 * np.pi, 0.0, 2 * np.pi), I.map_curved(0.1) if curved else I.map_affine)
+    prm = I.Params(order=p, n_elem=mesh.E, mach_ref=0.2, reynolds=100.0, viscous=viscous, kappa=1.0)
+    rng = np.random.default_rng(seed)
+    q = I.uniform_flow(mesh, prm)
+    q += 0.02 * rng.uniform(-1.0, 1.0, q.shape)
+    return mesh, prm, torch.tensor(q, dtype=torch.float64, device="cuda")
+
+
+def _context(mesh, prm):
+    from paper_1903_06304_amd import lmfr
+    g = lmfr.Context(prm, *mesh.connectivity())
+    g.set_geometry(*mesh.nodes(0.0))
+    return g
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+@pytest.mark.parametrize("curved,viscous", [(False, True), (True, True), (False, False)])
+def test_batch_of_strips_and_ordinary_cases(p, curved, viscous):
+    from paper_1903_06304_amd import lmfr
+    made = [_case(p, nx, ny, curved, viscous, 10 * p + i) for i, (nx, ny) in enumerate([(4, 5), (1, 6), (3, 3), (5, 1)])]
+    ctxs = [_context(m, prm) for m, prm, _ in made]
+    batch = lmfr.Batch(ctxs)
+    dt = 0.01
+    kw = dict(tol_pseudo=1e-8, tol_res=1e-6, krylov=20, max_lin_it=200, max_newton=4, jac_lag=2, prec="fp64")
+    qb = [q.clone() for _, _, q in made]
+    batch.bdf2_step(qb, None, [lmfr.step_opts(dt, **kw)] * len(made))
+    for (m, _, q), g, xb in zip(made, ctxs, qb):
+        xs = q.clone()
+        g.bdf2_step(xs, None, dt, **kw)
+        assert torch.isfinite(xs).all() and not torch.equal(xs, q)
+        assert torch.equal(xb, xs), (m.nx, m.ny)
