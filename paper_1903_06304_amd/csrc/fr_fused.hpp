@@ -3,8 +3,8 @@
 //   R      the residual (paper Eq. cpr_ns with the moving-mesh terms),
 //   JVP    the exact forward tangent Jv (and optionally R),
 //   AOP    the Newton operator  Av = inv_dtau Gamma v + c_time M v - Jv,
-// and, from the linearisation packs of a state, that operator on tangents alone (k_lin) and one
-// seeded column of every element's diagonal block of it.
+// and, from the linearisation packs of a state, that operator on tangents alone (k_lin) and
+// seeded columns of every element's diagonal block of it.
 //
 // Work mapping: a workgroup tile holds EPB elements of one case; each element owns
 // NT = max(Np, 4n) lanes, lane `lt` acting as solution point lt (lt < Np) and as flux
@@ -973,6 +973,7 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
     // a Gauss-Seidel coupling pass: the element's own tangent is zero, and so are its gradient,
     // its traces and its time terms, which are therefore not formed
     constexpr bool ZO = CS && !BLK;
+    const int col = blockIdx.y;   // block mode: the seeded column
     const int el = threadIdx.x / NT, lt = threadIdx.x % NT;
     for (int t = threadIdx.x; t < n * n; t += blockDim.x) s_D[t] = op.D[t];
     if (threadIdx.x < n) {
@@ -998,8 +999,8 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
         const double* fpk = a.fpack + cd.fpoff;
         const double* spk = a.spack + cd.spoff;
         __syncthreads();
-        // ---- stage 1: own and neighbour tangents (block columns: the unit seed of column
-        // seed0 in the element itself, and in a neighbour only when it is the element)
+        // ---- stage 1: own and neighbour tangents (block columns: the unit seed of the column in
+        // the element itself, and in a neighbour only when it is the element)
         LaneGeo lg;
         int bck = 0;   // boundary kind of the lane's face (0: interior)
         if (act) {
@@ -1015,7 +1016,7 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
             double qo[4];
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv)
-                qo[vv] = BLK ? ((vv * Np + ls == a.seed0) ? 1.0 : 0.0) : (cs ? 0.0 : ldo(v + vv * EN, id));
+                qo[vv] = BLK ? ((vv * Np + ls == col) ? 1.0 : 0.0) : (cs ? 0.0 : ldo(v + vv * EN, id));
             // the lane's own face entry is loaded on its own: selecting it from pk4 by the lane's
             // face makes the compiler index a stack copy of pk4 (scratch memory)
             lane_geo_load<P, VISC, MOV>(g, E, e, lt, ldo(g.nbr, (unsigned)(e * 4 + (lt % NF) / n)), lg);
@@ -1035,7 +1036,7 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
 #pragma unroll
                     for (int vv = 0; vv < 4; ++vv)
                         s_n[NI(el, ff * 4 + vv, lt)] =
-                            BLK ? ((nb == e && vv * Np + lt == a.seed0) ? 1.0 : 0.0) : (take ? ldo(v + vv * EN, nid) : 0.0);
+                            BLK ? ((nb == e && vv * Np + lt == col) ? 1.0 : 0.0) : (take ? ldo(v + vv * EN, nid) : 0.0);
                 }
             }
         }
@@ -1271,9 +1272,9 @@ k_lin(GroupArgs ga, KArgs a, OpTab op) {
                 const double Rd = -(vol + geo[G_IJ] * cor);
                 const double ttv = (vv == 0) ? tt[0] : (vv == 1) ? tt[1] : (vv == 2) ? tt[2] : tt[3];
                 if (BLK) {
-                    // column seed0 of the element's block, column-major; the time terms are zero
+                    // the column of the element's block, column-major; the time terms are zero
                     // away from the seeded point, where ttv - Rd is exactly -Rd
-                    out[(size_t)a.seed0 * (4 * Np) + vv * Np + lt] = ttv - Rd;
+                    out[(size_t)col * (4 * Np) + vv * Np + lt] = ttv - Rd;
                 } else {
                     out[vv * EN + id] = ttv - Rd;
                 }
@@ -1602,11 +1603,12 @@ inline unsigned grid_of(int ntiles, int grid, int resident) {
     return (unsigned)g;
 }
 
+// cols: block columns of the launch (block mode)
 template <auto KERNEL, bool STAY = false>
-void start(const GroupArgs& ga, const KArgs& a, const OpTab& op, int grid, int threads, hipStream_t s) {
+void start(const GroupArgs& ga, const KArgs& a, const OpTab& op, int grid, int threads, hipStream_t s, int cols = 1) {
     int resident = 0;
     if constexpr (STAY) resident = resident_workgroups<KERNEL>(threads);
-    hipLaunchKernelGGL(KERNEL, dim3(grid_of(ga.ntiles, grid, resident)), dim3(threads), 0, s, ga, a, op);
+    hipLaunchKernelGGL(KERNEL, dim3(grid_of(ga.ntiles, grid, resident), cols), dim3(threads), 0, s, ga, a, op);
 }
 
 template <int P, bool VISC, bool MOV, int MODE, int LANES>
@@ -1632,6 +1634,10 @@ fr_status run(const Solver& sv, const Group& gr, const KArgs& a, int grid, int x
     const OpTab& op = sv.cs[gr.ids[0]]->op;
     if constexpr (MODE == MODE_LIN || MODE == MODE_LINBLK) {
         constexpr bool B = MODE == MODE_LINBLK;
+        // every column of the blocks in one launch: a column alone costs its launch and, on meshes that
+        // do not fill the chip, its latency.  Factor in FP32, p = 3, us, against a launch per column:
+        // 64-element strip 78 (506), 16 x 16 O-grid 100 (589), 64 x 64 435 (791), 256 x 128 3,006 (3,355)
+        constexpr int cols = B ? 4 * (P + 1) * (P + 1) : 1;
         if (!a.fpack || !a.spack || (!B && !a.v)) { fr_set_error("linearised operator without packs"); return FR_EINVAL; }
         bool aff = false;
         // a Gauss-Seidel coupling pass: the variants that take v on lower or higher colours only
@@ -1651,13 +1657,13 @@ fr_status run(const Solver& sv, const Group& gr, const KArgs& a, int grid, int x
                     if (cs)
                         start<k_lin<P, VISC, MOV, LANES, B, true, !B>, true>(ga, a, op, grid, SH::threads, s);
                     else
-                        start<k_lin<P, VISC, MOV, LANES, B, true>, true>(ga, a, op, grid, SH::threads, s);
+                        start<k_lin<P, VISC, MOV, LANES, B, true>, true>(ga, a, op, grid, SH::threads, s, cols);
                 }
             } else {
                 if (cs)
                     start<k_lin<P, VISC, MOV, LANES, B, false, !B>, true>(ga, a, op, grid, SH::threads, s);
                 else
-                    start<k_lin<P, VISC, MOV, LANES, B, false>, true>(ga, a, op, grid, SH::threads, s);
+                    start<k_lin<P, VISC, MOV, LANES, B, false>, true>(ga, a, op, grid, SH::threads, s, cols);
             }
         }
     } else {

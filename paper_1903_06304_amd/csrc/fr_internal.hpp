@@ -64,7 +64,7 @@ struct Geo {
 enum { BC_NONE = 0, BC_FARFIELD = 1, BC_SLIP = 2, BC_WALL = 3 };
 
 // R; exact JVP; Newton operator; R plus the linearisation packs; Newton operator from the packs
-// (tangent-only staging); one seeded block column from the packs.  The values are part of the
+// (tangent-only staging); seeded block columns from the packs.  The values are part of the
 // autotuner's cache keys.
 enum FrMode { MODE_R = 0, MODE_JVP = 1, MODE_AOP = 2, MODE_PREP = 4, MODE_LIN = 5, MODE_LINBLK = 6, NMODES = 7 };
 
@@ -135,7 +135,6 @@ struct KArgs {
     double* out2;         // R (JVP) or NULL
     double c_time, inv_dtau;   // time-term coefficients when cstep is NULL
     const CaseStep* cstep;     // per-case coefficients (solver steps) or NULL
-    int seed0;            // seeded column (MODE_LINBLK)
     const int* flags;     // per-case flags (gi layout) or NULL
     int flag;             // which flag skips a case
     double* fpack;        // linearisation packs (MODE_PREP writes, MODE_LIN reads)

@@ -626,13 +626,8 @@ fr_status launch_block_assembly(Solver& sv, const double* q, const KArgs& base, 
             FR_TRY(launch_direct_assembly(sv, gr, a, s));
             continue;
         }
-        // meshes with boundary faces or self-neighbours: one seeded column of every element's block
-        // per launch
-        const int nb = 4 * (gr.p + 1) * (gr.p + 1);
-        for (int col = 0; col < nb; ++col) {
-            a.seed0 = col;
-            FR_TRY(launch_fused(sv, gr, MODE_LINBLK, a, gr.tune[MODE_LINBLK], s));
-        }
+        // meshes with boundary faces or self-neighbours: the seeded columns of every element's block
+        FR_TRY(launch_fused(sv, gr, MODE_LINBLK, a, gr.tune[MODE_LINBLK], s));
     }
     return FR_OK;
 }

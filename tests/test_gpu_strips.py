@@ -3,12 +3,15 @@ derivatives through its own faces' far sides and is assembled column by column.
 
 * A batch of strips and ordinary cases of the same order and kind: every case's BDF step is bit for
   bit the step it takes alone.
+* The blocks against the oracle's, to the 1e-12 of the largest entry that the other blocks meet, from
+  one element (its own neighbour on all faces) to several tiles.
 """
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
+from oracle.oracle import Oracle  # noqa: E402
 from paper_1903_06304_amd import inputs as I  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -46,3 +49,19 @@ def test_batch_of_strips_and_ordinary_cases(p, curved, viscous):
         g.bdf2_step(xs, None, dt, **kw)
         assert torch.isfinite(xs).all() and not torch.equal(xs, q)
         assert torch.equal(xb, xs), (m.nx, m.ny)
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (1, 3), (23, 1)])
+@pytest.mark.parametrize("curved", [False, True])
+def test_blocks_of_a_strip(p, nx, ny, curved):
+    mesh, prm, q = _case(p, nx, ny, curved, True, p)
+    g = _context(mesh, prm)
+    g.set_option("keep_blocks", 1)
+    g.block_jacobi_factor(q, 20.0, 3.0)
+    B = g.get_blocks().cpu().numpy()
+    xg, vg = mesh.nodes(0.0)
+    Bo = Oracle(prm, mesh, xg, vg).blocks(q.cpu().numpy(), 20.0, 3.0)
+    err = np.max(np.abs(B - Bo)) / np.max(np.abs(Bo))
+    print(f"[strip] p={p} {nx}x{ny} curved={curved}: blocks {err:.1e}", flush=True)
+    assert err <= 1e-12
