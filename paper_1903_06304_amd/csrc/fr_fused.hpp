@@ -1711,16 +1711,40 @@ fr_status run(const Solver& sv, const Group& gr, const KArgs& a, int grid, int x
     return FR_OK;
 }
 
+// Default workgroup width.  One wave to a workgroup meets no barrier of another: viscous residual at
+// p = 3, 128 x 128 elements, 14.5 us affine and 23.6 curved (16.2 and 25.8 at 128 lanes), 256 x 256
+// 43.0 and 74.2 (43.7, 76.0); J v at p <= 3; Euler residuals are the same or lose up to 6%, the packs'
+// kernels within 1% in whole steps, and keep 128.  What a compute unit gets of a launch decides the rest:
+//  - residuals with six, eight or ten single waves on the fullest one run better in pairs, at p = 3 at
+//    5,750, 7,820 and 9,750 deforming elements 12.1, 14.0 and 18.6 us (12.7, 14.4, 19.5 at 64 lanes),
+//    at p = 2 at 12,190 15.7 (16.4); not eight on affine meshes (9.3, 9.2 at 64) or at p = 2 (curved
+//    11.4, 11.2), nor ten on both (10.9, 10.5); four: 9.9 (9.1), twelve: 23.9 (21.0);
+//  - at p = 4 two elements of 25 points leave 14 of 64 lanes idle, five leave 3 of 128, so that the
+//    derivatives take 128 (J v of 256 x 256 elements 117.7 us affine, 297 curved; 130.6 and 349 at 64)
+//    unless the fullest unit then has over 1.2 times the elements: J v, 1,430 affine elements, 10 for 6:
+//    8.3 us (10.0 at 128), 4,096 curved Euler, 20 for 16: 10.6 (11.8); below that 128 wins or is even
+//    (3,370 curved Euler, 15 for 14: 9.3, 10.3 at 64), and with an odd number of pairs too, two SIMDs
+//    being a wave short (2,900 curved Euler, 15 for 12: 9.2, 9.4).
+template <int P, bool VISC, int MODE>
+int default_lanes(const Solver& sv, const Group& gr) {
+    constexpr int CUS = 256, E1 = Shape<P, 64>::EPB, E2 = Shape<P, 128>::EPB;
+    auto per_cu = [&](int epb) { return (gr.ntiles(epb) + CUS - 1) / CUS; };
+    if constexpr (MODE == MODE_JVP || MODE == MODE_AOP) {
+        if (P < 4) return 64;
+        const int w = per_cu(E2);
+        return w % 2 == 0 && 10 * E2 * w > 12 * E1 * per_cu(E1) ? 64 : 128;
+    } else if constexpr (MODE == MODE_R && VISC && P < 4) {
+        const int w = P > 1 ? per_cu(E1) : 0;
+        const bool aff = group_affine(sv, gr);
+        return w == 6 || (w == 8 && P == 3 && !aff) || (w == 10 && (P == 3 || !aff)) ? 128 : 64;
+    }
+    return 128;
+}
+
 // workgroup widths built per mode: plain doubles 64/128/256 lanes, dual numbers 64/128
 template <int P, bool VISC, bool MOV, int MODE>
 fr_status run_lanes(const Solver& sv, const Group& gr, const KArgs& a, const Tune& t, hipStream_t s) {
-    // One wave to a workgroup meets no barrier of another: viscous residual at p = 3, 128 x 128 elements,
-    // 14.5 us affine and 23.6 curved (16.2 and 25.8 at 128 lanes), 256 x 256 43.0 and 74.2 (43.7, 76.0);
-    // Euler residuals are the same or lose up to 6%, the packs' kernels within 1% in whole steps, and
-    // keep 128.  At p = 4 two elements of 25 points leave 14 of 64 lanes idle, five leave 3 of 128: J v
-    // of 256 x 256 elements 117.7 us affine, 297 curved (130.6 and 349 at 64 lanes).
-    constexpr bool dual = MODE == MODE_JVP || MODE == MODE_AOP;
-    int lanes = t.lanes > 0 ? t.lanes : (P != 4 && (dual || (MODE == MODE_R && VISC)) ? 64 : 128);
+    int lanes = t.lanes > 0 ? t.lanes : default_lanes<P, VISC, MODE>(sv, gr);
     if (gr.bnd && lanes > 128) lanes = 128;   // the boundary-face variants are built for 64 and 128 lanes
     switch (lanes) {
         case 64: return run<P, VISC, MOV, MODE, 64>(sv, gr, a, t.grid, t.xcd, s);
