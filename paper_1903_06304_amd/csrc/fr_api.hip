@@ -462,7 +462,7 @@ extern "C" fr_status fr_block_jacobi_apply(fr_ctx c, const double* r, double* z,
     KArgs op{};   // the Newton operator of the last factor (its packs, time coefficients)
     op.c_time = sv.f_ct; op.inv_dtau = sv.f_idt;
     op.fpack = sv.d_fpack; op.spack = sv.d_spack;
-    return precond_apply(sv, r, z, op, nullptr, 0, (hipStream_t)stream);
+    return precond_apply(sv, r, z, op, 0, nullptr, 0, (hipStream_t)stream);
 }
 
 // blocks as assembled (column-major per element) -> caller's array row-major

@@ -278,12 +278,12 @@ bool in_branches(const Solver& sv) {
 }
 
 // w = A P^-1 v.  The groups of a batch have no part of z or w in common (nor of the sweeps' scratch).
-fr_status operate(Solver& sv, const double* q, const double* v, double* z, double* w, hipStream_t s) {
+fr_status operate(Solver& sv, int m, const double* q, const double* v, double* z, double* w, hipStream_t s) {
     const int ng = (int)sv.groups.size();
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (in_branches(sv)) FR_HIP(hipStreamIsCapturing(s, &cap));
     if (cap != hipStreamCaptureStatusActive) {
-        FR_TRY(precond_apply(sv, v, z, bdf_args(sv, q), sv.d_gi, GI_DONE, s));
+        FR_TRY(precond_apply(sv, v, z, bdf_args(sv, q), m, sv.d_gi, GI_DONE, s));
         return bdf_op(sv, q, z, w, GI_DONE, s);
     }
     const int nside = ng - 1 < SIDE_STREAMS ? ng - 1 : SIDE_STREAMS;
@@ -292,7 +292,7 @@ fr_status operate(Solver& sv, const double* q, const double* v, double* z, doubl
     for (int i = 0; i < ng; ++i) {
         const int k = i % (nside + 1);
         hipStream_t t = k < nside ? sv.side[k] : s;
-        FR_TRY(precond_apply(sv, v, z, bdf_args(sv, q), sv.d_gi, GI_DONE, t, i));
+        FR_TRY(precond_apply(sv, v, z, bdf_args(sv, q), m, sv.d_gi, GI_DONE, t, i));
         FR_TRY(bdf_op(sv, q, z, w, GI_DONE, t, i));
     }
     for (int k = 0; k < nside; ++k) {
@@ -312,7 +312,7 @@ fr_status enqueue_arnoldi(Solver& sv, int m, int j, hipStream_t s) {
     double* V = sv.d_V;
     double* vj = V + (size_t)j * N;
     double* vn = vj + N;
-    FR_TRY(operate(sv, q, vj, z, w, s));
+    FR_TRY(operate(sv, m, q, vj, z, w, s));
     // classical Gram-Schmidt: h = V^T w, w -= V h (and once more when re-orthogonalising); each pass
     // over the basis walks its items the other way from the pass before it
     const GsRef g1{sv.d_gs, sv.gs_stride, L.DT, L.SC, L.H1, j, 1};
@@ -382,7 +382,7 @@ fr_status enqueue_end(Solver& sv, int m, hipStream_t s) {
     hipLaunchKernelGGL(k_backsub, dim3(sv.n), dim3(256), 0, s, k, m);
     FR_HIP(hipGetLastError());
     FR_TRY(la_combine(sv, sv.d_V, N, sv.d_gs, sv.gs_stride, L.Y, w, sv.d_gi, GI_IDLE, s));
-    FR_TRY(precond_apply(sv, w, z, bdf_args(sv, q), sv.d_gi, GI_IDLE, s));
+    FR_TRY(precond_apply(sv, w, z, bdf_args(sv, q), m, sv.d_gi, GI_IDLE, s));
     hipLaunchKernelGGL(k_add, dim3(vgrid(sv)), dim3(256), 0, s, vec(sv, GI_IDLE), z, x);
     FR_HIP(hipGetLastError());
     FR_TRY(bdf_op(sv, q, x, w, GI_IDLE, s));

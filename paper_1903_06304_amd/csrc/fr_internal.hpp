@@ -396,14 +396,14 @@ fr_status launch_block_invert(Solver& sv, int prec, const int* flags, hipStream_
 // explicit inverses of one group's element blocks, Gauss-Jordan in registers (fr_invert.hip)
 fr_status launch_block_invert_group(Solver& sv, int p, const GroupArgs& ga, int prec, const int* flags,
                                     hipStream_t s);
-fr_status launch_block_apply(const Solver& sv, const double* r, double* z, const int* flags, int flag, hipStream_t s);
-// restricted to the elements of one colour (color >= 0; -1: all):
+// block apply over the elements of one colour (color >= 0; -1: all):
 //   sub = false: z_e = D_e^-1 (r_e - b_e) (b may be null);  sub = true: z_e -= D_e^-1 r_e
-fr_status launch_block_apply_ex(const Solver& sv, const double* r, const double* b, double* z, int color, bool sub,
-                                const int* flags, int flag, hipStream_t s, int only = -1);
+// m: restart length of the GMRES it belongs to (0: none)
+fr_status launch_block_apply(const Solver& sv, const double* r, const double* b, double* z, int color, bool sub,
+                             int m, const int* flags, int flag, hipStream_t s, int only = -1);
 // z = P^-1 r with the solver's preconditioner; the Gauss-Seidel sweeps apply the Newton
 // operator described by op (its v and out are set here)
-fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op, const int* flags, int flag,
+fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op, int m, const int* flags, int flag,
                         hipStream_t s, int only = -1);
 // Gram-Schmidt over a basis whose vectors are stored unnormalised, V_i = s_i v_i, with the scales
 // s_i, the raw dot products and the coefficients in each case's GMRES state (doubles, offsets

@@ -668,12 +668,13 @@ std::vector<int> block_apply_widths(int p) {
 // size of the last-level cache
 constexpr size_t LLC_BYTES = (size_t)256 << 20;
 // Blocks and Krylov basis are each read once or twice an iteration; together beyond the cache they
-// only evict each other and the smaller vectors and packs, so the blocks are then streamed.  Whole
+// only evict each other and the smaller vectors and packs, so the blocks are then streamed.  m: restart
+// length of the solve the apply belongs to (0: none, no basis).  Whole
 // BDF2 steps, ms, streamed (plain): p = 3 FP32, blocks and basis 268 + 260 MB 19.2 (20.5); BF16
 // 134 + 260 MB 16.6 (16.9); FP32 151 + 146 MB 13.0 (13.1); p = 4 FP64 328 + 101 MB 18.9 (20.8); and
 // below the line 184 + 57 MB 13.7 (13.1), 134 + 65 MB 9.8 (9.7).
-static bool stream_blocks(const Solver& sv, size_t entry) {
-    const size_t basis = sv.d_V ? (size_t)(sv.kry_m + 1) * sv.Ntot * sizeof(double) : 0;
+static bool stream_blocks(const Solver& sv, size_t entry, int m) {
+    const size_t basis = m > 0 ? (size_t)(m + 1) * sv.Ntot * sizeof(double) : 0;
     return sv.Btot * entry + basis > LLC_BYTES;
 }
 
@@ -683,6 +684,7 @@ struct ApplyArgs {
     double* z;
     int color;
     int sub;
+    int m;
     const int* flags;
     int flag;
 };
@@ -693,7 +695,7 @@ static fr_status apply_as(const Solver& sv, const Group& gr, const ApplyArgs& x,
     GroupArgs ga = group_args(sv, gr, SH::EPB, x.color);
     if (!ga.pfx) { fr_set_error("tile prefix missing"); return FR_EINVAL; }
     if (ga.ntiles == 0) return FR_OK;
-    auto kernel = stream_blocks(sv, sizeof(Tin)) ? k_block_apply<Tin, NB, true> : k_block_apply<Tin, NB, false>;
+    auto kernel = stream_blocks(sv, sizeof(Tin), x.m) ? k_block_apply<Tin, NB, true> : k_block_apply<Tin, NB, false>;
     hipLaunchKernelGGL(kernel, dim3(ga.ntiles), dim3(SH::threads), 0, s, ga, (const Tin*)sv.d_inv, x.r, x.b, x.z, x.sub,
                        x.flags, x.flag, sv.inv_colour ? 1 : 0);
     FR_HIP(hipGetLastError());
@@ -712,9 +714,9 @@ static fr_status apply_p(const Solver& sv, const Group& gr, const ApplyArgs& x, 
     return FR_EUNSUPPORTED;
 }
 
-fr_status launch_block_apply_ex(const Solver& sv, const double* r, const double* b, double* z, int color, bool sub,
-                                const int* flags, int flag, hipStream_t s, int only) {
-    const ApplyArgs x{r, b, z, color, sub ? 1 : 0, flags, flag};
+fr_status launch_block_apply(const Solver& sv, const double* r, const double* b, double* z, int color, bool sub,
+                             int m, const int* flags, int flag, hipStream_t s, int only) {
+    const ApplyArgs x{r, b, z, color, sub ? 1 : 0, m, flags, flag};
     for (const Group& gr : sv.groups) {
         if (only >= 0 && &gr != &sv.groups[only]) continue;
         switch (sv.inv_prec) {
@@ -727,10 +729,6 @@ fr_status launch_block_apply_ex(const Solver& sv, const double* r, const double*
     return FR_OK;
 }
 
-fr_status launch_block_apply(const Solver& sv, const double* r, double* z, const int* flags, int flag, hipStream_t s) {
-    return launch_block_apply_ex(sv, r, nullptr, z, -1, false, flags, flag, s);
-}
-
 // Symmetric block Gauss-Seidel over the elements in colour order, P = (D + L) D^-1 (D + U)
 // with L / U the couplings of the Newton operator A to elements of lower / higher colour
 // (elements of one colour never share a face, so A restricted to a colour is D):
@@ -740,9 +738,9 @@ fr_status launch_block_apply(const Solver& sv, const double* r, double* z, const
 // 2 (K - 1) operator applications and about 1.5 block-apply passes per application.
 // Forward block Gauss-Seidel (option value 2), P = D + L, is the forward sweep alone:
 // K - 1 operator applications over one colour each and one block-apply pass.
-fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op, const int* flags, int flag,
+fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op, int m, const int* flags, int flag,
                         hipStream_t s, int only) {
-    if (sv.precond == 0) return launch_block_apply_ex(sv, r, nullptr, z, -1, false, flags, flag, s, only);
+    if (sv.precond == 0) return launch_block_apply(sv, r, nullptr, z, -1, false, m, flags, flag, s, only);
     FR_TRY(dalloc(&sv.d_gst, sv.Ntot));
     const int K = sv.ncolors;
     KArgs a = op;
@@ -758,13 +756,13 @@ fr_status precond_apply(Solver& sv, const double* r, double* z, const KArgs& op,
             a.cbelow = 1;
             FR_TRY(solver_fused(sv, MODE_LIN, a, s, only));
         }
-        FR_TRY(launch_block_apply_ex(sv, r, k > 0 ? sv.d_gst : nullptr, z, k, false, flags, flag, s, only));
+        FR_TRY(launch_block_apply(sv, r, k > 0 ? sv.d_gst : nullptr, z, k, false, m, flags, flag, s, only));
     }
     for (int k = K - 2; k >= 0 && sv.precond == 1; --k) {
         a.csweep = 1 + k;
         a.cbelow = 0;
         FR_TRY(solver_fused(sv, MODE_LIN, a, s, only));
-        FR_TRY(launch_block_apply_ex(sv, sv.d_gst, nullptr, z, k, true, flags, flag, s, only));
+        FR_TRY(launch_block_apply(sv, sv.d_gst, nullptr, z, k, true, m, flags, flag, s, only));
     }
     return FR_OK;
 }
