@@ -176,12 +176,14 @@ k_block_invert(GroupArgs ga, const double* __restrict__ blk, TO* __restrict__ in
             key = key > key1 ? key : key1;
         }
         key = wave_umax(key);
-        // no usable pivot: the block is singular (or not finite); the steps run on with row 0 so
-        // that the loop stays straight-line code, and the block is discarded
+        // no usable pivot: the block is singular, or not finite in TC (an infinity or a NaN anywhere
+        // spreads over the unused rows of its column, or is itself the largest there); the steps run
+        // on, with row 0 where there is none, so that the loop stays straight-line code, and the
+        // block is discarded
         const int p = key ? 127 - (int)(key & 127u) : 0;
         TC pv = lane_value(x0, p & 63);
         if (NB > 64) pv = p < 64 ? pv : lane_value(x1, p & 63);
-        bad = bad || !key || !(fabs(pv) > TC(0));
+        bad = bad || !key || !(fabs(pv) > TC(0) && fabs(pv) < TC(INFINITY));
         u0 = u0 || lane == p;
         u1 = u1 || lane + 64 == p;
         const int pq = (p >> 1) % TR, pa = 2 * ((p >> 1) / TR) + (p & 1);
