@@ -3,7 +3,7 @@
 // block in registers.
 //
 // A group of TR x CT threads holds an element, RPT x CPT entries each (Map): one wave up to
-// 64 x 64, four for 100 x 100.  Thread (tr, tc) holds the rows 2 tr + 2 TR i, + 1 (pairs, so that
+// 64 x 64 (more for a few blocks), four for 100 x 100.  Thread (tr, tc) holds the rows 2 tr + 2 TR i, + 1 (pairs, so that
 // loads and LDS reads are 16 bytes wide and consecutive) and the columns tc + CT b.  Step k, with
 // the column of step k at register column 0:
 //   1. its owners put the column into LDS; every wave reads it, one or two rows a lane, and takes
@@ -29,7 +29,6 @@
 //     nb            16           36           64           100
 //     FP64     0.12 (0.45)  0.59 (1.93)  2.28 (3.41)  7.94 (20.1)
 //     FP32     0.09 (0.27)  0.40 (1.12)  1.12 (1.63)  4.73 (8.34)
-// 256 FP64 blocks of 64, one wave a compute unit: 53 us (44), the latency of the 64 steps.
 #include "fr_internal.hpp"
 #include <type_traits>
 
@@ -80,12 +79,16 @@ __device__ __forceinline__ int case_of_tile(const GroupArgs& ga, int t) {
 
 // threads and entries of one element: TR x CT threads in NW waves, RPT x CPT entries each.  One
 // wave needs no barrier and shares a step's fixed work over most entries; 100 x 100 takes four for
-// its registers (two waves of 4 x 20 entries: 8.3 ms for 7.9 at FP64, 6.2 for 4.7 at FP32).
-template <int NB> struct Map;
-template <> struct Map<16> { static constexpr int TR = 8, CT = 8, NW = 1, OCC = 8; };
-template <> struct Map<36> { static constexpr int TR = 9, CT = 6, NW = 1, OCC = 4; };
-template <> struct Map<64> { static constexpr int TR = 8, CT = 8, NW = 1, OCC = 2; };
-template <> struct Map<100> { static constexpr int TR = 25, CT = 10, NW = 4, OCC = 3; };
+// its registers (two waves of 4 x 20 entries: 8.3 ms for 7.9 at FP64, 6.2 for 4.7 at FP32), 64 x 64
+// two or four where the blocks are too few to fill the chip (waves_64).  The arithmetic on an entry
+// is the same in all.
+template <int NB, int NW> struct Map;
+template <> struct Map<16, 1> { static constexpr int TR = 8, CT = 8, OCC = 8; };
+template <> struct Map<36, 1> { static constexpr int TR = 9, CT = 6, OCC = 4; };
+template <> struct Map<64, 1> { static constexpr int TR = 8, CT = 8, OCC = 2; };
+template <> struct Map<64, 2> { static constexpr int TR = 16, CT = 8, OCC = 4; };
+template <> struct Map<64, 4> { static constexpr int TR = 16, CT = 16, OCC = 4; };
+template <> struct Map<100, 4> { static constexpr int TR = 25, CT = 10, OCC = 3; };
 
 // what the LDS traffic of an element needs between its threads: a barrier, or only order within
 // its one wave
@@ -107,12 +110,12 @@ __device__ __forceinline__ unsigned pivot_key(double x, int row) {
 }
 __device__ __forceinline__ unsigned pivot_key(float x, int row) { return pivot_key(__float_as_uint(x), 0x7f800000u, row); }
 
-template <int NB, class TC, class TO>
-__global__ void __launch_bounds__(64 * Map<NB>::NW, Map<NB>::OCC)
+template <int NB, int NW, class TC, class TO>
+__global__ void __launch_bounds__(64 * NW, (Map<NB, NW>::OCC))
 k_block_invert(GroupArgs ga, const double* __restrict__ blk, TO* __restrict__ inv, int* __restrict__ gi,
                const int* __restrict__ flags, int cl) {
-    using M = Map<NB>;
-    constexpr int TR = M::TR, CT = M::CT, NW = M::NW, RPT = NB / TR, CPT = NB / CT, NTH = 64 * NW;
+    using M = Map<NB, NW>;
+    constexpr int TR = M::TR, CT = M::CT, RPT = NB / TR, CPT = NB / CT, NTH = 64 * NW;
     static_assert(RPT * TR == NB && CPT * CT == NB && RPT % 2 == 0 && CPT % 2 == 0, "whole pairs");
     static_assert(NB <= 127 && TR * CT <= NTH, "row numbers in 7 bits");
     typedef TC V2 __attribute__((ext_vector_type(2)));
@@ -260,21 +263,37 @@ k_block_invert(GroupArgs ga, const double* __restrict__ blk, TO* __restrict__ in
     }
 }
 
-template <int NB, class TC, class TO>
+template <int NB, int NW, class TC, class TO>
 fr_status launch_nb(Solver& sv, const GroupArgs& ga, const int* flags, hipStream_t s) {
-    hipLaunchKernelGGL((k_block_invert<NB, TC, TO>), dim3(ga.ntiles), dim3(64 * Map<NB>::NW), 0, s, ga, sv.d_blk,
+    hipLaunchKernelGGL((k_block_invert<NB, NW, TC, TO>), dim3(ga.ntiles), dim3(64 * NW), 0, s, ga, sv.d_blk,
                        (TO*)sv.d_inv, sv.d_gi, flags, sv.inv_colour ? 1 : 0);
     FR_HIP(hipGetLastError());
     return FR_OK;
 }
 
+// Waves of a 64 x 64 block.  A few blocks take the latency of their 64 steps, which more waves shorten
+// until the chip holds more than it can run of them.  us, one / two / four waves (panels in LDS, above):
+//     blocks       64               256              512              1,024            2,048
+//     FP64  49.8 39.9 38.2   51.2 42.0 40.7   58.3 53.8 50.6   76.6 60.2 67.2   85.6 88.4 104
+//           (41.0)           (42.4)           (49.2)           (70.5)           (126)
+//     FP32  44.7 35.9 33.3   45.6 37.0 34.9   49.5 44.0 40.1   59.4 48.5 53.2   73.8 65.9 78.5
+//           (32.5)           (33.4)           (38.5)           (49.9)           (71.6)
+template <class TC> int waves_64(int blocks) {
+    return blocks <= 512 ? 4 : blocks <= (sizeof(TC) == 8 ? 1024 : 2048) ? 2 : 1;
+}
+
 template <class TC, class TO>
 fr_status launch_p(Solver& sv, int p, const GroupArgs& ga, const int* flags, hipStream_t s) {
     switch (p) {
-        case 1: return launch_nb<16, TC, TO>(sv, ga, flags, s);
-        case 2: return launch_nb<36, TC, TO>(sv, ga, flags, s);
-        case 3: return launch_nb<64, TC, TO>(sv, ga, flags, s);
-        case 4: return launch_nb<100, TC, TO>(sv, ga, flags, s);
+        case 1: return launch_nb<16, 1, TC, TO>(sv, ga, flags, s);
+        case 2: return launch_nb<36, 1, TC, TO>(sv, ga, flags, s);
+        case 3:
+            switch (waves_64<TC>(ga.ntiles)) {
+                case 4: return launch_nb<64, 4, TC, TO>(sv, ga, flags, s);
+                case 2: return launch_nb<64, 2, TC, TO>(sv, ga, flags, s);
+            }
+            return launch_nb<64, 1, TC, TO>(sv, ga, flags, s);
+        case 4: return launch_nb<100, 4, TC, TO>(sv, ga, flags, s);
     }
     fr_set_error("order outside 1..4");
     return FR_EUNSUPPORTED;
