@@ -28,22 +28,30 @@ __device__ __forceinline__ int tile_member(const GroupArgs& ga, int t) {
 }
 
 // z_e = Ainv_e r_e for the elements of one group; state layout [4][E][Np] per case, block row/col
-// index v*Np + s.  Four parts of an element's threads share its columns, part q takes the columns
-// 4 u + q: a load of the element's threads covers four columns, consecutive in memory (a column alone
-// is 72 to 800 bytes, no whole lines), and a thread's chain of loads is a quarter as long, which is
-// the whole time where the elements do not fill the chip.  A thread holds R consecutive rows, one
-// load of 16 bytes (8 in BF16) each column; FP64 accumulation over a part's columns in ascending
-// order, the parts added in order.
+// index v*Np + s.  The columns make four sums, part q those of the columns 4 u + q in ascending order,
+// added in order.  Four parts of an element's threads take one each: a load of the element's threads
+// covers four columns, consecutive in memory (a column alone is 72 to 800 bytes, no whole lines), and a
+// thread's chain of loads is a quarter as long, which is the whole time where the elements do not fill
+// the chip.  A thread holds R consecutive rows, one load of 16 bytes (8 in BF16) each column; FP64
+// accumulation.
 //
 // Bound by the read of the blocks.  STREAM: with loads that leave no line in the last-level cache
-// (stream_blocks).  One application, us, against one part to an element with ordinary loads:
+// (stream_blocks).  One application, us, against one sum and part to an element with ordinary loads:
 //     elements         256            2,048          65,536
 //     p = 2 BF16   3.6 (4.7)      4.0 (4.8)       30.7 (33.4)
 //     p = 3 BF16   3.5 (5.3)      4.6 (6.6)        108 (117)
 //     p = 3 FP32   3.4 (5.0)      5.7 (7.4)        195 (220)
-//     p = 3 FP64   3.3 (4.5)     12.7 (12.4)       362 (391)
-//     p = 4 FP64   4.7 (5.6)     26.1 (24.6)       891 (995; 5.9 TB/s of blocks, a plain read 6.1)
+//     p = 3 FP64   3.3 (4.5)     11.5 (11.5)       347 (388)
+//     p = 4 FP64   4.7 (5.6)     24.8 (24.6)       891 (995; 5.9 TB/s of blocks, a plain read 6.1)
+// FULL: FP64 blocks that do fill the chip (apply_as), one row a thread and loads of 8 bytes; at
+// p = 4 in one part, whose threads keep the four sums.  us, against two rows and four parts:
+//     p = 3   8,192 plain 40.1 (41.3)   65,536 streamed 348 (359)    1,024 plain 6.1 (5.1)
+//     p = 4   3,000 plain 34.7 (36.4)   4,096 streamed 54.0 (52.0)   512 plain 7.9 (7.4)
 template <class Tin, int R> struct RowPack;
+template <> struct RowPack<double, 1> {
+    typedef double V;
+    __device__ static void expand(V v, double* x) { x[0] = v; }
+};
 template <> struct RowPack<double, 2> {
     typedef double V __attribute__((ext_vector_type(2)));
     __device__ static void expand(V v, double* x) { x[0] = v.x; x[1] = v.y; }
@@ -63,23 +71,25 @@ template <> struct RowPack<uint16_t, 4> {
 };
 
 // a workgroup: one element, or as many as 256 threads hold where an element's are fewer than a wave
-// or fill their last one badly (p <= 2)
-template <class Tin, int NB>
+// or fill their last one badly (p <= 2; FP32 at p = 1 half of them: 32,768 elements 7.5 us, 8.1 with 256)
+template <class Tin, int NB, bool FULL = false>
 struct ApplyShape {
-    static constexpr int R = sizeof(Tin) == 8 ? 2 : 4, PARTS = 4, TPE = NB / R, TPT = TPE * PARTS;
-    static constexpr int EPB = NB <= 36 ? 256 / TPT : 1, threads = EPB * TPT;
-    static_assert(NB % R == 0 && NB % PARTS == 0 && threads <= 256, "whole packs, whole quarters");
+    static constexpr int R = FULL ? 1 : sizeof(Tin) == 8 ? 2 : 4, SUMS = 4, PARTS = FULL && NB == 100 ? 1 : 4;
+    static constexpr int TPE = NB / R, TPT = TPE * PARTS, HOLD = NB == 16 && sizeof(Tin) == 4 ? 128 : 256;
+    static constexpr int EPB = NB <= 36 || PARTS == 1 ? HOLD / TPT : 1, threads = EPB * TPT;
+    static_assert(NB % R == 0 && NB % SUMS == 0 && threads <= 256, "whole packs, whole quarters");
 };
 
 // z_e = D_e^-1 r_e for every element, or, for the Gauss-Seidel sweeps, for the elements of
 // one colour only (tiles over that colour, ga.csel): z_e = D_e^-1 (r_e - b_e) (b may be null),
 // or z_e -= D_e^-1 r_e (sub).
-template <class Tin, int NB, bool STREAM>
+template <class Tin, int NB, bool STREAM, bool FULL>
 __global__ void __launch_bounds__(256)
 k_block_apply(GroupArgs ga, const Tin* __restrict__ inv, const double* __restrict__ r, const double* __restrict__ b,
               double* __restrict__ z, int sub, const int* __restrict__ flags, int flag, int cl) {
-    using SH = ApplyShape<Tin, NB>;
-    constexpr int Np = NB / 4, R = SH::R, TPE = SH::TPE, EPB = SH::EPB, S = SH::PARTS, Q = NB / S;
+    using SH = ApplyShape<Tin, NB, FULL>;
+    constexpr int Np = NB / 4, R = SH::R, TPE = SH::TPE, EPB = SH::EPB, S = SH::SUMS, Q = NB / S;
+    constexpr int PARTS = SH::PARTS, M = S / PARTS;   // M: sums of a thread, those of q = part + PARTS j
     using P = RowPack<Tin, R>;
     __shared__ double rs[EPB][NB + 1];
     __shared__ double sh[EPB][S][NB];
@@ -89,7 +99,7 @@ k_block_apply(GroupArgs ga, const Tin* __restrict__ inv, const double* __restric
     const int cid = ga.ids[lo];
     if (flags && flags[cid * GI_STRIDE + flag]) return;
     const CaseDev& cd = ga.cases[cid];
-    const int el = threadIdx.x / SH::TPT, part = threadIdx.x / TPE % S, r0 = (threadIdx.x % TPE) * R;
+    const int el = threadIdx.x / SH::TPT, part = threadIdx.x / TPE % PARTS, r0 = (threadIdx.x % TPE) * R;
     // one colour of the Gauss-Seidel sweeps (ga.csel set): the tiles run over the member's
     // elements of that colour, taken from its colour-sorted element list.  slot: the
     // element's block in the stored inverse (its position in that list in the colour layout)
@@ -104,43 +114,54 @@ k_block_apply(GroupArgs ga, const Tin* __restrict__ inv, const double* __restric
     if (!cl) slot = e;
     const size_t EN = (size_t)cd.E * Np;
     auto gid = [&](int row) { return cd.off + (row / Np) * EN + (size_t)e * Np + (row % Np); };
-    if (act && part < R) {
+    // a row to each part, as far as there are
+    static_assert(R <= PARTS, "a part stages and writes one row");
+    const bool has_row = act && part < R;
+    if (has_row) {
         const size_t g = gid(r0 + part);
         rs[el][r0 + part] = b ? r[g] - b[g] : r[g];
     }
     __syncthreads();
     const Tin* A = inv + cd.boff + (size_t)slot * NB * NB + r0;
-    double acc[R];
+    double acc[M][R];
 #pragma unroll
-    for (int k = 0; k < R; ++k) acc[k] = 0.0;
-    // the part's columns in batches whose loads are all issued before any is used
-    constexpr int NBAT = (Q + 15) / 16, U = (Q + NBAT - 1) / NBAT;
+    for (int j = 0; j < M; ++j)
+#pragma unroll
+        for (int k = 0; k < R; ++k) acc[j][k] = 0.0;
+    // a thread's columns in batches whose loads are all issued before any is used
+    constexpr int NBAT = (Q * M + 15) / 16, U = (Q + NBAT - 1) / NBAT;
     if (act) {
 #pragma unroll
         for (int u0 = 0; u0 < Q; u0 += U) {
-            typename P::V raw[U];
+            typename P::V raw[U][M];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (u0 + u < Q) {
-                    const auto* x = reinterpret_cast<const typename P::V*>(A + (size_t)(S * (u0 + u) + part) * NB);
-                    raw[u] = STREAM ? __builtin_nontemporal_load(x) : *x;
-                }
+#pragma unroll
+                for (int j = 0; j < M; ++j)
+                    if (u0 + u < Q) {
+                        const auto* x =
+                            reinterpret_cast<const typename P::V*>(A + (size_t)(S * (u0 + u) + part + PARTS * j) * NB);
+                        raw[u][j] = STREAM ? __builtin_nontemporal_load(x) : *x;
+                    }
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (u0 + u < Q) {
-                    double x[R];
-                    P::expand(raw[u], x);
-                    const double rc = rs[el][S * (u0 + u) + part];
 #pragma unroll
-                    for (int k = 0; k < R; ++k) acc[k] += x[k] * rc;
-                }
+                for (int j = 0; j < M; ++j)
+                    if (u0 + u < Q) {
+                        double x[R];
+                        P::expand(raw[u][j], x);
+                        const double rc = rs[el][S * (u0 + u) + part + PARTS * j];
+#pragma unroll
+                        for (int k = 0; k < R; ++k) acc[j][k] += x[k] * rc;
+                    }
         }
     }
 #pragma unroll
-    for (int k = 0; k < R; ++k) sh[el][part][r0 + k] = acc[k];
+    for (int j = 0; j < M; ++j)
+#pragma unroll
+        for (int k = 0; k < R; ++k) sh[el][part + PARTS * j][r0 + k] = acc[j][k];
     __syncthreads();
-    // R of the parts add and write a row each
-    if (!act || part >= R) return;
+    if (!has_row) return;
     const int row = r0 + part;
     const double v = ((sh[el][0][row] + sh[el][1][row]) + sh[el][2][row]) + sh[el][3][row];
     const size_t g = gid(row);
@@ -654,8 +675,14 @@ fr_status launch_block_invert(Solver& sv, int prec, const int* flags, hipStream_
     return FR_OK;
 }
 
+// orders whose FP64 blocks have a form for launches that fill the chip
+constexpr bool full_order(int nb) { return nb >= 64; }
+
 // tile widths (elements per workgroup) of the block apply
-template <int NB> static std::vector<int> apply_widths() { return {ApplyShape<double, NB>::EPB, ApplyShape<float, NB>::EPB}; }
+template <int NB> static std::vector<int> apply_widths() {
+    return {ApplyShape<double, NB>::EPB, ApplyShape<float, NB>::EPB, ApplyShape<uint16_t, NB>::EPB,
+            ApplyShape<double, NB, full_order(NB)>::EPB};
+}
 std::vector<int> block_apply_widths(int p) {
     switch (p) {
         case 1: return apply_widths<16>();
@@ -689,17 +716,29 @@ struct ApplyArgs {
     int flag;
 };
 
-template <class Tin, int NB>
-static fr_status apply_as(const Solver& sv, const Group& gr, const ApplyArgs& x, hipStream_t s) {
-    using SH = ApplyShape<Tin, NB>;
-    GroupArgs ga = group_args(sv, gr, SH::EPB, x.color);
+template <class Tin, int NB, bool FULL>
+static fr_status apply_form(const Solver& sv, const GroupArgs& ga, bool stream, const ApplyArgs& x, hipStream_t s) {
     if (!ga.pfx) { fr_set_error("tile prefix missing"); return FR_EINVAL; }
     if (ga.ntiles == 0) return FR_OK;
-    auto kernel = stream_blocks(sv, sizeof(Tin), x.m) ? k_block_apply<Tin, NB, true> : k_block_apply<Tin, NB, false>;
-    hipLaunchKernelGGL(kernel, dim3(ga.ntiles), dim3(SH::threads), 0, s, ga, (const Tin*)sv.d_inv, x.r, x.b, x.z, x.sub,
-                       x.flags, x.flag, sv.inv_colour ? 1 : 0);
+    auto kernel = stream ? k_block_apply<Tin, NB, true, FULL> : k_block_apply<Tin, NB, false, FULL>;
+    hipLaunchKernelGGL(kernel, dim3(ga.ntiles), dim3(ApplyShape<Tin, NB, FULL>::threads), 0, s, ga,
+                       (const Tin*)sv.d_inv, x.r, x.b, x.z, x.sub, x.flags, x.flag, sv.inv_colour ? 1 : 0);
     FR_HIP(hipGetLastError());
     return FR_OK;
+}
+
+template <class Tin, int NB>
+static fr_status apply_as(const Solver& sv, const Group& gr, const ApplyArgs& x, hipStream_t s) {
+    const bool stream = stream_blocks(sv, sizeof(Tin), x.m);
+    const GroupArgs ga = group_args(sv, gr, ApplyShape<Tin, NB>::EPB, x.color);
+    if constexpr (sizeof(Tin) == 8 && full_order(NB)) {
+        // from about eight elements a compute unit on (a tile of the other form holds one); at p = 4
+        // streamed loads want the wider ones (times at the kernel)
+        static_assert(ApplyShape<Tin, NB>::EPB == 1, "tiles count elements");
+        if (ga.ntiles >= 2048 && !(NB == 100 && stream))
+            return apply_form<Tin, NB, true>(sv, group_args(sv, gr, ApplyShape<Tin, NB, true>::EPB, x.color), stream, x, s);
+    }
+    return apply_form<Tin, NB, false>(sv, ga, stream, x, s);
 }
 
 template <class Tin>
