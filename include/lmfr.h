@@ -272,9 +272,10 @@ fr_status fr_set_option(fr_ctx ctx, const char* name, int64_t value);
 /* Choose the launch shape (workgroup width: elements per workgroup, persistent grid
  * size, tile order across XCDs) of the residual, JVP and Newton-operator kernels by timing the candidates on the
  * device with a free-stream state; block-column assembly takes the Newton operator's
- * shape.  cache_path (may be NULL): text file of earlier choices keyed by GPU
- * architecture, order, viscous/moving flags, mode and element-count bucket; entries
- * found there are used without timing, new ones are appended.  Synchronises `stream`.
+ * shape.  cache_path (may be NULL): text file of earlier choices keyed by a format tag, GPU
+ * architecture, order, viscous/moving/affine/boundary flags, mode and element-count bucket;
+ * entries found there are used without timing, new ones are appended, and entries of
+ * earlier formats (timed with other kernels) are left alone.  Synchronises `stream`.
  * The choice affects speed only: every shape computes the same values bit for bit. */
 fr_status fr_autotune(fr_ctx ctx, const char* cache_path, void* stream);
 

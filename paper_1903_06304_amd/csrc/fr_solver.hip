@@ -499,6 +499,10 @@ std::string arch_name(int dev) {
     return s;
 }
 
+// What the timings of a shape depend on.  TUNE_FORMAT names the kernels and the meaning of the stored
+// numbers: entries under another one were timed with other kernels (and a grid of 0 among them once
+// meant one workgroup per tile), so they are not taken.
+const char* const TUNE_FORMAT = "t2";
 std::string tune_key(const std::string& arch, const Solver& sv, const Group& g, int mode) {
     long long E = 0;
     for (long long e : g.elems) E += e;
@@ -507,8 +511,8 @@ std::string tune_key(const std::string& arch, const Solver& sv, const Group& g, 
     bool aff = true;   // all-affine groups run other kernel variants
     for (int id : g.ids) aff = aff && sv.cs[id]->all_affine;
     std::ostringstream o;
-    o << arch << " p" << g.p << " v" << g.visc << " m" << g.mov << " a" << (aff ? 1 : 0) << " mode" << mode
-      << " e2^" << bucket;
+    o << TUNE_FORMAT << " " << arch << " p" << g.p << " v" << g.visc << " m" << g.mov << " a" << (aff ? 1 : 0) << " b"
+      << (g.bnd ? 1 : 0) << " mode" << mode << " e2^" << bucket;
     return o.str();
 }
 
