@@ -10,7 +10,7 @@
 //      the unused row with the largest |a(r, k)| as pivot row p: one DPP maximum over integer keys,
 //      the leading bits of |a| above 127 - row (two entries that agree to 2^-13 count as a tie,
 //      which goes to the lower row);
-//   2. the owners of row p put it into LDS, and everyone applies a(r, c) -= a(r, k) / a(p, k) a(p, c).
+//   2. the owners of row p put it into LDS, and everyone applies a(r, c) -= a(r, k) a(p, c) / a(p, k).
 // Row p and column k of the in-place inverse come out of the same update: the row is zeroed in
 // its owners and its multiplier is 1 / a(p, k), the column is zeroed and its entry of the row is 1.
 // Register columns move down by one once the CT columns of register 0 have been pivots: the last
@@ -116,6 +116,11 @@ k_block_invert(GroupArgs ga, const double* __restrict__ blk, TO* __restrict__ in
                const int* __restrict__ flags, int cl) {
     using M = Map<NB, NW>;
     constexpr int TR = M::TR, CT = M::CT, RPT = NB / TR, CPT = NB / CT, NTH = 64 * NW;
+    // The reciprocal pivot multiplies the pivot row (ROW) or the column.  The row's products round to
+    // errors 3 to 7% smaller in the mean of |B X - 1|, those of the elimination in panels at one panel;
+    // the larger blocks are below their panels' errors with the column too (0.3 to 0.95 times), which
+    // is a multiplication less in six to ten
+    constexpr bool ROW = NB <= 36;
     static_assert(RPT * TR == NB && CPT * CT == NB && RPT % 2 == 0 && CPT % 2 == 0, "whole pairs");
     static_assert(NB <= 127 && TR * CT <= NTH, "row numbers in 7 bits");
     typedef TC V2 __attribute__((ext_vector_type(2)));
@@ -209,11 +214,18 @@ k_block_invert(GroupArgs ga, const double* __restrict__ blk, TO* __restrict__ in
         const TC ip = TC(1) / pv;
         TC g[RPT];
 #pragma unroll
-        for (int a = 0; a < RPT; ++a) g[a] = own_r == pq && a == pa ? ip : -f[a / 2][a % 2] * ip;
+        for (int a = 0; a < RPT; ++a) {
+            const bool own = own_r == pq && a == pa;
+            if (ROW) g[a] = own ? TC(1) : -f[a / 2][a % 2];
+            else g[a] = own ? ip : -f[a / 2][a % 2] * ip;
+        }
         group_sync<NW>();
         V2 y[CPT / 2];
 #pragma unroll
-        for (int i = 0; i < CPT / 2; ++i) y[i] = s_row[tc * (CPT / 2) + i];
+        for (int i = 0; i < CPT / 2; ++i) {
+            y[i] = s_row[tc * (CPT / 2) + i];
+            if (ROW) y[i] *= ip;
+        }
         TC c0[RPT];
 #pragma unroll
         for (int b = 0; b < CPT; ++b)
