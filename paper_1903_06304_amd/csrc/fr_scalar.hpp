@@ -78,20 +78,22 @@ template <int K> FR_HD Dual<K> fma_(double a, const Dual<K>& b, const Dual<K>& c
     for (int k = 0; k < K; ++k) r.d[k] = fma(a, b.d[k], c.d[k]); return r; }
 
 // ---- elementary functions
-// square root g and half its reciprocal h = 1 / (2 sqrt(x)) from the hardware estimate of 1/sqrt(x)
-// (2^-23): coupled Newton steps for both (Goldschmidt's iteration), then a residual step for g and
-// one for h, each below an ulp.  For normal x > 0; anything else but +0 gives no usable value, +0 and
-// negatives NaN.  (sqrt() and a division took 17 and 12 more instructions.)
-__device__ __forceinline__ void fsqrt_both(double x, double& g, double& h) {
-    const double y = __builtin_amdgcn_rsq(x);
+// square root g and half its reciprocal h = 1 / (2 sqrt(x)) from an estimate y of 1/sqrt(x) good to
+// 2^-23: coupled Newton steps for both (Goldschmidt's iteration), then a residual step for g, which
+// equals sqrt(x) but for an ulp in rare cases (none of 50 million), and a Newton step for h on that g:
+// no further off than 0.5 / sqrt(x) rounded twice, 1.5 ulp.  For normal x > 0; zeros, negatives and infinities give NaN (the callers' quantities
+// are not finite there in any case).  sqrt() and a division took 17 and 12 more instructions.
+FR_HD void sqrt_steps(double x, double y, double& g, double& h) {
     g = x * y;
     h = 0.5 * y;
-    double r = fma(-h, g, 0.5);
+    const double r = fma(-h, g, 0.5);
     g = fma(g, r, g);
     h = fma(h, r, h);
     g = fma(fma(-g, g, x), h, g);
-    r = fma(-h, g, 0.5);
-    h = fma(h, r, h);
+    h = fma(h, fma(-h, g + g, 1.0), h);
+}
+__device__ __forceinline__ void fsqrt_both(double x, double& g, double& h) {
+    sqrt_steps(x, __builtin_amdgcn_rsq(x), g, h);
 }
 __device__ __forceinline__ double ssqrt(double x) {
     double g, h;
