@@ -290,11 +290,10 @@ static bool is_tile_option(const char* name) {
     return !strcmp(name, "tile_lanes") || !strcmp(name, "tile_grid") || !strcmp(name, "tile_xcd");
 }
 
-// linearisation packs and the R of the pass that writes them
+// linearisation packs
 static fr_status ensure_packs(Solver& sv) {
     FR_TRY(dalloc(&sv.d_fpack, sv.fpack_len));
-    FR_TRY(dalloc(&sv.d_spack, sv.spack_len));
-    return dalloc(&sv.d_rscratch, sv.Ntot);
+    return dalloc(&sv.d_spack, sv.spack_len);
 }
 
 // solver options shared by contexts and batches; returns FR_EINVAL with no message for
@@ -343,7 +342,10 @@ extern "C" fr_status fr_set_option(fr_ctx c, const char* name, int64_t value) {
     Solver& sv = *c->self;
     if (!strcmp(name, "keep_blocks")) { sv.keep_blocks = value != 0; return FR_OK; }
     if (!strcmp(name, "operator_packs")) {
-        if (value) FR_TRY(ensure_packs(sv));
+        if (value) {
+            FR_TRY(ensure_packs(sv));
+            FR_TRY(dalloc(&sv.d_rscratch, sv.Ntot));   // R of the pass that writes them
+        }
         sv.op_packs = value != 0;
         return FR_OK;
     }
@@ -432,9 +434,10 @@ extern "C" fr_status fr_block_jacobi_factor(fr_ctx c, const double* q, double c_
     KArgs a{};
     a.c_time = c_time; a.inv_dtau = inv_dtau;
     sv.f_ct = c_time; sv.f_idt = inv_dtau;
-    // linearisation packs of q, from which the blocks are written down
+    // linearisation packs of q, from which the blocks are written down; the R that comes with them
+    // goes where the blocks will be (4 Np of an element's 16 Np^2 entries)
     FR_TRY(ensure_packs(sv));
-    KArgs p = plain_args(q, nullptr, sv.d_rscratch, nullptr);
+    KArgs p = plain_args(q, nullptr, sv.d_blk, nullptr);
     p.fpack = sv.d_fpack; p.spack = sv.d_spack;
     FR_TRY(solver_fused(sv, MODE_PREP, p, s));
     a.fpack = sv.d_fpack; a.spack = sv.d_spack;
