@@ -938,11 +938,11 @@ k_fused_aff(GroupArgs ga, KArgs a, OpTab op) {
 
 // Newton operator Av = inv_dtau Gamma v + c_time M v - J v from the linearisation packs of
 // the state (MODE_LIN).  Every stage that is linear in the state (gradients, traces,
-// interpolation, divergence, lifting) acts on the tangent v alone, so LDS holds doubles;
-// the nonlinear point functions (common flux, point flux) run on dual numbers whose
-// values come from the packs.  The tangent arithmetic is the dual-number arithmetic of
-// the other modes term by term (same sums in the same order); the result matches MODE_AOP
-// to a few ulp, where the compiler contracts different products into fused multiply-adds.
+// interpolation, divergence, lifting) acts on the tangent v alone, so LDS holds doubles.  Of the
+// point functions the inviscid fluxes run on dual numbers whose values come from the packs; the
+// viscous ones, linear but for the work of the stresses, are tangents formed from the packed
+// velocities and stresses.  The result matches MODE_AOP to rounding (1e-12 of the largest entry in
+// the tests): the viscous sums and the common velocity are formed in another order.
 template <int P, bool VISC, bool MOV, int LANES, bool BLK, bool BC, bool CS = false>
 __global__ void __launch_bounds__((Shape<P, LANES>::threads))
 k_lin(GroupArgs ga, KArgs a, OpTab op) {
@@ -1586,12 +1586,13 @@ int resident_workgroups(int threads) {
 // Grid of a launch, a multiple of 8 (the XCD count) so that every XCD walks an equal tile range: the
 // tuned size if there is one, else one workgroup per tile.  resident (the workgroups that the device
 // holds at a time, 0: not given): where they get tile counts that differ little (nine tenths of the
-// last round filled), that many workgroups stay and walk the tiles: they load the operators once and
-// ask for the next tile's connectivity a tile ahead.  Given for the general kernels of J v and of the
-// Newton operator, which run one or two waves a SIMD with little to hide a tile's start: J v, 256 x 256
-// curved elements, 126 us at p = 3 (139 with a workgroup per tile), 275 at p = 4 (297).  Not for the
-// others: the affine J v at p = 4 loses (124 for 118), a residual of 255 x 129 curved elements with
-// its 4,112 tiles in five even rounds of 823 takes 48.6 us for 42.2.
+// last round filled), that many workgroups stay, walk the tiles and load the operators once.  Given
+// for the general kernels of J v and of the Newton operator, which run one or two waves a SIMD with
+// little to hide a workgroup's start: J v, 256 x 256 curved elements, 126 us at p = 3 (139 with a
+// workgroup per tile), 275 at p = 4 (297).  Not for the others, which gain at some sizes and lose more
+// at others: over 64 residuals from 100 x 100 elements on 0.93 to 1.17 times, 1.010 in the mean (p = 3
+// curved 192 x 192 48.0 us for 44.5, p = 4 affine 256 x 256 84.7 for 78.4), J v with R 0.92 to 1.15
+// times, 0.992 in the mean (p = 3 Euler 255 x 129 45.2 for 41.2), the affine J v at p = 4 124 for 117.
 inline unsigned grid_of(int ntiles, int grid, int resident) {
     long long g = grid > 0 && grid < ntiles ? grid : ntiles;
     if (grid == 0 && resident > 0 && ntiles > resident) {

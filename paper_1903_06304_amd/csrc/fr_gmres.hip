@@ -18,8 +18,8 @@
 // too.  The sequence is captured into hipGraphs once and replayed: the Arnoldi steps in segments,
 // then the cycle's end.  The host keeps one segment queued behind the one that runs and
 // stops launching them when a segment that has ended reports every case stopped; it synchronises
-// once per cycle to read one "needs another cycle" flag per case.  The Newton loop (paper Sec. 3.2) keeps per-case convergence on the device
-// as well and synchronises once per Newton iteration.
+// once per cycle to read one "needs another cycle" flag per case.  The Newton loop (paper Sec. 3.2)
+// keeps per-case convergence on the device as well and synchronises once per Newton iteration.
 #include <cmath>
 #include <cstring>
 
@@ -269,8 +269,9 @@ fr_status bdf_op(const Solver& sv, const double* q, const double* v, double* Av,
 // join of the graph costs about 20 us a step; side by side the kernels of ten launches and more, each
 // too small for the chip, save more than that.  BDF2 steps of batches, ms, in branches (one after the
 // other): 5 groups, Jacobi 42.0 (45.2), 6 groups 31.6 (35.7); symmetric Gauss-Seidel, 4 groups 27.5
-// (33.7), 6 groups 49.1 (63.1); not taken: 3 groups, forward sweeps 16.8 (14.8), 4 groups, Jacobi 29.9
-// (28.1), 5 groups of 8 x 8 cases 28.4 (27.4).
+// (33.7), 6 groups 49.1 (63.1); forward sweeps, 4 groups of cases up to 96 x 96 18.0 (19.5) and 27.8
+// (32.5), up to 32 x 32 16.2 (17.8) and 16.6 (16.4); not taken: 3 groups, forward sweeps 16.8 (14.8), 4
+// groups, Jacobi 29.9 (28.1), 5 groups of 8 x 8 cases 28.4 (27.4).
 bool in_branches(const Solver& sv) {
     const int ng = (int)sv.groups.size(), K = sv.ncolors;
     const int each = sv.precond == 0 ? 2 : sv.precond == 1 ? 4 * K - 2 : 2 * K;
